@@ -3,8 +3,8 @@
 //   x = (-1)^sign * (sum_q limb_q 2^(64 q)) * 2^(exp - p),  mantissa normalised,
 // stored as one plane per limb (limb q of element idx at limb[q*plane + idx]).
 //
-//   (S1) k_limb_row_exp / k_limb_col_exp: e = max exp over the non-zero
-//        entries of a row of A / a column of B;
+//   (S1) k_limb_exponents: e = max exp over the non-zero entries of a row of
+//        A / a column of B (small products: in the producer);
 //   (S2)+(S3) k_producer_limbs: X = sgn(x) trunc(|x| 2^mu) is never formed;
 //        every w-bit slice window is read straight from the limb planes
 //        (negative values as the complement plus an incoming carry of one)
@@ -27,56 +27,34 @@
 #include "ozii_bytes.hpp"
 #include "ozii_elem.hpp"
 #include "ozii_kernels.hpp"
+#include "ozii_stage.hpp"
 
 using namespace ozk;
+using ozl::LimbOperand;
 
 namespace {
 
-constexpr int LIMB_ROWEXP_CHUNK = 16;
-
-// ---------------------------------------------------------------------------
-// (S1)
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_limb_row_exp(const uint64_t *__restrict__ limb,
-                                                      const int32_t *__restrict__ lexp, int64_t ld,
-                                                      int64_t plane, int nlimb, int64_t rows,
-                                                      int64_t cols, int32_t *e) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= rows) return;
-  const int64_t h0 = (int64_t)blockIdx.y * LIMB_ROWEXP_CHUNK;
-  const int64_t h1 = h0 + LIMB_ROWEXP_CHUNK < cols ? h0 + LIMB_ROWEXP_CHUNK : cols;
-  int32_t best = EXP_ZERO;
-  for (int64_t h = h0; h < h1; ++h) {
-    const int64_t idx = i + h * ld;
-    if (limb[(int64_t)(nlimb - 1) * plane + idx] != 0) {
-      const int32_t v = lexp[idx];
-      best = v > best ? v : best;
-    }
-  }
-  if (best != EXP_ZERO) atomicMax(e + i, best);
+// exponent of the entry at idx (EXP_ZERO for zero)
+__device__ __forceinline__ int32_t limb_exponent(const LimbOperand &X, int nlimb, int64_t idx) {
+  return X.limb[(int64_t)(nlimb - 1) * X.plane + idx] != 0 ? X.lexp[idx] : EXP_ZERO;
 }
 
-__global__ __launch_bounds__(256) void k_limb_col_exp(const uint64_t *__restrict__ limb,
-                                                      const int32_t *__restrict__ lexp, int64_t ld,
-                                                      int64_t plane, int nlimb, int64_t rows,
-                                                      int64_t cols, int32_t *e) {
-  const int lane = threadIdx.x & 63;
-  const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= cols) return;
-  int32_t best = EXP_ZERO;
-  for (int64_t h = lane; h < rows; h += 64) {
-    const int64_t idx = h + j * ld;
-    if (limb[(int64_t)(nlimb - 1) * plane + idx] != 0) {
-      const int32_t v = lexp[idx];
-      best = v > best ? v : best;
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const int32_t o = __shfl_xor(best, off, 64);
-    best = o > best ? o : best;
-  }
-  if (lane == 0) e[j] = best;
+// ---------------------------------------------------------------------------
+// (S1), both operands in one launch as k_exponents of the expansion product:
+// the first ga workgroups take rba rows of A each, the others rbb columns of B
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_limb_exponents(LimbOperand A, LimbOperand B, int nlimb,
+                                                        int64_t K, int ga, int rba, int rbb) {
+  __shared__ int32_t sm[64];
+  const bool isa = (int)blockIdx.x < ga;
+  const LimbOperand X = isa ? A : B;
+  const int rb = isa ? rba : rbb;
+  const int64_t o0 = (int64_t)(isa ? blockIdx.x : blockIdx.x - ga) * rb;
+  const int64_t so = isa ? 1 : X.ld, sh = isa ? X.ld : 1;
+  const int32_t v = block_exponents(
+      [&](int64_t o, int64_t h) { return limb_exponent(X, nlimb, o * so + h * sh); }, isa, o0,
+      X.nout, K, rb, sm);
+  if ((int)threadIdx.x < rb && o0 + threadIdx.x < X.nout) X.exps[o0 + threadIdx.x] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -139,15 +117,19 @@ __device__ __forceinline__ void emit_f64_residues(const uint32_t (&F)[4][NWM],
   }
 }
 
-template <int NWM, bool F64>
-__global__ __launch_bounds__(256) void k_producer_limbs(
-    const uint64_t *__restrict__ limb, const int32_t *__restrict__ lexp,
-    const uint8_t *__restrict__ lsign, int64_t ld, int64_t plane, int nlimb, int rowwise,
-    int64_t nout, int64_t K, int64_t KB, const int32_t *__restrict__ exps,
-    const DevPlan *__restrict__ pl, uint8_t *__restrict__ planes, int64_t plane_elems) {
+template <int NWM, bool F64, bool OWN>
+__global__ __launch_bounds__(256) void k_producer_limbs(LimbOperand A, LimbOperand B, int nlimb,
+                                                        int64_t K, int64_t KB, int oba,
+                                                        const DevPlan *__restrict__ pl) {
   constexpr int NLL = (NWM + 3) / 2;  // limbs covering NWM + 2 words
   const int T = threadIdx.x;
-  const int64_t kb = blockIdx.x, ob = blockIdx.y;
+  const uint32_t oy = blockIdx.x / (uint32_t)KB;
+  const bool isa = (int)oy < oba;
+  const LimbOperand X = isa ? A : B;
+  const uint64_t *__restrict__ limb = X.limb;
+  const int64_t ld = X.ld, plane = X.plane, nout = X.nout, plane_elems = X.plane_elems;
+  uint8_t *planes = (uint8_t *)X.planes;
+  const int64_t kb = blockIdx.x - oy * (uint32_t)KB, ob = isa ? oy : oy - oba;
   const int64_t o = ob * 16 + ((T >> 2) & 15);
   const int64_t h0 = kb * 64 + 16 * (T >> 6) + 4 * (T & 3);
   const uint32_t offb = (uint32_t)((ob * KB + kb) * 1024 + 4 * T);  // < 2^31
@@ -158,7 +140,22 @@ __global__ __launch_bounds__(256) void k_producer_limbs(
   const int l1 = ((int)blockIdx.z + 1) * nmod / (int)gridDim.z;
 
   int32_t ex = EXP_ZERO;
-  if (o < nout) ex = exps[o];
+  if constexpr (OWN) {
+    // the workgroup finds the exponents of its 16 outputs itself
+    __shared__ int32_t sm[64], sex[16];
+    const int64_t so = isa ? 1 : ld, sh_ = isa ? ld : 1;
+    const int32_t v = block_exponents(
+        [&](int64_t oo, int64_t h) { return limb_exponent(X, nlimb, oo * so + h * sh_); }, isa,
+        ob * 16, nout, K, 16, sm);
+    if (T < 16) {
+      sex[T] = v;
+      if (kb == 0 && blockIdx.z == 0 && ob * 16 + T < nout) X.exps[ob * 16 + T] = v;
+    }
+    __syncthreads();
+    if (o < nout) ex = sex[(T >> 2) & 15];
+  } else {
+    if (o < nout) ex = X.exps[o];
+  }
   int64_t idx[4];
   int32_t sh[4];
   uint32_t neg[4], live[4], cin[4];
@@ -170,15 +167,15 @@ __global__ __launch_bounds__(256) void k_producer_limbs(
     live[e] = 0;
     const int64_t h = h0 + e;
     if (ex != EXP_ZERO && h < K) {
-      const int64_t id = rowwise ? o + h * ld : h + o * ld;
+      const int64_t id = isa ? o + h * ld : h + o * ld;
       if (limb[(int64_t)(nlimb - 1) * plane + id] != 0) {
-        const int64_t s = (int64_t)lexp[id] - p + (Q - 1 - (int64_t)ex);
+        const int64_t s = (int64_t)X.lexp[id] - p + (Q - 1 - (int64_t)ex);
         // below -(p + 64) every bit of the value is truncated away
         if (s > -(int64_t)(p + 64)) {
           live[e] = 1;
           sh[e] = (int32_t)s;
           idx[e] = id;
-          neg[e] = lsign[id] & 1u;
+          neg[e] = X.lsign[id] & 1u;
         }
       }
     }
@@ -564,62 +561,69 @@ __global__ void k_limb_zero(uint64_t *limb, int32_t *lexp, uint8_t *lsign, int64
 
 namespace ozl {
 
-hipError_t launch_limb_exponents(const uint64_t *limb, const int32_t *lexp, int64_t ld,
-                                 int64_t plane, int nlimb, int64_t rows, int64_t cols,
-                                 int rowwise, int32_t *e, hipStream_t s) {
-  if (rowwise) {
-    if (rows <= 0) return hipSuccess;
-    hipError_t err = launch_fill_int(e, EXP_ZERO, rows, s);
-    if (err != hipSuccess || cols <= 0) return err;
-    dim3 g((unsigned)((rows + 255) / 256),
-           (unsigned)((cols + LIMB_ROWEXP_CHUNK - 1) / LIMB_ROWEXP_CHUNK));
-    hipLaunchKernelGGL(k_limb_row_exp, g, dim3(256), 0, s, limb, lexp, ld, plane, nlimb, rows,
-                       cols, e);
-  } else {
-    if (cols <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_limb_col_exp, dim3((unsigned)((cols + 3) / 4)), dim3(256), 0, s, limb,
-                       lexp, ld, plane, nlimb, rows, cols, e);
-  }
+hipError_t launch_limb_exponents(const LimbOperand &A, const LimbOperand &B, int nlimb, int64_t K,
+                                 hipStream_t s) {
+  if (A.nout <= 0 && B.nout <= 0) return hipSuccess;
+  const int rba = exponent_rb(A.nout), rbb = exponent_rb(B.nout);
+  const int64_t ga = (A.nout + rba - 1) / rba, gb = (B.nout + rbb - 1) / rbb;
+  hipLaunchKernelGGL(k_limb_exponents, dim3((unsigned)(ga + gb)), dim3(256), 0, s, A, B, nlimb, K,
+                     (int)ga, rba, rbb);
   return hipGetLastError();
 }
 
-template <bool F64>
-static void producer_limbs_nw(int nwt, dim3 g, hipStream_t s, const uint64_t *limb,
-                              const int32_t *lexp, const uint8_t *lsign, int64_t ld,
-                              int64_t plane, int nlimb, int rowwise, int64_t nout, int64_t K,
-                              int64_t KB, const int32_t *exps, const DevPlan *pl, uint8_t *planes,
-                              int64_t plane_elems) {
-  if (nwt <= 4)
-    hipLaunchKernelGGL((k_producer_limbs<4, F64>), g, dim3(256), 0, s, limb, lexp, lsign, ld,
-                       plane, nlimb, rowwise, nout, K, KB, exps, pl, planes, plane_elems);
-  else if (nwt <= 6)
-    hipLaunchKernelGGL((k_producer_limbs<6, F64>), g, dim3(256), 0, s, limb, lexp, lsign, ld,
-                       plane, nlimb, rowwise, nout, K, KB, exps, pl, planes, plane_elems);
-  else
-    hipLaunchKernelGGL((k_producer_limbs<REC_PWMAX, F64>), g, dim3(256), 0, s, limb, lexp, lsign,
-                       ld, plane, nlimb, rowwise, nout, K, KB, exps, pl, planes, plane_elems);
+// Grid of the limb producer over both operands: KB (OBA + OBB) blocks, and
+// the moduli split over up to 8 parts while the blocks alone give fewer than
+// 4096 wavefronts (four per SIMD).  own: small products find their exponents
+// in the producer; the scans touch a limb and an exponent per element.
+struct LProdGrid {
+  int64_t KB, OBA;
+  dim3 g;
+  bool own;
+};
+static LProdGrid lprod_grid(const LimbOperand &A, const LimbOperand &B, int64_t K, int64_t Kp,
+                            int nmod) {
+  LProdGrid r{};
+  r.KB = Kp / 64;
+  r.OBA = A.noutp / 16;
+  const int64_t nb = r.KB * (r.OBA + B.noutp / 16);
+  r.g = dim3((unsigned)nb, 1, (unsigned)std::max<int64_t>(1, std::min<int64_t>({8, (int64_t)nmod,
+                                                                   (4096 + 4 * nb - 1) / (4 * nb)})));
+  r.own = nb * (int64_t)r.g.z * 16 * K * 12 <= OWN_EXP_BYTES;
+  return r;
 }
 
-hipError_t launch_producer_limbs(const uint64_t *limb, const int32_t *lexp, const uint8_t *lsign,
-                                 int64_t ld, int64_t plane, int nlimb, int rowwise, int64_t nout,
-                                 int64_t noutp, int64_t K, int64_t Kp, const int32_t *exps,
-                                 const DevPlan *pl, int nmod, int nwt, int kind, void *planes,
-                                 int64_t plane_elems, hipStream_t s) {
-  const int64_t KB = Kp / 64, OB = noutp / 16;
-  if (KB <= 0 || OB <= 0) return hipSuccess;
-  if (plane_elems >= ((int64_t)1 << 31) || nwt > REC_PWMAX) return hipErrorInvalidValue;
+bool producer_limbs_owns_exponents(const LimbOperand &A, const LimbOperand &B, int64_t K,
+                                   int64_t Kp, int nmod) {
+  return lprod_grid(A, B, K, Kp, nmod).own;
+}
+
+template <bool F64, bool OWN>
+static void producer_limbs_nw(int nwt, const LProdGrid &G, hipStream_t s, const LimbOperand &A,
+                              const LimbOperand &B, int nlimb, int64_t K, const DevPlan *pl) {
+#define OZ_PRODL(NWM_)                                                                             \
+  hipLaunchKernelGGL((k_producer_limbs<NWM_, F64, OWN>), G.g, dim3(256), 0, s, A, B, nlimb, K, \
+                     G.KB, (int)G.OBA, pl)
+  if (nwt <= 4) OZ_PRODL(4);
+  else if (nwt <= 6) OZ_PRODL(6);
+  else OZ_PRODL(REC_PWMAX);
+#undef OZ_PRODL
+}
+
+hipError_t launch_producer_limbs(const LimbOperand &A, const LimbOperand &B, int nlimb, int64_t K,
+                                 int64_t Kp, const DevPlan *pl, int nmod, int nwt, int kind,
+                                 hipStream_t s) {
+  if (Kp < 64 || A.noutp + B.noutp < 16) return hipSuccess;
+  if (std::max(A.plane_elems, B.plane_elems) >= ((int64_t)1 << 31) || nwt > REC_PWMAX)
+    return hipErrorInvalidValue;
   if (kind != PLANES_I8 && kind != PLANES_F64) return hipErrorInvalidValue;
-  // split the moduli over up to 8 parts while the blocks alone give fewer
-  // than 4096 wavefronts (four per SIMD)
-  dim3 g((unsigned)KB, (unsigned)OB,
-         (unsigned)std::max<int64_t>(1, std::min<int64_t>({8, (int64_t)nmod,
-                                                            (4096 + 4 * KB * OB - 1) / (4 * KB * OB)})));
-  if (kind == PLANES_F64)
-    producer_limbs_nw<true>(nwt, g, s, limb, lexp, lsign, ld, plane, nlimb, rowwise, nout, K, KB,
-                            exps, pl, (uint8_t *)planes, plane_elems);
-  else
-    producer_limbs_nw<false>(nwt, g, s, limb, lexp, lsign, ld, plane, nlimb, rowwise, nout, K, KB,
-                             exps, pl, (uint8_t *)planes, plane_elems);
+  const LProdGrid G = lprod_grid(A, B, K, Kp, nmod);
+  if (kind == PLANES_F64) {
+    if (G.own) producer_limbs_nw<true, true>(nwt, G, s, A, B, nlimb, K, pl);
+    else producer_limbs_nw<true, false>(nwt, G, s, A, B, nlimb, K, pl);
+  } else {
+    if (G.own) producer_limbs_nw<false, true>(nwt, G, s, A, B, nlimb, K, pl);
+    else producer_limbs_nw<false, false>(nwt, G, s, A, B, nlimb, K, pl);
+  }
   return hipGetLastError();
 }
 

@@ -24,6 +24,7 @@
 #include "ozii_stage.hpp"
 
 using namespace ozk;
+using ozl::Operand;
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
@@ -32,24 +33,6 @@ namespace {
 // ---------------------------------------------------------------------------
 // (S1) exponents
 // ---------------------------------------------------------------------------
-// Row maxima: a 2-D grid, each thread scans a chunk of one row and the chunk
-// maxima meet in e[i] through an atomic max (e pre-filled with EXP_ZERO).
-constexpr int ROWEXP_CHUNK = 16;
-template <int NC>
-__global__ __launch_bounds__(256) void k_row_exponents(const double *A, int64_t lda, int64_t rows,
-                                                       int64_t cols, int32_t *e) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= rows) return;
-  const int64_t h0 = (int64_t)blockIdx.y * ROWEXP_CHUNK;
-  const int64_t h1 = h0 + ROWEXP_CHUNK < cols ? h0 + ROWEXP_CHUNK : cols;
-  int32_t best = EXP_ZERO;
-  for (int64_t h = h0; h < h1; ++h) {
-    int32_t v = exponent_of<NC>(A + (i + h * lda) * NC);
-    best = v > best ? v : best;
-  }
-  if (best != EXP_ZERO) atomicMax(e + i, best);
-}
-
 // C = 0 for an M x N matrix of nc-component expansions (leading dimension
 // ldc), one double per thread
 __global__ __launch_bounds__(256) void k_zero_expansions(double *C, int64_t ldc, int64_t rows,
@@ -61,28 +44,25 @@ __global__ __launch_bounds__(256) void k_zero_expansions(double *C, int64_t ldc,
   C[j * ldc * nc + r] = 0.0;
 }
 
-__global__ void k_fill_i32(int32_t *p, int32_t v, int64_t cnt) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t < cnt) p[t] = v;
-}
-
+// Both operands in one launch, no pre-filled output and no atomics: the first
+// ga workgroups take rba rows of A each, the others rbb columns of B.  Bound
+// by latency on small operands, by HBM on large ones.  With the two
+// producers merged into one launch as well (separate fill, row, column and
+// two producer launches before): QD 1792 x 1792 x 256 update 516 -> 475 us,
+// DD 777 x 1001 x 333 product 130 -> 116 us on MI355X.
 template <int NC>
-__global__ __launch_bounds__(256) void k_col_exponents(const double *B, int64_t ldb, int64_t rows,
-                                                       int64_t cols, int32_t *e) {
-  const int lane = threadIdx.x & 63;
-  int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (j >= cols) return;
-  int32_t best = EXP_ZERO;
-  for (int64_t h = lane; h < rows; h += 64) {
-    int32_t v = exponent_of<NC>(B + (h + j * ldb) * NC);
-    best = v > best ? v : best;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    int32_t o = __shfl_xor(best, off, 64);
-    best = o > best ? o : best;
-  }
-  if (lane == 0) e[j] = best;
+__global__ __launch_bounds__(256) void k_exponents(Operand A, Operand B, int64_t K, int ga, int rba,
+                                                   int rbb) {
+  __shared__ int32_t sm[64];
+  const bool isa = (int)blockIdx.x < ga;
+  const Operand X = isa ? A : B;
+  const int rb = isa ? rba : rbb;
+  const int64_t o0 = (int64_t)(isa ? blockIdx.x : blockIdx.x - ga) * rb;
+  const int64_t so = isa ? NC : X.ld * NC, sh = isa ? X.ld * NC : NC;
+  const int32_t v = block_exponents(
+      [&](int64_t o, int64_t h) { return exponent_at<NC>(X.X + o * so + h * sh); }, isa, o0, X.nout,
+      K, rb, sm);
+  if ((int)threadIdx.x < rb && o0 + threadIdx.x < X.nout) X.exps[o0 + threadIdx.x] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -110,22 +90,48 @@ __global__ __launch_bounds__(256) void k_col_exponents(const double *B, int64_t 
 // floor(acc/m) is exact as the high word of (acc << k) * ceil(2^(32-k)/m):
 // acc < 2^(32-k)/m and (acc << k) < 2^24 hold for w <= 300.
 // ---------------------------------------------------------------------------
-template <int NC, int NWX, int NWM, int PL, int EPT>
-__global__ __launch_bounds__(256) void k_producer_b(const double *__restrict__ X, int64_t ld,
-                                                    int rowwise, int64_t nout, int64_t K,
-                                                    int64_t KB, const int32_t *__restrict__ exps,
-                                                    const DevPlan *__restrict__ pl,
-                                                    uint8_t *__restrict__ planes,
-                                                    int64_t plane_elems) {
+//
+// One launch covers both operands: output blocks below oba are row blocks of
+// A, the others column blocks of B; blockIdx.x = output block * (KB, EPT = 1:
+// 4 KB) + inner block.  OWN: the workgroup first finds the exponents
+// of its 16 outputs itself (every workgroup of an output block repeats the
+// scan, the first stores them for the consumer), which saves the exponent
+// launch of small products: QD 16 x 16 x 16 43.9 -> 25.5 us with three
+// launches instead of seven.
+template <int NC, int NWX, int NWM, int PL, int EPT, bool OWN>
+__global__ __launch_bounds__(256) void k_producer_b(Operand A, Operand B, int64_t K, int64_t KB,
+                                                    int oba, const DevPlan *__restrict__ pl) {
   // blockIdx.z: a part of the moduli (small products run several parts to
   // fill the chip; each part repeats the conversion and slicing).  EPT = 1:
-  // four workgroups per block, blockIdx.x = 4 kb + quarter.
+  // four workgroups per block.
+  const uint32_t per = (uint32_t)KB * (EPT == 4 ? 1u : 4u);
+  const uint32_t oy = blockIdx.x / per, kx = blockIdx.x - oy * per;
+  const bool isa = (int)oy < oba;
+  const Operand X = isa ? A : B;
+  const int64_t ob = isa ? oy : oy - oba;
   const int nmod = pl->nmod, np = (int)gridDim.z, part = (int)blockIdx.z;
-  const int64_t kb = EPT == 4 ? (int64_t)blockIdx.x : (int64_t)(blockIdx.x >> 2);
-  const int T = EPT == 4 ? (int)threadIdx.x : (int)(((blockIdx.x & 3u) << 8) + threadIdx.x);
-  produce_block_b<NC, NWX, NWM, PL, EPT>(X, ld, rowwise, nout, K, KB, exps, pl, planes,
-                                         plane_elems, kb, blockIdx.y, T, part * nmod / np,
-                                         (part + 1) * nmod / np);
+  const int64_t kb = EPT == 4 ? (int64_t)kx : (int64_t)(kx >> 2);
+  const int T = EPT == 4 ? (int)threadIdx.x : (int)(((kx & 3u) << 8) + threadIdx.x);
+  const int32_t *exps = X.exps;
+  int64_t eoff = 0;
+  if constexpr (OWN) {
+    __shared__ int32_t sm[64], sex[16];
+    const int64_t so = isa ? NC : X.ld * NC, sh = isa ? X.ld * NC : NC;
+    const int32_t v = block_exponents(
+        [&](int64_t o, int64_t h) { return exponent_at<NC>(X.X + o * so + h * sh); }, isa, ob * 16,
+        X.nout, K, 16, sm);
+    if (threadIdx.x < 16) {
+      sex[threadIdx.x] = v;
+      const int64_t o = ob * 16 + threadIdx.x;
+      if (kx == 0 && part == 0 && o < X.nout) X.exps[o] = v;
+    }
+    __syncthreads();
+    exps = sex;
+    eoff = ob * 16;
+  }
+  produce_block_b<NC, NWX, NWM, PL, EPT>(X.X, X.ld, isa, X.nout, K, KB, exps, pl,
+                                         (uint8_t *)X.planes, X.plane_elems, kb, ob, T,
+                                         part * nmod / np, (part + 1) * nmod / np, eoff);
 }
 
 // Producer: one workgroup fills one 16-row x 64-k window of every plane.
@@ -137,14 +143,19 @@ __global__ __launch_bounds__(256) void k_producer_b(const double *__restrict__ X
 //   PL_F64: residues as doubles, 1 KiB blocks of 16 rows x 8 k (lane l: row
 //           l%16, k l/16 and 4 + l/16), eight blocks per window.
 template <int NC, int NWX, int NH, int PL>
-__global__ __launch_bounds__(256) void k_producer(const double *X, int64_t ld, int rowwise,
-                                                  int64_t nout, int64_t K, int64_t KB,
-                                                  const int32_t *exps, const DevPlan *pl,
-                                                  void *planes, int64_t plane_elems) {
+__global__ __launch_bounds__(256) void k_producer(Operand A, Operand B, int64_t K, int64_t KB,
+                                                  int oba, const DevPlan *pl) {
   __shared__ uint32_t stage[256 * STG];
+  const uint32_t oy = blockIdx.x / (uint32_t)KB;
+  const bool isa = (int)oy < oba;
+  const Operand op = isa ? A : B;
+  const double *X = op.X;
+  const int64_t ld = op.ld, nout = op.nout, plane_elems = op.plane_elems;
+  const int32_t *exps = op.exps;
+  void *planes = op.planes;
   uint32_t *st = stage + threadIdx.x * STG;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t kb = blockIdx.x, ob = blockIdx.y;
+  const int64_t kb = blockIdx.x - oy * (uint32_t)KB, ob = isa ? oy : oy - oba;
   const int nmod = pl->nmod, Q = pl->Q;
   for (int q = 0; q < 4; ++q) {
     int64_t o, h, off;
@@ -165,7 +176,7 @@ __global__ __launch_bounds__(256) void k_producer(const double *X, int64_t ld, i
     if (o < nout && h < K) {
       const int32_t ex = exps[o];
       if (ex != EXP_ZERO) {
-        src = rowwise ? X + (o + h * ld) * NC : X + (h + o * ld) * NC;
+        src = isa ? X + (o + h * ld) * NC : X + (h + o * ld) * NC;
         mu = Q - 1 - ex;
       }
     }
@@ -1152,123 +1163,98 @@ hipError_t launch_zero_expansions(int nc, double *C, int64_t ldc, int64_t M, int
   return hipGetLastError();
 }
 
-hipError_t launch_exponents(int nc, const double *X, int64_t ld, int64_t rows, int64_t cols,
-                            int rowwise, int32_t *e, hipStream_t s) {
-  if (rowwise) {
-    if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, e,
-                       EXP_ZERO, rows);
-    if (cols <= 0) return hipGetLastError();
-    dim3 g((unsigned)((rows + 255) / 256), (unsigned)((cols + ROWEXP_CHUNK - 1) / ROWEXP_CHUNK));
-    if (nc == 2) hipLaunchKernelGGL(k_row_exponents<2>, g, dim3(256), 0, s, X, ld, rows, cols, e);
-    else if (nc == 3) hipLaunchKernelGGL(k_row_exponents<3>, g, dim3(256), 0, s, X, ld, rows, cols, e);
-    else hipLaunchKernelGGL(k_row_exponents<4>, g, dim3(256), 0, s, X, ld, rows, cols, e);
-  } else {
-    if (cols <= 0) return hipSuccess;
-    dim3 g((unsigned)((cols + 3) / 4));
-    if (nc == 2) hipLaunchKernelGGL(k_col_exponents<2>, g, dim3(256), 0, s, X, ld, rows, cols, e);
-    else if (nc == 3) hipLaunchKernelGGL(k_col_exponents<3>, g, dim3(256), 0, s, X, ld, rows, cols, e);
-    else hipLaunchKernelGGL(k_col_exponents<4>, g, dim3(256), 0, s, X, ld, rows, cols, e);
-  }
+hipError_t launch_exponents(int nc, const Operand &A, const Operand &B, int64_t K, hipStream_t s) {
+  if (A.nout <= 0 && B.nout <= 0) return hipSuccess;
+  const int rba = exponent_rb(A.nout), rbb = exponent_rb(B.nout);
+  const int64_t ga = (A.nout + rba - 1) / rba, gb = (B.nout + rbb - 1) / rbb;
+  dim3 g((unsigned)(ga + gb));
+  if (nc == 2) hipLaunchKernelGGL(k_exponents<2>, g, dim3(256), 0, s, A, B, K, (int)ga, rba, rbb);
+  else if (nc == 3) hipLaunchKernelGGL(k_exponents<3>, g, dim3(256), 0, s, A, B, K, (int)ga, rba, rbb);
+  else hipLaunchKernelGGL(k_exponents<4>, g, dim3(256), 0, s, A, B, K, (int)ga, rba, rbb);
   return hipGetLastError();
 }
 
-template <int NC, int NWX, int PL>
-static void producer_nh(int nh, dim3 g, hipStream_t s, const double *X, int64_t ld, int rowwise,
-                        int64_t nout, int64_t K, int64_t KB, const int32_t *exps,
-                        const DevPlan *pl, void *planes, int64_t plane_elems) {
-  if (nh <= 8)
-    hipLaunchKernelGGL((k_producer<NC, NWX, 8, PL>), g, dim3(256), 0, s, X, ld, rowwise, nout, K,
-                       KB, exps, pl, planes, plane_elems);
-  else if (nh <= 12)
-    hipLaunchKernelGGL((k_producer<NC, NWX, 12, PL>), g, dim3(256), 0, s, X, ld, rowwise, nout, K,
-                       KB, exps, pl, planes, plane_elems);
-  else
-    hipLaunchKernelGGL((k_producer<NC, NWX, NHMAX, PL>), g, dim3(256), 0, s, X, ld, rowwise, nout,
-                       K, KB, exps, pl, planes, plane_elems);
+// Grid of the producers over both operands: KB (OBA + OBB) blocks, moduli parts.
+struct ProdGrid {
+  int64_t KB, OBA, OB;
+  dim3 g;
+  bool fine, own;
+};
+
+// Byte back-ends on products too small to give 4096 wavefronts (four per
+// SIMD): one element per thread, then the moduli split over up to 8 parts.
+// Small products also find their exponents in the producer (own).
+static ProdGrid prod_grid(int nc, const Operand &A, const Operand &B, int64_t K, int64_t Kp,
+                          int nmod, bool bytes) {
+  ProdGrid r{};
+  r.KB = Kp / 64;
+  r.OBA = A.noutp / 16;
+  r.OB = r.OBA + B.noutp / 16;
+  r.fine = bytes && r.KB * r.OB * 4 < 4096;
+  const int64_t waves = r.KB * r.OB * (r.fine ? 16 : 4);
+  r.g = dim3((unsigned)(r.KB * (r.fine ? 4 : 1) * r.OB));
+  if (bytes) r.g.z = (unsigned)std::max<int64_t>(1, std::min<int64_t>({8, nmod, (4096 + waves - 1) / waves}));
+  // bytes that the workgroups' own scans touch: 16 outputs x K elements each
+  const int64_t scan = (int64_t)r.g.x * r.g.z * 16 * K * 8 * nc;
+  r.own = r.fine && scan <= OWN_EXP_BYTES;
+  return r;
 }
 
-template <int NC, int NWX, int PL, int EPT>
-static void producer_b_ept(int nwt, dim3 g, hipStream_t s, const double *X, int64_t ld,
-                           int rowwise, int64_t nout, int64_t K, int64_t KB, const int32_t *exps,
-                           const DevPlan *pl, uint8_t *P, int64_t plane_elems) {
-  if (nwt <= 4)
-    hipLaunchKernelGGL((k_producer_b<NC, NWX, 4, PL, EPT>), g, dim3(256), 0, s, X, ld, rowwise,
-                       nout, K, KB, exps, pl, P, plane_elems);
-  else if (nwt <= 6)
-    hipLaunchKernelGGL((k_producer_b<NC, NWX, 6, PL, EPT>), g, dim3(256), 0, s, X, ld, rowwise,
-                       nout, K, KB, exps, pl, P, plane_elems);
-  else
-    hipLaunchKernelGGL((k_producer_b<NC, NWX, REC_PWMAX, PL, EPT>), g, dim3(256), 0, s, X, ld,
-                       rowwise, nout, K, KB, exps, pl, P, plane_elems);
+bool producer_owns_exponents(int nc, const Operand &A, const Operand &B, int64_t K, int64_t Kp,
+                             int nmod, int kind) {
+  return kind != PLANES_F64 && prod_grid(nc, A, B, K, Kp, nmod, true).own;
 }
 
-// g: (KB, OB, moduli parts); fine: one element per thread (four workgroups
-// per block) for products too small to fill the chip otherwise
-template <int NC, int NWX, int PL>
-static void producer_b_nw(int nwt, bool fine, dim3 g, hipStream_t s, const double *X, int64_t ld,
-                          int rowwise, int64_t nout, int64_t K, int64_t KB, const int32_t *exps,
-                          const DevPlan *pl, void *planes, int64_t plane_elems) {
-  uint8_t *P = (uint8_t *)planes;
-  if (fine) {
-    g.x *= 4;
-    producer_b_ept<NC, NWX, PL, 1>(nwt, g, s, X, ld, rowwise, nout, K, KB, exps, pl, P, plane_elems);
-  } else {
-    producer_b_ept<NC, NWX, PL, 4>(nwt, g, s, X, ld, rowwise, nout, K, KB, exps, pl, P, plane_elems);
-  }
+template <int NC, int NWX>
+static void producer_f64(int nh, const ProdGrid &G, hipStream_t s, const Operand &A,
+                         const Operand &B, int64_t K, const DevPlan *pl) {
+#define OZ_PRODF(NH_)                                                                            \
+  hipLaunchKernelGGL((k_producer<NC, NWX, NH_, PL_F64>), G.g, dim3(256), 0, s, A, B, K, G.KB, \
+                     (int)G.OBA, pl)
+  if (nh <= 8) OZ_PRODF(8);
+  else if (nh <= 12) OZ_PRODF(12);
+  else OZ_PRODF(NHMAX);
+#undef OZ_PRODF
 }
 
-template <int PL>
-static void producer_b(int nc, int nwx, int nwt, bool fine, dim3 g, hipStream_t s, const double *X,
-                       int64_t ld, int rowwise, int64_t nout, int64_t K, int64_t KB,
-                       const int32_t *exps, const DevPlan *pl, void *planes,
-                       int64_t plane_elems) {
-#define OZ_PRODB(NC_, NWX_)                                                                     \
-  producer_b_nw<NC_, NWX_, PL>(nwt, fine, g, s, X, ld, rowwise, nout, K, KB, exps, pl, planes, \
-                               plane_elems)
-  if (nc == 2) { if (nwx <= 8) OZ_PRODB(2, 8); else OZ_PRODB(2, 12); }
-  else if (nc == 3) { if (nwx <= 8) OZ_PRODB(3, 8); else OZ_PRODB(3, 12); }
-  else { if (nwx <= 8) OZ_PRODB(4, 8); else OZ_PRODB(4, 12); }
+template <int NC, int NWX, int PL, int EPT, bool OWN>
+static void producer_b_nwt(int nwt, const ProdGrid &G, hipStream_t s, const Operand &A,
+                           const Operand &B, int64_t K, const DevPlan *pl) {
+#define OZ_PRODB(NWM_)                                                                             \
+  hipLaunchKernelGGL((k_producer_b<NC, NWX, NWM_, PL, EPT, OWN>), G.g, dim3(256), 0, s, A, B, K, \
+                     G.KB, (int)G.OBA, pl)
+  if (nwt <= 4) OZ_PRODB(4);
+  else if (nwt <= 6) OZ_PRODB(6);
+  else OZ_PRODB(REC_PWMAX);
 #undef OZ_PRODB
 }
 
-template <int PL>
-static void producer_pl(int nc, int nwx, int nh, dim3 g, hipStream_t s, const double *X,
-                        int64_t ld, int rowwise, int64_t nout, int64_t K, int64_t KB,
-                        const int32_t *exps, const DevPlan *pl, void *planes,
-                        int64_t plane_elems) {
-#define OZ_PROD(NC_, NWX_) \
-  producer_nh<NC_, NWX_, PL>(nh, g, s, X, ld, rowwise, nout, K, KB, exps, pl, planes, plane_elems)
+template <int NC, int NWX, int PL>
+static void producer_b(int nwt, const ProdGrid &G, hipStream_t s, const Operand &A,
+                       const Operand &B, int64_t K, const DevPlan *pl) {
+  if (G.own) producer_b_nwt<NC, NWX, PL, 1, true>(nwt, G, s, A, B, K, pl);
+  else if (G.fine) producer_b_nwt<NC, NWX, PL, 1, false>(nwt, G, s, A, B, K, pl);
+  else producer_b_nwt<NC, NWX, PL, 4, false>(nwt, G, s, A, B, K, pl);
+}
+
+hipError_t launch_producer(int nc, int nwx, int nh, int nwt, const Operand &A, const Operand &B,
+                           int64_t K, int64_t Kp, const DevPlan *pl, int nmod, int kind,
+                           hipStream_t s) {
+  const ProdGrid G = prod_grid(nc, A, B, K, Kp, nmod, kind != PLANES_F64);
+  if (G.KB <= 0 || G.OB <= 0) return hipSuccess;
+  // the byte producer addresses a plane with 32-bit offsets
+  if (kind != PLANES_F64 && std::max(A.plane_elems, B.plane_elems) >= ((int64_t)1 << 31))
+    return hipErrorInvalidValue;
+#define OZ_PROD(NC_, NWX_)                                                                \
+  do {                                                                                    \
+    if (kind == PLANES_F8) producer_b<NC_, NWX_, PL_F8>(nwt, G, s, A, B, K, pl);          \
+    else if (kind == PLANES_F64) producer_f64<NC_, NWX_>(nh, G, s, A, B, K, pl);          \
+    else producer_b<NC_, NWX_, PL_I8>(nwt, G, s, A, B, K, pl);                            \
+  } while (0)
   if (nc == 2) { if (nwx <= 8) OZ_PROD(2, 8); else OZ_PROD(2, 12); }
   else if (nc == 3) { if (nwx <= 8) OZ_PROD(3, 8); else OZ_PROD(3, 12); }
   else { if (nwx <= 8) OZ_PROD(4, 8); else OZ_PROD(4, 12); }
 #undef OZ_PROD
-}
-
-hipError_t launch_producer(int nc, int nwx, int nh, int nwt, const double *X, int64_t ld, int rowwise,
-                           int64_t nout, int64_t noutp, int64_t K, int64_t Kp,
-                           const int32_t *exps, const DevPlan *pl, int nmod, int backend,
-                           void *planes,
-                           int64_t plane_elems, hipStream_t s) {
-  const int64_t KB = Kp / 64, OB = noutp / 16;
-  if (KB <= 0 || OB <= 0) return hipSuccess;
-  // the byte producer addresses a plane with 32-bit offsets
-  if (backend != PLANES_F64 && plane_elems >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-  dim3 g((unsigned)KB, (unsigned)OB);
-  // byte back-ends on products too small to give 4096 wavefronts (four per
-  // SIMD): one element per thread, then the moduli split over up to 8 parts
-  const bool fine = KB * OB * 4 < 4096;
-  const int64_t waves = KB * OB * (fine ? 16 : 4);
-  dim3 gb = g;
-  gb.z = (unsigned)std::max<int64_t>(1, std::min<int64_t>({8, nmod, (4096 + waves - 1) / waves}));
-  if (backend == PLANES_F8)
-    producer_b<PL_F8>(nc, nwx, nwt, fine, gb, s, X, ld, rowwise, nout, K, KB, exps, pl, planes,
-                      plane_elems);
-  else if (backend == PLANES_F64)
-    producer_pl<PL_F64>(nc, nwx, nh, g, s, X, ld, rowwise, nout, K, KB, exps, pl, planes, plane_elems);
-  else
-    producer_b<PL_I8>(nc, nwx, nwt, fine, gb, s, X, ld, rowwise, nout, K, KB, exps, pl, planes,
-                      plane_elems);
   return hipGetLastError();
 }
 

@@ -688,22 +688,16 @@ ozII_status gemm_impl(ozII_ctx *h, int mode, int nc, int64_t M, int64_t N, int64
   // algorithmic bytes of the residue planes and t-planes of this back-end
   const double res_bytes = (double)hp->S * hp->nmod * hp->planes_per() * hp->el_bytes();
   const double t_bytes = (double)hp->ng * hp->nmod * hp->t_bytes();
-  {
+  const ozl::Operand opA{A, lda, M, L.Mp, ea, pa, L.planeA}, opB{B, ldb, N, L.Np, eb, pb, L.planeB};
+  if (!ozl::producer_owns_exponents(nc, opA, opB, K, L.Kp, hp->nmod, hp->planes_kind())) {
     ProfScope ps(h, OZ_STAGE_EXP, 8.0 * nc * (double)(M * K + K * N), 0, s);
-    if ((e = ozl::launch_exponents(nc, A, lda, M, K, 1, ea, s)) != hipSuccess) return hip_fail(h, e, "exponents(A)");
-    if ((e = ozl::launch_exponents(nc, B, ldb, K, N, 0, eb, s)) != hipSuccess) return hip_fail(h, e, "exponents(B)");
+    if ((e = ozl::launch_exponents(nc, opA, opB, K, s)) != hipSuccess) return hip_fail(h, e, "exponents");
   }
   {
-    ProfScope ps(h, OZ_STAGE_PRODUCER, (double)M * K * (8.0 * nc + res_bytes), 0, s);
-    if ((e = ozl::launch_producer(nc, hp->nwx, hp->nh, (hp->w + 2 + 31) / 32, A, lda, 1, M, L.Mp, K, L.Kp, ea, dp,
-                                  hp->nmod, hp->planes_kind(), pa, L.planeA, s)) != hipSuccess)
-      return hip_fail(h, e, "producer(A)");
-  }
-  {
-    ProfScope ps(h, OZ_STAGE_PRODUCER, (double)N * K * (8.0 * nc + res_bytes), 0, s);
-    if ((e = ozl::launch_producer(nc, hp->nwx, hp->nh, (hp->w + 2 + 31) / 32, B, ldb, 0, N, L.Np, K, L.Kp, eb, dp,
-                                  hp->nmod, hp->planes_kind(), pb, L.planeB, s)) != hipSuccess)
-      return hip_fail(h, e, "producer(B)");
+    ProfScope ps(h, OZ_STAGE_PRODUCER, (double)(M + N) * K * (8.0 * nc + res_bytes), 0, s);
+    if ((e = ozl::launch_producer(nc, hp->nwx, hp->nh, (hp->w + 2 + 31) / 32, opA, opB, K, L.Kp, dp,
+                                  hp->nmod, hp->planes_kind(), s)) != hipSuccess)
+      return hip_fail(h, e, "producer");
   }
   // (S4)-(S6) fused: the t-values of a tile stay in LDS (INT8, no stage copies)
   if (o && (o->flags & OZII_F_FUSED) && hp->backend == OZII_BE_INT8 && !ea_out && !eb_out &&
@@ -836,26 +830,18 @@ ozII_status gemm_limbs_impl(ozII_ctx *h, int mode, int nlimb, int64_t M, int64_t
   const double in_bytes = 8.0 * nlimb + 5.0;  // limbs, exponent and sign per element
   const double res_bytes = (double)hp->S * hp->nmod * hp->el_bytes(),
                t_bytes = (double)hp->ng * hp->nmod * hp->t_bytes();
-  {
+  const ozl::LimbOperand opA{A->limb, A->exp, A->sign, A->ld, A->plane, M, L.Mp, ea, pa, L.planeA},
+      opB{B->limb, B->exp, B->sign, B->ld, B->plane, N, L.Np, eb, pb, L.planeB};
+  if (!ozl::producer_limbs_owns_exponents(opA, opB, K, L.Kp, hp->nmod)) {
     ProfScope ps(h, OZ_STAGE_EXP, 12.0 * (double)(M * K + K * N), 0);
-    if ((e = ozl::launch_limb_exponents(A->limb, A->exp, A->ld, A->plane, nlimb, M, K, 1, ea, s)) != hipSuccess)
-      return hip_fail(h, e, "limb exponents(A)");
-    if ((e = ozl::launch_limb_exponents(B->limb, B->exp, B->ld, B->plane, nlimb, K, N, 0, eb, s)) != hipSuccess)
-      return hip_fail(h, e, "limb exponents(B)");
+    if ((e = ozl::launch_limb_exponents(opA, opB, nlimb, K, s)) != hipSuccess)
+      return hip_fail(h, e, "limb exponents");
   }
   {
-    ProfScope ps(h, OZ_STAGE_PRODUCER, (double)M * K * (in_bytes + res_bytes), 0);
-    if ((e = ozl::launch_producer_limbs(A->limb, A->exp, A->sign, A->ld, A->plane, nlimb, 1, M,
-                                        L.Mp, K, L.Kp, ea, dp, hp->nmod, nwt, hp->planes_kind(), pa,
-                                        L.planeA, s)) != hipSuccess)
-      return hip_fail(h, e, "limb producer(A)");
-  }
-  {
-    ProfScope ps(h, OZ_STAGE_PRODUCER, (double)N * K * (in_bytes + res_bytes), 0);
-    if ((e = ozl::launch_producer_limbs(B->limb, B->exp, B->sign, B->ld, B->plane, nlimb, 0, N,
-                                        L.Np, K, L.Kp, eb, dp, hp->nmod, nwt, hp->planes_kind(), pb,
-                                        L.planeB, s)) != hipSuccess)
-      return hip_fail(h, e, "limb producer(B)");
+    ProfScope ps(h, OZ_STAGE_PRODUCER, (double)(M + N) * K * (in_bytes + res_bytes), 0);
+    if ((e = ozl::launch_producer_limbs(opA, opB, nlimb, K, L.Kp, dp, hp->nmod, nwt,
+                                        hp->planes_kind(), s)) != hipSuccess)
+      return hip_fail(h, e, "limb producer");
   }
   {
     ProfScope ps(h, OZ_STAGE_GEMM, res_bytes * (double)(M + N) * K + t_bytes * M * N,

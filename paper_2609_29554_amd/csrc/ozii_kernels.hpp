@@ -40,14 +40,28 @@ inline int gemm_tile_auto(int64_t prods, int64_t Mp, int64_t Np) {
 hipError_t launch_zero_expansions(int nc, double *C, int64_t ldc, int64_t M, int64_t N,
                                   hipStream_t s);
 // Ozaki-II product stages
-hipError_t launch_exponents(int nc, const double *X, int64_t ld, int64_t rows, int64_t cols,
-                            int rowwise, int32_t *e, hipStream_t s);
+// One operand of a product: A (rows are the outputs) or B (columns are).
+// noutp: outputs padded to the GEMM tile, the rows of its residue planes.
+struct Operand {
+  const double *X;
+  int64_t ld, nout, noutp;
+  int32_t *exps;
+  void *planes;
+  int64_t plane_elems;
+};
+// operand scans of at most this many bytes stay in the producer: they then
+// cost less than the launch they save
+constexpr int64_t OWN_EXP_BYTES = (int64_t)16 << 20;
+// (S1) of both operands; not needed where the producer finds the exponents
+hipError_t launch_exponents(int nc, const Operand &A, const Operand &B, int64_t K, hipStream_t s);
+bool producer_owns_exponents(int nc, const Operand &A, const Operand &B, int64_t K, int64_t Kp,
+                             int nmod, int kind);
 // plane encodings of the producer (one per back-end)
 enum { PLANES_I8 = 0, PLANES_F8 = 1, PLANES_F64 = 2 };
-hipError_t launch_producer(int nc, int nwx, int nh, int nwt, const double *X, int64_t ld, int rowwise,
-                           int64_t nout, int64_t noutp, int64_t K, int64_t Kp,
-                           const int32_t *exps, const DevPlan *pl, int nmod, int planes_kind,
-                           void *planes, int64_t plane_elems, hipStream_t s);
+// (S2)+(S3) of both operands in one launch
+hipError_t launch_producer(int nc, int nwx, int nh, int nwt, const Operand &A, const Operand &B,
+                           int64_t K, int64_t Kp, const DevPlan *pl, int nmod, int kind,
+                           hipStream_t s);
 hipError_t launch_gemm_i8(const int8_t *pa, const int8_t *pb, uint8_t *tpl, const DevPlan *pl,
                           int ng, int nmod, int64_t Mp, int64_t Np, int64_t Kp, int64_t planeA,
                           int64_t planeB, int tile, hipStream_t s);
@@ -106,16 +120,22 @@ hipError_t launch_fill_int(int *p, int v, int64_t cnt, hipStream_t s);
 // cw[k M N + i + j M]), the rounding of those sums into a limb matrix, the
 // update C = RN_p(C - T) (T: M x N limb matrix with ld M, plane M N; dw:
 // 2 nlimb + 2 words per element of scratch) and a zero fill
-hipError_t launch_limb_exponents(const uint64_t *limb, const int32_t *lexp, int64_t ld,
-                                 int64_t plane, int nlimb, int64_t rows, int64_t cols,
-                                 int rowwise, int32_t *e, hipStream_t s);
-// kind: PLANES_I8 (byte residues) or PLANES_F64 (binary64 moduli);
-// tbytes: 1 (byte t-planes) or 4 (binary64 moduli)
-hipError_t launch_producer_limbs(const uint64_t *limb, const int32_t *lexp, const uint8_t *lsign,
-                                 int64_t ld, int64_t plane, int nlimb, int rowwise, int64_t nout,
-                                 int64_t noutp, int64_t K, int64_t Kp, const int32_t *exps,
-                                 const DevPlan *pl, int nmod, int nwt, int kind, void *planes,
-                                 int64_t plane_elems, hipStream_t s);
+struct LimbOperand {
+  const uint64_t *limb;
+  const int32_t *lexp;
+  const uint8_t *lsign;
+  int64_t ld, plane, nout, noutp;
+  int32_t *exps;
+  void *planes;
+  int64_t plane_elems;
+};
+hipError_t launch_limb_exponents(const LimbOperand &A, const LimbOperand &B, int nlimb, int64_t K,
+                                 hipStream_t s);
+bool producer_limbs_owns_exponents(const LimbOperand &A, const LimbOperand &B, int64_t K,
+                                   int64_t Kp, int nmod);
+hipError_t launch_producer_limbs(const LimbOperand &A, const LimbOperand &B, int nlimb, int64_t K,
+                                 int64_t Kp, const DevPlan *pl, int nmod, int nwt, int kind,
+                                 hipStream_t s);
 hipError_t launch_consumer_limbs(const void *tpl, int tbytes, int64_t Mp, int64_t Np, int64_t M,
                                  int64_t N, const DevPlan *pl, int nd, int nvw, uint32_t *cw,
                                  hipStream_t s);

@@ -18,6 +18,61 @@ namespace ozk {
 // Plane encodings of the three back-ends of (S3)/(S4).
 enum { PL_I8 = 0, PL_F8 = 1, PL_F64 = 2 };
 
+// (S1) shared exponents of RB consecutive outputs (rows of A or columns of
+// B) by one 256-thread workgroup: f(o, h) is the exponent of entry h of
+// output o (EXP_ZERO for zero), o < nout, h < K.  RB a power of two up to 64.
+// Consecutive threads take consecutive outputs of a row-wise operand and
+// consecutive inner indices of a column-wise one, so either way a wavefront
+// reads contiguous elements; 256 / RB threads share an output.  Thread t < RB
+// returns the maximum of output o0 + t.  sm: 64 words of LDS.
+template <class F>
+__device__ __forceinline__ int32_t block_exponents(F f, bool rowwise, int64_t o0, int64_t nout,
+                                                   int64_t K, int RB, int32_t *sm) {
+  const int t = (int)threadIdx.x, lane = t & 63, wv = t >> 6, G = 256 / RB;
+  const int r = rowwise ? t % RB : t / G, g = rowwise ? t / RB : t % G;
+  int32_t best = EXP_ZERO;
+  if (o0 + r < nout) {
+#pragma unroll 8
+    for (int64_t h = g; h < K; h += G) {
+      const int32_t v = f(o0 + r, h);
+      best = v > best ? v : best;
+    }
+  }
+  const int lo = rowwise ? RB : 1, hi = rowwise ? 64 : (G < 64 ? G : 64);
+  for (int off = lo; off < hi; off <<= 1) {
+    const int32_t o = __shfl_xor(best, off, 64);
+    best = o > best ? o : best;
+  }
+  // partial maxima per wavefront: RB of them row-wise, 64 / G (or one) column-wise
+  const int per = rowwise ? RB : (G < 64 ? 64 / G : 1);
+  if (rowwise ? lane < RB : lane % (64 / per) == 0) sm[wv * per + (rowwise ? lane : lane * per / 64)] = best;
+  __syncthreads();
+  if (t < RB) {
+    if (rowwise) {
+      best = sm[t];
+      for (int k = 1; k < 4; ++k) best = sm[k * RB + t] > best ? sm[k * RB + t] : best;
+    } else {
+      const int wper = G <= 64 ? 1 : G / 64;  // wavefronts per output
+      best = sm[t * wper];
+      for (int k = 1; k < wper; ++k) best = sm[t * wper + k] > best ? sm[t * wper + k] : best;
+    }
+  }
+  return best;
+}
+
+// Exponent of an expansion in memory: the leading component decides unless
+// it is zero, so the others are only read then.
+template <int NC>
+__device__ __forceinline__ int32_t exponent_at(const double *x) {
+  if (x[0] != 0.0) return exponent_of<1>(x);
+  return exponent_of<NC>(x);
+}
+
+// Outputs per workgroup of the exponent kernels: few on small operands, so
+// that the chip is filled; 16 (whole 128-byte lines at any component count)
+// once 256 workgroups remain.
+inline int exponent_rb(int64_t nout) { return nout >= 4096 ? 16 : (nout >= 512 ? 4 : 1); }
+
 // Producer of the byte back-ends (INT8 residues, FP8 base-17 digits): the
 // caller's threads fill block (ob, kb) -- rows 16 ob .. 16 ob + 15, inner
 // indices 64 kb .. 64 kb + 63 -- of every plane.  EPT = 4: 256 threads,
@@ -43,7 +98,7 @@ __device__ __forceinline__ void produce_block_b(const double *__restrict__ X, in
                                                 const DevPlan *__restrict__ pl,
                                                 uint8_t *__restrict__ planes,
                                                 int64_t plane_elems, int64_t kb, int64_t ob,
-                                                int T, int l0, int l1) {
+                                                int T, int l0, int l1, int64_t eoff = 0) {
   // block byte E0 .. E0 + EPT - 1: byte E is row (E/16)%16, inner index
   // 16(E/256) + 4((E/4)%4) + E%4 of the block
   const int E0 = EPT * T;
@@ -56,7 +111,7 @@ __device__ __forceinline__ void produce_block_b(const double *__restrict__ X, in
 
   uint32_t Xw[EPT][NWX];
   int32_t ex = EXP_ZERO;
-  if (o < nout) ex = exps[o];
+  if (o < nout) ex = exps[o - eoff];  // exps starts at output eoff
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
     const int64_t h = h0 + e;
