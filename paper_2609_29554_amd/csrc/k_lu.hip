@@ -20,21 +20,20 @@ namespace {
 // Exchange between the workgroups of the cooperative panel kernel.
 //
 // Each workgroup owns two 128-byte candidate lines (one per parity of the
-// pivot column): word 0 holds an arrival epoch, the rest the workgroup's
-// pivot candidate for that column -- its row position and physical row, its
-// value in the pivot column and in the next column -- and a buffer crow holds
-// the rest of that row.  A workgroup writes the payload with device-coherent
-// stores, waits for them to complete and then stores the epoch (no release
-// fence, which would write back the whole L2 every column; see
-// cand_arrive).  Readers poll the epochs and read every payload and crow
-// with device-coherent loads, which go past the non-coherent caches, so no
-// cache invalidation is needed on the reading side; they are issued only
-// after the epochs were seen (the wait ends in a workgroup barrier).  Waits
-// are bounded: a timeout raises the sticky error flag, after which every
-// later wait returns at once, so a broken invariant ends the kernel quickly.
+// pivot column) with its pivot candidate for that column -- its row position,
+// its physical row and its value in the pivot column -- and two row buffers
+// with the rest of that row.  Every 8-byte word carries 32 bits of payload
+// and the 32-bit tag of its column, so a reader that sees the tag has the
+// payload: one round trip, no arrival counter, no wait of the writer for its
+// stores and no fence.  Words are written and read with device-coherent
+// 8-byte accesses.  A line is overwritten two columns later, which its owner
+// reaches only after every workgroup has published the column in between,
+// and a workgroup publishes that after it has read all it needs of the first.
+// Tags grow over all panels of a handle (the base is a device word that
+// k_panel_begin advances), so nothing has to be cleared.  Waits are bounded:
+// a timeout raises the sticky error flag and ends the kernel.
 // ---------------------------------------------------------------------------
-constexpr int CAND_WORDS = 32;  // uint32 per candidate line
-constexpr int CAND_KEY = 4;     // first payload word of the key doubles
+constexpr int LINE_WORDS = 16;  // 8-byte words per candidate line
 
 __device__ __forceinline__ uint32_t ld_dev_u32(const uint32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -46,53 +45,34 @@ __device__ __forceinline__ double ld_dev_f64(const double *p) {
   return d;
 }
 
-__device__ __forceinline__ void st_dev_u32(uint32_t *p, uint32_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ uint64_t ld_dev_u64(const uint64_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void st_dev_f64(double *p, double v) {
+__device__ __forceinline__ void st_tagged(uint64_t *p, uint32_t v, uint32_t tag) {
+  __hip_atomic_store(p, ((uint64_t)tag << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// a double as two tagged words, low half first
+__device__ __forceinline__ void st_tagged_f64(uint64_t *p, double v, uint32_t tag) {
   uint64_t u;
   __builtin_memcpy(&u, &v, 8);
-  __hip_atomic_store((uint64_t *)p, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  st_tagged(p, (uint32_t)u, tag);
+  st_tagged(p + 1, (uint32_t)(u >> 32), tag);
+}
+__device__ __forceinline__ double join_f64(uint64_t lo, uint64_t hi) {
+  const uint64_t u = (hi << 32) | (uint32_t)lo;
+  double d;
+  __builtin_memcpy(&d, &u, 8);
+  return d;
 }
 
-// Publish the epoch in this workgroup's candidate line.  Everything the
-// other workgroups read of it (the line's payload, the candidate row) is
-// written with device-coherent stores, so it only has to have completed
-// before the epoch is stored: every wave waits for its own stores
-// (s_waitcnt vmcnt(0)), then the workgroup barrier, then the epoch -- no
-// write-back of the XCD's L2, which a release fence would do every column.
-__device__ __forceinline__ void cand_arrive(uint32_t *line, uint32_t epoch) {
-  __builtin_amdgcn_s_waitcnt(0x0F70);
-  __syncthreads();
-  if (threadIdx.x == 0) st_dev_u32(line, epoch);
-}
-
-// Wait until the lines of all G workgroups (buffer b) carry an epoch of at
-// least `epoch`.  Returns false when the wait failed (timeout now or
-// earlier); the caller must then stop using data published by others.
-__device__ __forceinline__ bool cand_wait(const uint32_t *lines, int G, int b, uint32_t epoch,
-                                          int *err) {
-  __shared__ int s_fail;
-  if ((int)threadIdx.x < G) {
-    // bounded by the 100 MHz real-time counter: about one second
-    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-    uint32_t spins = 0;
-    const uint32_t *f = lines + ((size_t)b * G + threadIdx.x) * CAND_WORDS;
-    // epochs only grow: a workgroup that already arrived for a later epoch
-    // has also arrived for this one
-    while ((int32_t)(ld_dev_u32(f) - epoch) < 0) {
-      if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
-      if ((++spins & 63u) == 0 && __builtin_amdgcn_s_memrealtime() - t0 > 100000000ull) {
-        __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        break;
-      }
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0)
-    s_fail = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-  __syncthreads();
-  return !s_fail;
+// One step of a bounded wait: true when it has to be given up, because about
+// a second has passed (100 MHz real-time counter) or another wait failed.
+__device__ __forceinline__ bool wait_expired(uint32_t &spins, uint64_t t0, int *err) {
+  if ((++spins & 63u) != 0) return false;
+  if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return true;
+  if (__builtin_amdgcn_s_memrealtime() - t0 <= 100000000ull) return false;
+  __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
 }
 
 // Candidate order of the pivot search: larger |value| first, then the lower
@@ -204,31 +184,46 @@ __device__ __forceinline__ int lead_winner(double lead, int nlead, int &w) {
 }
 
 constexpr int PANEL_NT = 512;  // threads per panel workgroup
+constexpr int PANEL_NW = PANEL_NT - 64;  // of these, the ones that apply the updates
+
+// Before a panel: nothing moved yet, and a fresh range of tags (a panel has
+// at most 512 columns).
+__global__ void k_panel_begin(uint32_t *epoch, int *nmoved) {
+  *epoch += 1024u;
+  *nmoved = 0;
+}
 
 // ---------------------------------------------------------------------------
 // (P1) panel.  Panel rows [k, n), columns [k, k+kb).  Workgroup w owns the
 // physical rows k + w*R .. k + w*R + R - 1 and keeps them in LDS for the
 // whole panel.  Rows are never moved during the panel: the row permutation
 // is tracked in LDS (position -> physical row and back, every workgroup
-// keeping an identical copy) and applied once afterwards.  Per column j:
-//   1. wait for every workgroup's candidate for column j (largest |value| in
-//      its active rows, ties to the lowest position) and reduce the table
-//      identically everywhere: the winner is LAPACK's i?amax on the permuted
-//      column;
-//   2. wavefront 0 divides the active rows by the pivot and updates column
-//      j+1 (the candidate line carries the pivot row's value there) while
-//      the other wavefronts fetch the rest of the pivot row;
-//   3. pick the local candidate for column j+1, finish that row's update and
-//      publish it (the critical path), then arrive;
-//   4. update the remaining columns of the other active rows while the other
-//      workgroups arrive.
-// Every element still receives its multiply-subtracts in column order.
+// keeping an identical copy) and applied once afterwards.
+//
+// The columns form one dependent chain, and wavefront 0 of every workgroup
+// walks it alone: per column j it reads the candidates of all workgroups
+// straight into registers as they arrive (largest |value|, ties to the lowest
+// position: LAPACK's i?amax on the permuted column), divides its active rows
+// (one per lane) by the pivot, updates column j+1, picks the local candidate
+// of that column and publishes it.  The other wavefronts fetch the pivot row
+// while it divides, then finish and publish the candidate's row and apply
+// the rank-1 update to the rest, which may last until wavefront 0 has
+// divided the next column.  Two barriers per column: after the division and
+// after the choice of the candidate.  Every element still receives its
+// multiply-subtracts in column order.
+//
+// Bound by the latency of that chain: the exchange across the XCDs (one store
+// and one load), then in QD a division (3.5 us) and a multiply-subtract.
+// getrf on MI355X against the same kernel with an arrival counter, separate
+// payload reads and eight barriers per column: QD n = 2048, b = 128 31.0 ->
+// 25.8 ms, DD n = 130, b = 32 1.07 -> 0.81 ms.
 // ---------------------------------------------------------------------------
 template <int NC>
 __global__ __launch_bounds__(PANEL_NT) void k_panel(double *A, int64_t lda, int64_t n, int64_t k,
                                                     int kb, int R, int64_t *ipiv, int32_t *info,
-                                                    uint32_t *lines, int *err, double *crow,
-                                                    int *perm_out, int *moved, int *nmoved) {
+                                                    uint64_t *lines, int *err, uint64_t *crow,
+                                                    const uint32_t *epoch, int *perm_out,
+                                                    int *moved, int *nmoved) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   // the panel is the critical path of the factorisation, and with
   // look-ahead the previous step's Schur update runs beside it on the same
@@ -237,19 +232,19 @@ __global__ __launch_bounds__(PANEL_NT) void k_panel(double *A, int64_t lda, int6
   const int nr = (int)(n - k);
   const int G = gridDim.x, wg = blockIdx.x, tid = threadIdx.x;
   double *rows = (double *)smem_raw;                 // R * kb * NC
-  double *piv = rows + (size_t)R * kb * NC;          // kb * NC
-  int *sperm = (int *)(piv + (size_t)kb * NC);       // nr
+  double *pivs = rows + (size_t)R * kb * NC;         // 2 * kb * NC, by column parity
+  int *sperm = (int *)(pivs + (size_t)2 * kb * NC);  // nr
   int *sinv = sperm + nr;                            // nr
-  __shared__ double tkey[256][NC], tnxt[256][NC];
-  __shared__ int tpos[256], tidx[256], tphys[256];
-  __shared__ uint32_t active;
-  __shared__ int s_info, s_wi, s_ppos, s_pphys, s_zero, s_best;
+  __shared__ int s_seq, s_fail, s_info, s_best;
+  __shared__ int s_wi[2], s_zero[2];
+  __shared__ uint32_t s_active[2];
 
   const int r0 = wg * R;
   const int cnt = r0 < nr ? (nr - r0 < R ? nr - r0 : R) : 0;
+  const uint32_t tag0 = *epoch + 1u;  // tag of column 0
   auto RW = [&](int r, int c) { return rows + ((size_t)r * kb + c) * NC; };
-  auto LINE = [&](int b, int w) { return lines + ((size_t)b * G + w) * CAND_WORDS; };
-  auto CROW = [&](int b, int w) { return crow + ((size_t)b * G + w) * kb * NC; };
+  auto LINE = [&](int b, int w) { return lines + ((size_t)b * G + w) * LINE_WORDS; };
+  auto CROW = [&](int b, int w) { return crow + ((size_t)b * G + w) * kb * NC * 2; };
 
   for (int idx = tid; idx < cnt * kb; idx += PANEL_NT) {
     const int r = idx % cnt, c = idx / cnt;
@@ -262,267 +257,265 @@ __global__ __launch_bounds__(PANEL_NT) void k_panel(double *A, int64_t lda, int6
     sinv[p] = p;
   }
   if (tid == 0) {
-    active = cnt >= 32 ? 0xffffffffu : ((1u << cnt) - 1u);
+    s_seq = 0;
+    s_fail = 0;
     s_info = 0;
+    s_best = -1;
   }
   __syncthreads();
+  // rows not yet chosen as pivots (wavefront 0)
+  uint32_t active = cnt >= 32 ? 0xffffffffu : ((1u << cnt) - 1u);
 
-  // local candidate for column c among the active rows (thread 0), result in
-  // s_best (local row or -1)
-  auto pick = [&](int c) {
-    if (tid == 0) {
-      int best = -1;
-      double bk[NC];
-      for (int r = 0; r < cnt; ++r) {
-        if (!((active >> r) & 1u)) continue;
-        double x[NC];
-        ozx::load<NC>(RW(r, c), x);
-        bool take = best < 0;
-        if (!take) {
-          if (ozx::abs_greater<NC>(x, bk)) take = true;
-          else if (!ozx::abs_greater<NC>(bk, x) && sinv[r0 + r] < sinv[r0 + best]) take = true;
-        }
-        if (take) {
-          best = r;
+  // wavefront 0, lane r holding row r's value x of column c (live: the row
+  // is active): the local candidate, its line published
+  auto choose = [&](const double (&x)[NC], bool live, int c) {
+    double ck[NC];
+    int cpos = 0x7fffffff, cidx = -1, w = 0;
 #pragma unroll
-          for (int q = 0; q < NC; ++q) bk[q] = x[q];
-        }
-      }
-      s_best = best;
+    for (int q = 0; q < NC; ++q) ck[q] = live ? x[q] : 0.0;
+    if (live) {
+      cpos = sinv[r0 + tid];
+      cidx = tid;
     }
-    __syncthreads();
-  };
-  // publish the candidate of column c (row s_best) into buffer b: the line
-  // payload (position, physical row, values in columns c and c+1) and the
-  // row's columns c+2 .. kb-1 in crow
-  auto publish = [&](int c, int b) {
-    const int best = s_best;
-    uint32_t *ln = LINE(b, wg);
-    if (tid == 0) {
-      double *kv = (double *)(ln + CAND_KEY);
-      if (best >= 0) {
-        st_dev_u32(ln + 1, (uint32_t)sinv[r0 + best]);
-        st_dev_u32(ln + 2, (uint32_t)(r0 + best));
+    const int how = lead_winner(live ? fabs(ck[0]) : -1.0, 1, w);
+    if (how == 1) cidx = w;
+    else if (how == 2) cand_allreduce<NC>(ck, cpos, cidx);
+    else cidx = -1;
+    uint64_t *ln = LINE(c & 1, wg);
+    const uint32_t tag = tag0 + (uint32_t)c;
+    if (tid == (cidx < 0 ? 0 : cidx)) {
+      st_tagged(ln, cidx < 0 ? 0x7fffffffu : (uint32_t)cpos, tag);
+      st_tagged(ln + 1, cidx < 0 ? 0xffffffffu : (uint32_t)(r0 + cidx), tag);
 #pragma unroll
-        for (int q = 0; q < NC; ++q) {
-          st_dev_f64(kv + q, RW(best, c)[q]);
-          st_dev_f64(kv + NC + q, c + 1 < kb ? RW(best, c + 1)[q] : 0.0);
-        }
-      } else {
-        st_dev_u32(ln + 1, 0x7fffffffu);
-        st_dev_u32(ln + 2, 0xffffffffu);
-      }
-    }
-    if (best >= 0) {
-      double *cr = CROW(b, wg);
-      for (int idx = tid; idx < (kb - c - 2) * NC; idx += PANEL_NT)
-        st_dev_f64(cr + (size_t)(c + 2) * NC + idx, RW(best, c + 2)[idx]);
+      for (int q = 0; q < NC; ++q) st_tagged_f64(ln + 2 + 2 * q, x[q], tag);
+      s_best = cidx;
     }
   };
-
-  pick(0);
-  publish(0, 0);
-  cand_arrive(LINE(0, wg), 1u);
+  if (tid < 64) {
+    double x[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) x[q] = tid < cnt ? RW(tid, 0)[q] : 0.0;
+    choose(x, tid < cnt, 0);
+  }
+  __syncthreads();
+  if (s_best >= 0) {
+    uint64_t *cr = CROW(0, wg);
+    for (int idx = NC + tid; idx < kb * NC; idx += PANEL_NT)
+      st_tagged_f64(cr + 2 * (size_t)idx, RW(s_best, 0)[idx], tag0);
+  }
 
   for (int j = 0; j < kb; ++j) {
     const int buf = j & 1;
-    if (!cand_wait(lines, G, buf, (uint32_t)(j + 1), err)) return;
-    // read the candidate table (one line per thread, device-coherent) and
-    // reduce it identically in every workgroup: four entries per lane of the
-    // first wavefront, then a butterfly
-    if (tid < G) {
-      // every device-coherent load first, then the LDS stores: the compiler
-      // keeps atomic loads in program order, so a store between two of them
-      // would make each load wait for the previous one's round trip
-      const uint32_t *ln = LINE(buf, tid);
-      const double *kv = (const double *)(ln + CAND_KEY);
-      const int ph = (int)ld_dev_u32(ln + 2);
-      const int pos = (int)ld_dev_u32(ln + 1);
-      double kk[NC], kn[NC];
+    const uint32_t tag = tag0 + (uint32_t)j;
+    const bool last = j + 1 >= kb;
+    double *piv = pivs + (size_t)buf * kb * NC;
+    double l[NC];  // wavefront 0: this lane's multiplier
 #pragma unroll
-      for (int q = 0; q < NC; ++q) kk[q] = ld_dev_f64(kv + q);
-#pragma unroll
-      for (int q = 0; q < NC; ++q) kn[q] = ld_dev_f64(kv + NC + q);
-      tpos[tid] = pos;
-      tphys[tid] = ph;
-      tidx[tid] = ph >= 0 ? tid : -1;
-#pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        tkey[tid][q] = kk[q];
-        tnxt[tid][q] = kn[q];
-      }
-    }
-    __syncthreads();
+    for (int q = 0; q < NC; ++q) l[q] = 0.0;
+    bool live = false;
     if (tid < 64) {
+      // the best of this lane's lines, two polled at a time
       double bk[NC];
-      int bp = 0x7fffffff, bi = -1;
+      int bp = 0x7fffffff, bi = -1, bph = -1;
 #pragma unroll
       for (int q = 0; q < NC; ++q) bk[q] = 0.0;
-      // leading magnitudes of this lane's entries first; the full order
-      // only when they do not single out the winner
-      double lead = -1.0;
-      int nlead = 0, lb = 0;
-      for (int gi = tid; gi < G; gi += 64) {
-        if (tidx[gi] < 0) continue;
-        const double m = fabs(tkey[gi][0]);
-        if (m != m) lead = m;
-        else if (m > lead) { lead = m; nlead = 1; lb = gi; }
-        else if (m == lead) ++nlead;
-      }
-      int w = 0;
-      const int how = lead_winner(lead, nlead, w);
-      if (how == 1) {
-        bi = __builtin_amdgcn_readlane(lb, w);
-        bp = tpos[bi];
+      bool expired = false;
+      const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+      uint32_t spins = 0;
+      for (int g0 = tid; g0 < G; g0 += 128) {
+        const bool two = g0 + 64 < G;
+        const uint64_t *la = LINE(buf, g0), *lb = LINE(buf, two ? g0 + 64 : g0);
+        uint64_t wa[2 + 2 * NC], wb[2 + 2 * NC];
+        for (;;) {
 #pragma unroll
-        for (int q = 0; q < NC; ++q) bk[q] = tkey[bi][q];
-      } else if (how == 2) {
-        for (int gi = tid; gi < G; gi += 64) {
-          double kk[NC];
+          for (int q = 0; q < 2 + 2 * NC; ++q) wa[q] = ld_dev_u64(la + q);
 #pragma unroll
-          for (int q = 0; q < NC; ++q) kk[q] = tkey[gi][q];
-          if (cand_better<NC>(kk, tpos[gi], tidx[gi], bk, bp, bi)) {
+          for (int q = 0; q < 2 + 2 * NC; ++q) wb[q] = ld_dev_u64(lb + q);
+          bool ok = true;
 #pragma unroll
-            for (int q = 0; q < NC; ++q) bk[q] = kk[q];
-            bp = tpos[gi];
-            bi = tidx[gi];
+          for (int q = 0; q < 2 + 2 * NC; ++q)
+            ok = ok && (uint32_t)(wa[q] >> 32) == tag && (uint32_t)(wb[q] >> 32) == tag;
+          if (ok) break;
+          if (wait_expired(spins, t0, err)) {
+            expired = true;
+            break;
           }
         }
-        cand_allreduce<NC>(bk, bp, bi);
-      }
-      if (tid == 0) {
-        // the winner, and (for a consistent table) the bookkeeping of the
-        // interchange, before the single barrier below
-        const int wi0 = bi, pp0 = bp, ph0 = bi >= 0 ? tphys[bi] : -1;
-        bool z = true;
+        if (expired) break;
+        auto take = [&](const uint64_t (&w)[2 + 2 * NC], int g) {
+          double kk[NC];
 #pragma unroll
-        for (int q = 0; q < NC; ++q) z = z && (bk[q] == 0.0);
-        s_wi = wi0;
-        s_ppos = pp0;
-        s_pphys = ph0;
-        s_zero = z ? 1 : 0;
-        if (!(wi0 < 0 || pp0 < j || pp0 >= nr || ph0 < 0 || ph0 >= nr)) {
+          for (int q = 0; q < NC; ++q) kk[q] = join_f64(w[2 + 2 * q], w[3 + 2 * q]);
+          const int ph = (int)(uint32_t)w[1], pos = (int)(uint32_t)w[0];
+          if (cand_better<NC>(kk, pos, ph >= 0 ? g : -1, bk, bp, bi)) {
 #pragma unroll
-          for (int q = 0; q < NC; ++q) {
-            piv[(size_t)j * NC + q] = tkey[wi0][q];
-            if (j + 1 < kb) piv[(size_t)(j + 1) * NC + q] = tnxt[wi0][q];
+            for (int q = 0; q < NC; ++q) bk[q] = kk[q];
+            bp = pos;
+            bi = g;
+            bph = ph;
           }
+        };
+        take(wa, g0);
+        if (two) take(wb, g0 + 64);
+      }
+      const bool fail = __ballot(expired) != 0;
+      // the winner over the lanes: its entry in every lane
+      int w = 0;
+      const int how = lead_winner(bi >= 0 ? fabs(bk[0]) : -1.0, 1, w);
+      if (how == 2) {
+        int wi = bi;
+        double tk[NC];
+        int tp = bp;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) tk[q] = bk[q];
+        cand_allreduce<NC>(tk, tp, wi);
+        w = __ffsll((unsigned long long)__ballot(bi == wi)) - 1;
+      }
+      const int wi = __builtin_amdgcn_readlane(bi, w), ppos = __builtin_amdgcn_readlane(bp, w);
+      const int pphys = __builtin_amdgcn_readlane(bph, w);
+      double d[NC];
+      bool zero = true;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        d[q] = readlane_f64(bk[q], w);
+        zero = zero && d[q] == 0.0;
+      }
+      // an empty or inconsistent table can only follow a failed wait
+      const bool bad = fail || how == 0 || wi < 0 || ppos < j || ppos >= nr || pphys < 0 || pphys >= nr;
+      if (!bad && pphys >= r0 && pphys < r0 + cnt) active &= ~(1u << (pphys - r0));
+      if (tid == 0) {
+        if (bad) {
+          if (!fail) __hip_atomic_store(err, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          s_fail = 1;
+        } else {
+#pragma unroll
+          for (int q = 0; q < NC; ++q) piv[(size_t)j * NC + q] = d[q];
           const int q = sperm[j];
-          sperm[j] = ph0;
-          sperm[pp0] = q;
-          sinv[ph0] = j;
-          sinv[q] = pp0;
-          if (ph0 >= r0 && ph0 < r0 + cnt) active &= ~(1u << (ph0 - r0));
-          if (z && s_info == 0) s_info = (int)(k + j + 1);
-          if (wg == 0) ipiv[k + j] = k + pp0;
+          sperm[j] = pphys;
+          sperm[ppos] = q;
+          sinv[pphys] = j;
+          sinv[q] = ppos;
+          if (zero && s_info == 0) s_info = (int)(k + j + 1);
+          if (wg == 0) ipiv[k + j] = k + ppos;
+        }
+        s_wi[buf] = bad ? -1 : wi;
+        s_zero[buf] = zero ? 1 : 0;
+        s_active[buf] = active;
+        // the other wavefronts may fetch the pivot row now
+        __hip_atomic_store(&s_seq, j + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      live = !bad && tid < cnt && ((active >> (tid & 31)) & 1u);
+      if (live && !zero) {
+        double a[NC];
+        ozx::load<NC>(RW(tid, j), a);
+        ozx::div<NC>(a, d, l);
+        ozx::store<NC>(RW(tid, j), l);
+      }
+    } else {
+      // columns j+1 .. kb-1 of the pivot row
+      while (__hip_atomic_load(&s_seq, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= j)
+        __builtin_amdgcn_s_sleep(1);
+      const int wi = s_wi[buf];
+      if (wi >= 0) {
+        const uint64_t *cr = CROW(buf, wi) + 2 * (size_t)(j + 1) * NC;
+        double *pd = piv + (size_t)(j + 1) * NC;
+        const int total = (kb - j - 1) * NC;
+        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+        uint32_t spins = 0;
+        constexpr int PF = 2;
+        for (int b0 = tid - 64; b0 < total; b0 += PANEL_NW * PF) {
+          uint64_t lo[PF], hi[PF];
+          bool expired = false;
+          for (;;) {
+            bool ok = true;
+#pragma unroll
+            for (int u = 0; u < PF; ++u) {
+              const int idx = b0 + u * PANEL_NW < total ? b0 + u * PANEL_NW : b0;
+              lo[u] = ld_dev_u64(cr + 2 * (size_t)idx);
+              hi[u] = ld_dev_u64(cr + 2 * (size_t)idx + 1);
+            }
+#pragma unroll
+            for (int u = 0; u < PF; ++u)
+              ok = ok && (uint32_t)(lo[u] >> 32) == tag && (uint32_t)(hi[u] >> 32) == tag;
+            if (ok) break;
+            if (wait_expired(spins, t0, err)) {
+              expired = true;
+              break;
+            }
+          }
+          if (expired) {
+            s_fail = 1;
+            break;
+          }
+#pragma unroll
+          for (int u = 0; u < PF; ++u) {
+            const int idx = b0 + u * PANEL_NW;
+            if (idx < total) pd[idx] = join_f64(lo[u], hi[u]);
+          }
         }
       }
     }
     __syncthreads();
-    const int wi = s_wi, ppos = s_ppos, pphys = s_pphys, zero = s_zero;
-    // an empty or inconsistent table can only follow a failed wait
-    if (wi < 0 || ppos < j || ppos >= nr || pphys < 0 || pphys >= nr) {
-      if (tid == 0) __hip_atomic_store(err, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return;
-    }
-    const bool last = j + 1 >= kb;
+    if (s_fail) return;
+    if (last) break;
+    const int zero = s_zero[buf];
     if (tid < 64) {
-      // wavefront 0: l = a / pivot for the active rows (one per lane, R <=
-      // 32), then column j+1, whose values stay in the lanes: the local
-      // candidate for column j+1 is their butterfly maximum in the pivot
-      // order (the order of pick(), which any reduction tree respects)
-      double ck[NC];
-      int cpos = 0x7fffffff, cidx = -1;
+      // column j+1 of the active rows, and this workgroup's candidate in it
+      double x[NC];
 #pragma unroll
-      for (int q = 0; q < NC; ++q) ck[q] = 0.0;
-      const int r = tid;
-      if (r < cnt && ((active >> r) & 1u)) {
-        double x[NC];
-        if (!last) ozx::load<NC>(RW(r, j + 1), x);
+      for (int q = 0; q < NC; ++q) x[q] = 0.0;
+      if (live) {
+        ozx::load<NC>(RW(tid, j + 1), x);
         if (!zero) {
-          double a[NC], d[NC], l[NC];
-          ozx::load<NC>(RW(r, j), a);
-          ozx::load<NC>(piv + (size_t)j * NC, d);
-          ozx::div<NC>(a, d, l);
-          ozx::store<NC>(RW(r, j), l);
-          if (!last) {
-            double u[NC], o[NC];
-            ozx::load<NC>(piv + (size_t)(j + 1) * NC, u);
-            ozx::fms<NC>(x, l, u, o);
-            ozx::store<NC>(RW(r, j + 1), o);
+          double u[NC], o[NC];
+          ozx::load<NC>(piv + (size_t)(j + 1) * NC, u);
+          ozx::fms<NC>(x, l, u, o);
+          ozx::store<NC>(RW(tid, j + 1), o);
+#pragma unroll
+          for (int q = 0; q < NC; ++q) x[q] = o[q];
+        }
+      }
+      choose(x, live, j + 1);
+    }
+    __syncthreads();
+    if (tid >= 64) {
+      const int best = s_best, width = kb - j - 2;
+      const uint32_t act = s_active[buf];
+      // the candidate's row first, published as it is finished
+      if (best >= 0) {
+        uint64_t *cr = CROW(buf ^ 1, wg);
+        for (int c = j + 2 + tid - 64; c < kb; c += PANEL_NW) {
+          double x[NC];
+          ozx::load<NC>(RW(best, c), x);
+          if (!zero) {
+            double lv[NC], u[NC], o[NC];
+            ozx::load<NC>(RW(best, j), lv);
+            ozx::load<NC>(piv + (size_t)c * NC, u);
+            ozx::fms<NC>(x, lv, u, o);
+            ozx::store<NC>(RW(best, c), o);
 #pragma unroll
             for (int q = 0; q < NC; ++q) x[q] = o[q];
           }
-        }
-        if (!last) {
 #pragma unroll
-          for (int q = 0; q < NC; ++q) ck[q] = x[q];
-          cpos = sinv[r0 + r];
-          cidx = r;
+          for (int q = 0; q < NC; ++q)
+            st_tagged_f64(cr + 2 * ((size_t)c * NC + q), x[q], tag + 1u);
         }
       }
-      if (!last) {
-        int w = 0;
-        const int how = lead_winner(cidx >= 0 ? fabs(ck[0]) : -1.0, 1, w);
-        if (how == 1) cidx = __builtin_amdgcn_readlane(cidx, w);
-        else if (how == 2) cand_allreduce<NC>(ck, cpos, cidx);
-        if (tid == 0) s_best = cidx;
-      }
-    } else {
-      // the other wavefronts: columns j+2 .. kb-1 of the pivot row, PF
-      // loads in flight per thread before their LDS stores (see above)
-      constexpr int PF = 8;
-      const double *cr = CROW(buf, wi) + (size_t)(j + 2) * NC;
-      double *pd = piv + (size_t)(j + 2) * NC;
-      const int total = (kb - j - 2) * NC;
-      for (int b0 = tid - 64; b0 < total; b0 += (PANEL_NT - 64) * PF) {
-        double v[PF];
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-          const int idx = b0 + u * (PANEL_NT - 64);
-          v[u] = idx < total ? ld_dev_f64(cr + idx) : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-          const int idx = b0 + u * (PANEL_NT - 64);
-          if (idx < total) pd[idx] = v[u];
+      // the rest of the rank-1 update
+      if (!zero && width > 0) {
+        for (int idx = tid - 64; idx < cnt * width; idx += PANEL_NW) {
+          const int r = idx % cnt, c = j + 2 + idx / cnt;
+          if (((act >> r) & 1u) && r != best) {
+            double a[NC], lv[NC], u[NC], o[NC];
+            ozx::load<NC>(RW(r, c), a);
+            ozx::load<NC>(RW(r, j), lv);
+            ozx::load<NC>(piv + (size_t)c * NC, u);
+            ozx::fms<NC>(a, lv, u, o);
+            ozx::store<NC>(RW(r, c), o);
+          }
         }
       }
     }
-    __syncthreads();
-    if (last) break;
-    // candidate for column j+1 (s_best, from wavefront 0): finish its row
-    // first, publish, arrive
-    const int best = s_best;
-    const int width = kb - j - 2;
-    if (!zero && best >= 0) {
-      for (int c = j + 2 + tid; c < kb; c += PANEL_NT) {
-        double x[NC], l[NC], u[NC], o[NC];
-        ozx::load<NC>(RW(best, c), x);
-        ozx::load<NC>(RW(best, j), l);
-        ozx::load<NC>(piv + (size_t)c * NC, u);
-        ozx::fms<NC>(x, l, u, o);
-        ozx::store<NC>(RW(best, c), o);
-      }
-      __syncthreads();
-    }
-    publish(j + 1, (j + 1) & 1);
-    cand_arrive(LINE((j + 1) & 1, wg), (uint32_t)(j + 2));
-    // the rest of the rank-1 update, overlapped with the other arrivals
-    if (!zero && width > 0) {
-      for (int idx = tid; idx < cnt * width; idx += PANEL_NT) {
-        const int r = idx % cnt, c = j + 2 + idx / cnt;
-        if (((active >> r) & 1u) && r != best) {
-          double a[NC], l[NC], u[NC], o[NC];
-          ozx::load<NC>(RW(r, c), a);
-          ozx::load<NC>(RW(r, j), l);
-          ozx::load<NC>(piv + (size_t)c * NC, u);
-          ozx::fms<NC>(a, l, u, o);
-          ozx::store<NC>(RW(r, c), o);
-        }
-      }
-    }
-    __syncthreads();
   }
   // write the rows back to their physical places
   for (int idx = tid; idx < cnt * kb; idx += PANEL_NT) {
@@ -1096,8 +1089,10 @@ __global__ void k_fill_int(int *p, int v, int64_t cnt) {
 namespace ozl {
 
 size_t panel_lds_bytes(int nc, int kb, int R, int64_t nr) {
-  return (size_t)R * kb * nc * 8 + (size_t)kb * nc * 8 + (size_t)nr * 8;
+  return (size_t)R * kb * nc * 8 + (size_t)2 * kb * nc * 8 + (size_t)nr * 8;
 }
+
+size_t panel_row_bytes(int kb) { return (size_t)kb * 4 * 16; }
 
 const void *panel_kernel_ptr(int nc) {
   if (nc == 2) return (const void *)k_panel<2>;
@@ -1106,14 +1101,15 @@ const void *panel_kernel_ptr(int nc) {
 }
 
 hipError_t launch_panel(int nc, double *A, int64_t lda, int64_t n, int64_t k, int kb, int R, int G,
-                        int64_t *ipiv, int32_t *info, uint32_t *lines, int *err, double *crow,
-                        int *perm, int *moved, int *nmoved, hipStream_t s) {
+                        int64_t *ipiv, int32_t *info, uint64_t *lines, int *err, uint64_t *crow,
+                        uint32_t *epoch, int *perm, int *moved, int *nmoved, hipStream_t s) {
   const size_t lds = panel_lds_bytes(nc, kb, R, n - k);
   const void *fn = panel_kernel_ptr(nc);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_panel_begin, dim3(1), dim3(1), 0, s, epoch, nmoved);
   void *args[] = {&A, &lda, &n, &k, &kb, &R, &ipiv, &info, &lines, &err,
-                  &crow, &perm, &moved, &nmoved};
+                  &crow, &epoch, &perm, &moved, &nmoved};
   return hipLaunchCooperativeKernel(fn, dim3(G), dim3(PANEL_NT), args, (unsigned)lds, s);
 }
 

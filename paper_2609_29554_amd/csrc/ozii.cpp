@@ -350,9 +350,10 @@ struct ozII_ctx {
   size_t ws_bytes = 0;
   // panel scratch
   uint32_t *bar = nullptr;
-  uint32_t *flags = nullptr;  // panel candidate lines, two 128-byte lines per workgroup
+  uint64_t *lines = nullptr;  // panel candidate lines, two 128-byte lines per workgroup
   int *err = nullptr;
-  double *crow = nullptr;
+  uint64_t *crow = nullptr;   // panel candidate rows
+  uint32_t *epoch = nullptr;  // base of the panels' tags
   int *perm = nullptr, *moved = nullptr, *nmoved = nullptr;
   int64_t panel_n = 0;
   int panel_kb = 0;
@@ -611,10 +612,17 @@ ozII_status ensure_panel(ozII_ctx *h, int64_t n, int kb) {
     if (e == hipSuccess) {
       h->err = (int *)(h->bar + 4);
       h->nmoved = (int *)(h->bar + 8);
+      h->epoch = h->bar + 9;
     }
   }
-  if (e == hipSuccess && !h->flags) e = hipMalloc((void **)&h->flags, 2 * 128 * G);
-  if (e == hipSuccess) e = hipMalloc((void **)&h->crow, sizeof(double) * 2 * G * kk * 4);
+  if (e == hipSuccess && !h->lines) {
+    e = hipMalloc((void **)&h->lines, 2 * 128 * G);
+    if (e == hipSuccess) e = hipMemset(h->lines, 0, 2 * 128 * G);
+  }
+  const size_t crow_bytes = 2 * G * ozl::panel_row_bytes(kk);
+  if (e == hipSuccess) e = hipMalloc((void **)&h->crow, crow_bytes);
+  if (e == hipSuccess) e = hipMemset(h->crow, 0, crow_bytes);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e == hipSuccess) e = hipMalloc((void **)&h->perm, sizeof(int) * nn);
   if (e == hipSuccess) e = hipMalloc((void **)&h->moved, sizeof(int) * nn);
   if (e != hipSuccess) return fail(h, OZII_ENOMEM, "panel scratch allocation failed");
@@ -1097,7 +1105,7 @@ ozII_status ozII_destroy(ozII_handle h) {
   if (h->lcand) hipFree(h->lcand);
   if (h->bar) {
     hipFree(h->bar);
-    hipFree(h->flags);
+    hipFree(h->lines);
     hipFree(h->crow);
     hipFree(h->perm);
     hipFree(h->moved);
@@ -1271,18 +1279,23 @@ ozII_status ozII_getrf(ozII_handle h, int32_t nc, int64_t n, double *A, int64_t 
   for (int64_t k = 0; k < n; k += b) {
     const int kb = (int)std::min<int64_t>(b, n - k);
     const int64_t nr = n - k;
-    // panel geometry: G co-resident workgroups of R rows each.  Fewer,
-    // taller workgroups make the per-column exchange cheaper (every
-    // workgroup reads every candidate line), so 128 are tried first and 256
-    // when 128 would not hold the rows in LDS (static LDS of the kernel:
-    // about 20 KiB).
+    // panel geometry: G co-resident workgroups of R rows each.  Every
+    // workgroup reads every candidate line, so fewer, taller workgroups make
+    // the exchange of a column cheaper, and below about 20 rows the update of
+    // a workgroup's rows hides behind it: measured, getrf with 8 / 16 / 32 /
+    // 64 / 96 / 128 workgroups: DD n = 130 814 / 817 / 831 / 860 / 894 / 942
+    // us, DD 512 2.79 / 2.63 / 2.68 / 2.86 / 2.95 / 2.97 ms, QD 1024 12.8 /
+    // 12.6 / 12.5 / 12.0 / 12.4 / 12.7 ms, QD 2048 (64 / 96 / 128) 25.9 / 25.7 /
+    // 26.2 ms.  More workgroups where the rows do not fit in LDS (the kernel's
+    // static LDS is below 512 bytes).
     int G = 0, R = 0;
-    for (int G0 : {128, 256}) {
+    const int G20 = (int)std::min<int64_t>(128, std::max<int64_t>(8, (nr + 19) / 20));
+    for (int G0 : {G20, 128, 256}) {
       int g = G0, r = 0, maxb = 0;
       bool ok = false;
       for (;;) {
         r = (int)((nr + g - 1) / g);
-        if (r > 32 || ozl::panel_lds_bytes(nc, kb, r, nr) + 20480 > 160 * 1024) break;
+        if (r > 32 || ozl::panel_lds_bytes(nc, kb, r, nr) + 512 > 160 * 1024) break;
         e = ozl::panel_max_blocks(nc, kb, r, nr, &maxb);
         if (e != hipSuccess) return hip_fail(h, e, "panel occupancy");
         if (maxb >= g) {
@@ -1300,15 +1313,12 @@ ozII_status ozII_getrf(ozII_handle h, int32_t nc, int64_t n, double *A, int64_t 
     }
     if (G <= 0) return fail(h, OZII_EUNSUPPORTED, "panel does not fit in LDS for a resident kernel");
     G = (int)std::min<int64_t>(G, (nr + R - 1) / R);
-    if ((e = ozl::launch_fill_int((int *)h->flags, 0, 2 * 32 * 256, s)) != hipSuccess) return hip_fail(h, e, "fill lines");
-    // a panel that stops early leaves no moved rows behind for laswp
-    if ((e = ozl::launch_fill_int(h->nmoved, 0, 1, s)) != hipSuccess) return hip_fail(h, e, "fill nmoved");
     {
       // (P1) panel k; with look-ahead it runs while the side stream finishes
       // the previous step's update on the columns right of it
       ProfScope ps(h, OZ_STAGE_PANEL, 16.0 * nc * (double)nr * kb, (double)nr * kb * kb / 2.0);
-      if ((e = ozl::launch_panel(nc, A, lda, n, k, kb, R, G, ipiv, info, h->flags, h->err, h->crow,
-                                 h->perm, h->moved, h->nmoved, s)) != hipSuccess)
+      if ((e = ozl::launch_panel(nc, A, lda, n, k, kb, R, G, ipiv, info, h->lines, h->err, h->crow,
+                                 h->epoch, h->perm, h->moved, h->nmoved, s)) != hipSuccess)
         return hip_fail(h, e, "panel");
     }
     if (side_busy) {
