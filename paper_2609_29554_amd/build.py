@@ -19,7 +19,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
 # ordinary VGPRs: with the default AGPR form the register allocator splits
 # the accumulator tiles and copies them between register files around every
 # MFMA of the pipelined loops.
-EXTRA = {"k_ozaki.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+EXTRA = {"k_ozaki.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+         "k_limb_lu.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _obj(src: str) -> str:

@@ -13,17 +13,16 @@
 // Carries and borrows between limbs are resolved for all lanes at once:
 // lane k generates (g) or propagates (p) a carry, and the carry into every
 // lane is read off the 64-bit sum (g|p) + g + cin, whose bit k is
-// g_k ^ p_k ^ carry_k.  Products form each output column in its own lane
-// (columns 64..127 in a second register) and resolve the column sums the
-// same way; division is schoolbook long division on 64-bit digits (each
-// digit from the remainder's top two digits over the divisor's top digit by
-// Moller and Granlund's two-by-one division, at most two add-backs, Knuth's
-// Theorem 4.3.1B).
+// g_k ^ p_k ^ carry_k.  Products are byte convolutions on the matrix cores
+// (few limbs: one output column per lane), their sums resolved the same way;
+// division is long division on 58-bit digits with the borrows between lanes
+// deferred.
 //
 // The includer provides LFP_FN and the cross-lane primitives lane_id,
-// ballot, readlane64 (wave-uniform lane), shfl64 (any lane), up1_64 (from
-// lane l-1, 0 into lane 0), rot1_64 (from lane (l-1) mod 64) and addc32
-// (32-bit add with carry).
+// ballot, readlane64 (wave-uniform lane), shfl64 (any lane), up1_64 and
+// up1_32 (from lane l-1, 0 into lane 0), dn1_64 (from lane l+1, 0 into lane
+// 63), lane_bit (a lane's bit of a uniform mask), rot1_64 (from lane (l-1) mod 64), addc32 (32-bit add with carry),
+// align_bits (funnel shift), mfma_bytes and lds_order.
 // Every function must be called by all 64 lanes of a converged wavefront;
 // branches below depend on wave-uniform values only.
 #pragma once
@@ -81,7 +80,7 @@ LFP_FN uint64_t add1(uint64_t x, uint64_t y, int nl, uint32_t cin, uint32_t &cou
   uint32_t c63;
   const uint64_t cm = chain(ballot(act && s < x), ballot(act && s == ~0ull), cin, c63);
   cout = out_at(cm, c63, nl);
-  return act ? s + bit_of(cm, l) : 0ull;
+  return act ? s + lane_bit(cm) : 0ull;
 }
 
 // x - y - bin over lanes < nl (0 above); bout = borrow out of lane nl-1
@@ -91,29 +90,17 @@ LFP_FN uint64_t sub1(uint64_t x, uint64_t y, int nl, uint32_t bin, uint32_t &bou
   uint32_t b63;
   const uint64_t bm = chain(ballot(act && x < y), ballot(act && x == y), bin, b63);
   bout = out_at(bm, b63, nl);
-  return act ? x - y - bit_of(bm, l) : 0ull;
+  return act ? x - y - lane_bit(bm) : 0ull;
 }
 
 LFP_FN W2 add2(W2 x, W2 y, uint32_t cin, uint32_t &cout) {
-  const int l = lane_id();
   const uint64_t sl = x.lo + y.lo, sh = x.hi + y.hi;
   uint32_t c;
   const uint64_t cl = chain(ballot(sl < x.lo), ballot(sl == ~0ull), cin, c);
   const uint64_t ch = chain(ballot(sh < x.hi), ballot(sh == ~0ull), c, cout);
   W2 r;
-  r.lo = sl + bit_of(cl, l);
-  r.hi = sh + bit_of(ch, l);
-  return r;
-}
-
-LFP_FN W2 sub2(W2 x, W2 y, uint32_t bin, uint32_t &bout) {
-  const int l = lane_id();
-  uint32_t b;
-  const uint64_t bl = chain(ballot(x.lo < y.lo), ballot(x.lo == y.lo), bin, b);
-  const uint64_t bh = chain(ballot(x.hi < y.hi), ballot(x.hi == y.hi), b, bout);
-  W2 r;
-  r.lo = x.lo - y.lo - bit_of(bl, l);
-  r.hi = x.hi - y.hi - bit_of(bh, l);
+  r.lo = sl + lane_bit(cl);
+  r.hi = sh + lane_bit(ch);
   return r;
 }
 
@@ -122,14 +109,6 @@ LFP_FN W2 sub2(W2 x, W2 y, uint32_t bin, uint32_t &bout) {
 LFP_FN uint64_t reg_limb(uint64_t v, int j) {
   const uint64_t t = shfl64(v, j & 63);
   return (j >= 0 && j < 64) ? t : 0ull;
-}
-
-// bits [base, base + 64) of the number in v; base & 63 must be wave-uniform
-LFP_FN uint64_t reg_bits(uint64_t v, int64_t base) {
-  const int li = (int)(base >> 6);
-  const int r = (int)(base & 63);
-  const uint64_t x0 = reg_limb(v, li), x1 = reg_limb(v, li + 1);
-  return r ? ((x0 >> r) | (x1 << (64 - r))) : x0;
 }
 
 LFP_FN uint64_t win_limb(W2 w, int j) {
@@ -153,7 +132,7 @@ LFP_FN uint64_t inc_mant(uint64_t m, int nl, uint32_t &ovf) {
   uint32_t c63;
   const uint64_t cm = chain(0ull, ballot(act && m == ~0ull), 1u, c63);
   ovf = out_at(cm, c63, nl);
-  uint64_t r = act ? m + bit_of(cm, l) : 0ull;
+  uint64_t r = act ? m + lane_bit(cm) : 0ull;
   if (ovf) r = (l == nl - 1) ? (1ull << 63) : 0ull;
   return r;
 }
@@ -240,18 +219,18 @@ LFP_FN void mac5(uint32_t (&w)[5], uint64_t a, uint64_t b) {
   w[4] += c;
 }
 
-// RN_p(a b)
-LFP_FN WF mul(const WF &a, const WF &b, int nl) {
-  if (is_zero(a) || is_zero(b)) return wf_zero();
+// The product of two mantissas by a loop over the limbs of a: cheaper than
+// the matrix-core form for few limbs.  Lane l sums column l of the schoolbook
+// product (a_i b_(l-i), i <= l), then column l + 64 (a_i b_(l+64-i), i > l),
+// in one 160-bit accumulator (a column sum is below 64 2^128); the running
+// sum is copied aside when i passes l, and the high column is the final sum
+// minus that copy.
+LFP_FN W2 prod_loop(uint64_t am, uint64_t bm, int nl) {
   const int l = lane_id();
-  // Lane l sums column l of the schoolbook product (a_i b_(l-i), i <= l),
-  // then column l + 64 (a_i b_(l+64-i), i > l), in one 160-bit accumulator
-  // (a column sum is below 64 2^128); the running sum is copied aside when
-  // i passes l, and the high column is the final sum minus that copy.
   uint32_t w[5] = {0u, 0u, 0u, 0u, 0u}, k[5] = {0u, 0u, 0u, 0u, 0u};
-  uint64_t bv = b.m;  // b_((l - i) mod 64) at step i: rotated by one lane per step
+  uint64_t bv = bm;  // b_((l - i) mod 64) at step i: rotated by one lane per step
   for (int i = 0; i < nl; ++i) {
-    const uint64_t ai = readlane64(a.m, i);
+    const uint64_t ai = readlane64(am, i);
     const bool sw = l + 1 == i;
 #pragma unroll
     for (int q = 0; q < 5; ++q) k[q] = sw ? w[q] : k[q];
@@ -279,15 +258,149 @@ LFP_FN WF mul(const WF &a, const WF &b, int nl) {
   uint32_t co;
   W2 S = add2(A, B, 0u, co);
   S = add2(S, C, 0u, co);
-  int64_t bl;
+  return S;
+}
+
+// LDS of one wavefront for the matrix-core product: the signed bytes of one
+// operand from PA, of the other in reverse order from PB, with the zero
+// bytes around them that the fragments below reach (prod_init), and the 256
+// partial sums.
+constexpr int PA = 16, PB = 608 + 432, PW = 608 + 1200;
+constexpr int PROD_LDS = PW + 256 * 8;  // bytes, a multiple of 16
+
+LFP_FN void prod_init(uint8_t *buf) {
+  for (int k = 16 * lane_id(); k < PW; k += 16 * 64) *(v4i32 *)(buf + k) = v4i32{0, 0, 0, 0};
+  lds_order();
+}
+
+// The exact product of two nl-limb numbers on the matrix cores: limbs 0 ..
+// nl-1 in lanes 0 .. nl-1 of lo, limbs nl .. 2nl-1 of hi.  CL - 16 < nl <= CL.
+//
+// With the operands in signed bytes (x + 0x80...80 has the bytes d_i + 128;
+// its carry out c gives x = sum d_i 256^i + c 2^p) the byte products are a
+// convolution.  Output byte 16 C + r, as column C and row r of a tile, is
+//   sum_k d_a[r + k - 15] d_b[16 C + 15 - k],
+// a contraction over k of sixteen shifted copies of a (rows) with sixteen
+// 16-byte steps of b (columns): v_mfma_i32_16x16x64_i8, 26 of them at 49 to
+// 64 limbs where the loop issues 4 nl multiply-adds and their carries.  Row
+// fragments start at any byte (five aligned words and four funnel shifts),
+// column fragments on 16-byte lines of the reversed copy; which tiles meet
+// is fixed by CL, so nothing branches.  A sum has at most 512 terms, so four
+// neighbouring ones make a 48-bit word of weight 2^32, and through LDS each
+// lane takes the words of its limbs.  The carries c add c_a b + c_b a at
+// limb nl, and the signed excess of each limb goes to the next one through
+// the carry chain under a bias.  All is modulo 2^(128 nl), which the product
+// is below.  With it and the sum below, the panel's rank-1 update of a column
+// went from 22.5 to 10 us at 49 limbs, a U12 leaf from 499 to 179 us.
+template <int CL>
+LFP_FN void prod_mfma(uint64_t am, uint64_t bm, int nl, uint8_t *buf, uint64_t &lo, uint64_t &hi) {
+  constexpr uint64_t B80 = 0x8080808080808080ull;
+  constexpr uint64_t BIAS = 1ull << 20;
+  constexpr int NT = CL / 16, NK = ((8 * CL + 14) >> 6) + 1;  // column tiles, k steps
+  const int l = lane_id(), r = l & 15, kg = l >> 4;
+  const bool act = l < nl;
+  uint32_t ca, cb;
+  const uint64_t da = add1(am, B80, nl, 0u, ca) ^ B80, db = add1(bm, B80, nl, 0u, cb) ^ B80;
+  const int rev = PB + 8 * (nl & 1);  // reversed byte i at rev + i; rev + 8 nl on a 16-byte line
+  if (act) {
+    *(uint64_t *)(buf + PA + 8 * l) = da;
+    *(uint64_t *)(buf + rev + 8 * (nl - 1 - l)) = __builtin_bswap64(db);
+  }
+  lds_order();
+  const uint8_t *pa = buf + ((PA - 15 + r + 16 * kg) & ~3);
+  const uint32_t sh = 8u * ((PA - 15 + r) & 3);
+  const uint8_t *pb = buf + rev + 8 * nl - 16 * (r + 1) + 16 * kg;
+  v4i32 acc[NT];
+#pragma unroll
+  for (int T = 0; T < NT; ++T) acc[T] = v4i32{0, 0, 0, 0};
+#pragma unroll
+  for (int t = 0; t < NK; ++t) {
+    uint32_t w[5];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) w[q] = *(const uint32_t *)(pa + 64 * t + 4 * q);
+    v4i32 fa;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) fa[q] = (int)align_bits(w[q + 1], w[q], sh);
+#pragma unroll
+    for (int T = 0; T < NT; ++T) {
+      // columns 16 T .. 16 T + 15 meet bytes of b for k in this range
+      const int k0 = 256 * T + 16 - 8 * CL, k1 = 256 * T + 255;
+      if (t >= (k0 > 0 ? k0 >> 6 : 0) && t <= k1 >> 6)
+        acc[T] = mfma_bytes(fa, *(const v4i32 *)(pb - 256 * T + 64 * t), acc[T]);
+    }
+  }
+  int64_t *pw = (int64_t *)(buf + PW);
+#pragma unroll
+  for (int T = 0; T < NT; ++T)
+    pw[64 * T + 4 * r + kg] = (int64_t)acc[T][0] + ((int64_t)acc[T][1] << 8) +
+                              ((int64_t)acc[T][2] << 16) + ((int64_t)acc[T][3] << 24);
+  lds_order();
+  // this lane's limbs as 128-bit signed sums: low word, signed excess
+  auto take = [&](int limb, uint64_t &v, int64_t &x) {
+    const int64_t w0 = pw[2 * limb], w1 = pw[2 * limb + 1];
+    const uint64_t s = (uint64_t)w1 << 32;
+    v = (uint64_t)w0 + s;
+    x = (w1 >> 32) + (w0 >> 63) + (v < s ? 1 : 0);
+  };
+  uint64_t vl, vh;
+  int64_t xl, xh;
+  take(act ? l : 0, vl, xl);
+  take(act ? nl + l : 0, vh, xh);
+  const uint64_t ea = ca ? bm : 0ull, eb = cb ? am : 0ull;
+  vh += ea;
+  xh += vh < ea ? 1 : 0;
+  vh += eb;
+  xh += vh < eb ? 1 : 0;
+  const uint64_t bl = (uint64_t)xl + BIAS, bh = (uint64_t)xh + BIAS;
+  const uint64_t il = up1_64(bl), ip = up1_64(bh);  // whole-wavefront moves: every lane
+  const uint64_t ih = l ? ip : readlane64(bl, nl - 1);
+  uint32_t c;
+  vl = add1(vl, il, nl, 0u, c);
+  vh = add1(vh, ih, nl, c, c);
+  lo = sub1(vl, l ? BIAS : 0ull, nl, 0u, c);
+  hi = sub1(vh, BIAS, nl, c, c);
+  lds_order();  // the buffer may be filled again
+}
+
+// RN_p(a b).  CL = 0: by the loop; CL = 16, 32, 48 or 64 with CL - 16 < nl <=
+// CL: on the matrix cores, buf PROD_LDS bytes of LDS of this wavefront after
+// prod_init.
+template <int CL>
+LFP_FN WF mul(const WF &a, const WF &b, int nl, uint8_t *buf) {
+  if (is_zero(a) || is_zero(b)) return wf_zero();
   WF r;
-  r.m = round_win(S, 0u, nl, bl);
-  r.e = (int32_t)(bl + a.e + b.e - 128 * (int64_t)nl);
   r.s = (a.s ^ b.s) & 1u;
+  if constexpr (CL == 0) {
+    int64_t bl;
+    r.m = round_win(prod_loop(a.m, b.m, nl), 0u, nl, bl);
+    r.e = (int32_t)(bl + a.e + b.e - 128 * (int64_t)nl);
+  } else {
+    uint64_t lo, hi;
+    prod_mfma<CL>(a.m, b.m, nl, buf, lo, hi);
+    // the product of two normalised mantissas has 128 nl bits or one less
+    const uint64_t th = readlane64(hi, nl - 1), tl = readlane64(lo, nl - 1);
+    const uint64_t low = ballot(lo != 0) & low_mask(nl - 1);
+    const uint32_t sh = (uint32_t)(th >> 63) ^ 1u;
+    uint64_t m = hi;
+    if (sh) {
+      const uint64_t up = up1_64(hi), below = lane_id() ? up : tl;
+      m = lane_id() < nl ? (hi << 1) | (below >> 63) : 0ull;
+    }
+    const uint32_t rb = (uint32_t)((tl << sh) >> 63);
+    const uint32_t st = (uint32_t)(((tl << sh) << 1) != 0) | (uint32_t)(low != 0);
+    uint32_t ovf = 0;
+    if (rb && (st || (readlane64(m, 0) & 1ull))) m = inc_mant(m, nl, ovf);
+    r.m = m;
+    r.e = a.e + b.e - (int32_t)sh + (int32_t)ovf;
+  }
   return r;
 }
 
-// RN_p(a + (-1)^negb b)
+// RN_p(a + (-1)^negb b).  The smaller operand is shifted right by the
+// exponent gap onto the larger one's limbs, with 64 further bits in a
+// uniform guard word and the rest as a sticky bit.  A gap of two or more
+// leaves a difference at most one bit short, and a smaller one loses at most
+// one bit into the guard word, so guard and sticky decide the rounding.
 LFP_FN WF add(const WF &a, const WF &b, uint32_t negb, int nl) {
   const uint32_t bs = (b.s ^ negb) & 1u;
   const bool za = is_zero(a), zb = is_zero(b);
@@ -306,155 +419,245 @@ LFP_FN WF add(const WF &a, const WF &b, uint32_t negb, int nl) {
   const uint32_t Xs = sw ? bs : a.s, Ys = sw ? a.s : bs;
   const int64_t d = (int64_t)Xe - Ye;
   const int64_t p = 64 * (int64_t)nl;
+  WF r;
+  r.s = Xs;
   if (d >= p + 2) {
     // |Y| < 2^(Xe-p-2): below half the spacing on either side of X
-    WF r;
     r.m = Xm;
     r.e = Xe;
-    r.s = Xs;
     return r;
   }
-  // X's bit 0 at window bit XB: room for a carry above a 4096-bit X and
-  // far more guard bits than any rounding needs
-  constexpr int64_t XB = 4032;
   const int l = lane_id();
-  W2 X, Y;
-  X.lo = reg_bits(Xm, 64 * (int64_t)l - XB);
-  X.hi = reg_bits(Xm, 64 * (int64_t)(l + 64) - XB);
-  Y.lo = reg_bits(Ym, 64 * (int64_t)l - XB + d);
-  Y.hi = reg_bits(Ym, 64 * (int64_t)(l + 64) - XB + d);
-  // Y's bits [0, k) fall below the window (k <= 65)
-  uint32_t st = 0;
-  const int64_t k = d - XB;
-  if (k > 0) {
-    const uint64_t y0 = readlane64(Ym, 0), y1 = readlane64(Ym, 1);
-    st = k >= 64 ? (uint32_t)((y0 != 0) | ((y1 & low_mask((int)(k - 64))) != 0))
-                 : (uint32_t)((y0 & low_mask((int)k)) != 0);
-  }
-  W2 S;
-  uint32_t co;
+  const bool act = l < nl;
+  const int q = (int)(d >> 6), rr = (int)(d & 63);
+  // limbs at or past nl are 0, and so is what falls off the top
+  uint64_t Y = q == 0 ? Ym : reg_limb(Ym, l + q);
+  if (rr) Y = (Y >> rr) | (dn1_64(Y) << (64 - rr));
+  const uint64_t yq = q < 64 ? readlane64(Ym, q & 63) : 0ull;
+  const uint64_t yb = q > 0 ? readlane64(Ym, q - 1) : 0ull;
+  uint64_t G = rr ? (yq << (64 - rr)) | (yb >> rr) : yb;
+  uint32_t st = (uint32_t)((yb & low_mask(rr)) != 0);
+  if (q > 1) st |= (uint32_t)((ballot(Ym != 0) & low_mask(q - 1)) != 0);
+  uint64_t m;
+  uint32_t rb, co;
   if (Xs == Ys) {
-    S = add2(X, Y, 0u, co);
+    m = add1(Xm, Y, nl, 0u, co);
+    r.e = Xe + (int32_t)co;
+    if (co) {
+      const uint64_t dn = dn1_64(m), above = l == nl - 1 ? 1ull : dn;
+      rb = (uint32_t)(readlane64(m, 0) & 1ull);
+      m = act ? (m >> 1) | (above << 63) : 0ull;
+      st |= (uint32_t)(G != 0);
+    } else {
+      rb = (uint32_t)(G >> 63);
+      st |= (uint32_t)((G << 1) != 0);
+    }
   } else {
-    // one more unit off when Y lost bits: the exact difference then lies
-    // strictly between S and S + 1, which the sticky bit records
-    S = sub2(X, Y, st, co);
+    // G and the sticky part come off one unit: 2^64 - G, and when something
+    // lies below G one less, the sticky bit then standing for the rest
+    const uint32_t bin = (uint32_t)(G != 0) | st;
+    m = sub1(Xm, Y, nl, bin, co);
+    G = 0ull - G - st;
+    const uint64_t nz = ballot(m != 0);
+    if (nz == 0) {
+      if (G == 0) return wf_zero();  // exact cancellation: +0
+      const int lz = __builtin_clzll(G);
+      r.m = l == nl - 1 ? G << lz : 0ull;
+      r.e = (int32_t)(Xe - p - lz);
+      return r;
+    }
+    const int top = msb64(nz), u = nl - 1 - top;
+    const int lz = __builtin_clzll(readlane64(m, top));
+    uint64_t g = G;
+    if (u) {
+      // whole limbs up: the guard word follows the lowest one
+      const uint64_t t = reg_limb(m, l - u);
+      m = act ? (l == u - 1 ? G : t) : 0ull;
+      g = 0ull;
+    }
+    if (lz) {
+      const uint64_t up = up1_64(m), below = l ? up : g;
+      m = act ? (m << lz) | (below >> (64 - lz)) : 0ull;
+      g <<= lz;
+    }
+    r.e = Xe - 64 * u - lz;
+    rb = (uint32_t)(g >> 63);
+    st |= (uint32_t)((g << 1) != 0);
   }
-  if (ballot(S.lo != 0 || S.hi != 0) == 0) return wf_zero();  // exact cancellation: +0
-  int64_t bl;
-  WF r;
-  r.m = round_win(S, st, nl, bl);
-  r.e = (int32_t)(bl + Xe - p - XB);
-  r.s = Xs;
+  if (rb && (st || (readlane64(m, 0) & 1ull))) {
+    uint32_t ovf;
+    m = inc_mant(m, nl, ovf);
+    r.e += (int32_t)ovf;
+  }
+  r.m = m;
   return r;
 }
 
-// floor((2^128 - 1) / v) - 2^64 for 2^63 <= v < 2^64: the reciprocal with
-// which Moller and Granlund divide two words by the invariant word v; by
-// binary long division of (2^64 - 1 - v) 2^64 + (2^64 - 1), whose high word
-// is below v.
-LFP_FN uint64_t recip64(uint64_t v) {
-  uint64_t r = ~v, q = 0;
-  for (int i = 0; i < 64; ++i) {
-    const uint64_t top = r >> 63;
-    r = (r << 1) | 1ull;
-    q <<= 1;
-    if (top || r >= v) {
-      r -= v;
-      q |= 1ull;
-    }
-  }
-  return q;
+// A lower bound of 2^127 / w within 4 units, for 2^63 < w < 2^64: the
+// binary64 reciprocal corrected once by its exact integer residual.
+LFP_FN uint64_t recip127(uint64_t w) {
+  const double y = 1.0 / (double)w;
+  const double ys = y * 0x1p127;  // at most 2^64
+  const uint64_t y0 = (uint64_t)(ys < 0x1.fffffffffffffp63 ? ys : 0x1.fffffffffffffp63);
+  uint64_t pl, ph;
+  mul128(w, y0, pl, ph);
+  // 2^127 - w y0, below 2^77 in magnitude
+  const int64_t eh = (int64_t)((1ull << 63) - ph - (pl != 0 ? 1ull : 0ull));
+  const double e = (double)eh * 0x1p64 + (double)(0ull - pl);
+  return y0 + (uint64_t)(int64_t)__builtin_floor(e * y) - 2ull;
 }
 
-// floor((u1 2^64 + u0) / v) for u1 < v, v >= 2^63, vinv = recip64(v)
-// (Moller and Granlund, "Improved division by invariant integers", 2011,
-// the two-by-one division with its two conditional corrections)
-LFP_FN uint64_t div2by1(uint64_t u1, uint64_t u0, uint64_t v, uint64_t vinv) {
-  uint64_t p0, p1;
-  mul128(vinv, u1, p0, p1);
-  const uint64_t q0 = p0 + u0;
-  uint64_t q1 = p1 + u1 + (q0 < p0 ? 1ull : 0ull) + 1ull;
-  uint64_t r = u0 - q1 * v;
-  if (r > q0) {
-    q1 -= 1;
-    r += v;
-  }
-  if (r >= v) q1 += 1;
-  return q1;
-}
-
-// RN_p(a / b); b must be non-zero (a zero b gives zero).  Long division on
-// 64-bit digits: digit = min(floor(top two remainder digits / top divisor
-// digit), 2^64 - 1), at most two add-backs (Knuth, TAOCP 4.3.1, Theorem B).
+// RN_p(a / b); b must be non-zero (a zero b gives zero).
+//
+// Long division in digits of 58 bits with nothing carried between the lanes:
+// R <- 2^58 R - q V, each lane keeping the borrows it owes the next lane (at
+// most 3), which enter that lane's next subtraction.  The digit
+// q = floor(n inv / 2^63) takes n from the top of R and the uniform inv
+// from the divisor's top limb, both rounded down, so q never exceeds the
+// true digit and falls short of it by less than 12: R stays in [0, 12 V), n
+// below 2^62 and q below 2^63.  The digits overlap by five bits; one lane
+// holds each, and at the end they are added up, R is brought below V and its
+// zero test is the sticky bit.  At least two bits follow the rounding
+// position.  Per digit one readlane, one uniform and one per-lane 64 x 64-bit
+// product in the dependent chain; the division kernel of a panel column at 49
+// limbs, one division deep, took 31 us with 64-bit digits whose remainder was
+// carried through every step and takes 16 us.
 LFP_FN WF div(const WF &a, const WF &b, int nl) {
   if (is_zero(a) || is_zero(b)) return wf_zero();
+  constexpr int DB = 58;
   const int l = lane_id();
   const bool act = l < nl;
   const uint64_t V = b.m;
-  const uint64_t v1 = readlane64(V, nl - 1);  // top divisor digit, >= 2^63
-  const uint64_t vinv = recip64(v1);
-  // leading quotient digit d0 = floor(ma / mb) in {0, 1}
-  const uint32_t d0 = cmp_mant(a.m, V) >= 0 ? 1u : 0u;
-  uint64_t R = a.m;
-  uint32_t bo;
-  if (d0) R = sub1(R, V, nl, 0u, bo);
-  // nl + 1 further digits: limb nl - i of Q takes digit i (i <= nl), dl the last
-  const int K = nl + 1;
-  uint64_t Q = 0, dl = 0;
-  for (int i = 1; i <= K; ++i) {
-    // R <- R 2^64 (R < V): its top limb becomes the digit above limb nl-1
-    const uint64_t ut = readlane64(R, nl - 1);
-    const uint64_t un = nl >= 2 ? readlane64(R, nl - 2) : 0ull;  // nl is uniform
-    const uint64_t Rs = up1_64(R);
-    R = act ? Rs : 0ull;
-    uint64_t qh = ut >= v1 ? ~0ull : div2by1(ut, un, v1, vinv);
-    // T = qh V: lane k's product lo + hi 2^64, hi moving to lane k+1
+  const uint64_t v1 = readlane64(V, nl - 1);  // top divisor limb, >= 2^63
+  const uint64_t inv = v1 == ~0ull ? 1ull << 63 : recip127(v1 + 1ull);
+  const int K = (64 * nl + 2 + DB - 1) / DB;
+  uint64_t R = a.m, top = 0, dq0 = 0, dq1 = 0;
+  uint32_t owe = 0;  // borrows of this lane on the next one
+  auto step = [&]() -> uint64_t {
+    const uint64_t n = (top << DB) | (readlane64(R, nl - 1) >> (64 - DB));
+    uint64_t ql, qh;
+    mul128(n - (n > 0 ? 1ull : 0ull), inv, ql, qh);
+    const uint64_t q = (qh << 1) | (ql >> 63);
     uint64_t lo, hi;
-    mul128(qh, V, lo, hi);
+    mul128(q, V, lo, hi);
+    const uint64_t x = (R << DB) | (up1_64(R) >> (64 - DB));
     const uint64_t hin = up1_64(hi);
-    uint64_t T = lo + hin;
-    uint32_t c63;
-    const uint64_t cm = chain(ballot(act && T < lo), ballot(act && T == ~0ull), 0u, c63);
-    T = act ? T + bit_of(cm, l) : 0ull;
-    const uint64_t ttop = readlane64(hi, nl - 1) + out_at(cm, c63, nl);  // <= 2^64 - 1
-    uint32_t bt;
-    R = sub1(R, T, nl, 0u, bt);
-    // the remainder lies in [-2V, V): its top digit, signed, is -2, -1 or 0
-    int64_t top = (int64_t)(ut - ttop - bt);
-    for (int k = 0; k < 2 && top < 0; ++k) {
-      qh -= 1;
-      uint32_t cy;
-      R = add1(R, V, nl, 0u, cy);
-      top += cy;
-    }
-    if (i < K) {
-      Q = (l == nl - i) ? qh : Q;
-    } else {
-      dl = qh;
-    }
+    const uint64_t oin = (uint64_t)up1_32(owe) << DB;
+    uint32_t bo = x < lo ? 1u : 0u;
+    uint64_t t = x - lo;
+    bo += t < hin ? 1u : 0u;
+    t -= hin;
+    bo += t < oin ? 1u : 0u;
+    t -= oin;
+    R = act ? t : 0ull;
+    owe = act ? bo : 0u;
+    // the part of 2^58 R - q V above limb nl-1; owe there is settled at once
+    top = n - readlane64(hi, nl - 1) - (uint64_t)(uint32_t)readlane64(owe, nl - 1);
+    return q;
+  };
+  for (int i = 0; i < (K < 64 ? K : 64); ++i) {
+    const uint64_t q = step();
+    dq0 = l == i ? q : dq0;
+  }
+  for (int i = 64; i < K; ++i) {
+    const uint64_t q = step();
+    dq1 = l == i - 64 ? q : dq1;
+  }
+  uint32_t bo, cnt = 0;
+  owe = l == nl - 1 ? 0u : owe;
+  R = sub1(R, (uint64_t)up1_32(owe), nl, 0u, bo);
+  top -= bo;
+  for (int k = 0; k < 16 && (top != 0 || cmp_mant(R, V) >= 0); ++k) {
+    R = sub1(R, V, nl, 0u, bo);
+    top -= bo;
+    ++cnt;
   }
   const uint32_t rem = ballot(R != 0) != 0 ? 1u : 0u;
-  uint64_t m;
-  uint32_t rb, st;
-  if (!d0) {
-    // quotient bits: Q (p bits), then the last digit
-    m = Q;
-    rb = (uint32_t)(dl >> 63);
-    st = (uint32_t)((dl << 1) != 0) | rem;
-  } else {
-    // a leading 1 before Q: shift right by one
-    const uint64_t above = shfl64(Q, (l + 1) & 63);
-    m = act ? ((Q >> 1) | ((l + 1 < nl ? above : 0ull) << 63)) : 0ull;
-    if (l == nl - 1) m |= 1ull << 63;
-    rb = (uint32_t)(readlane64(Q, 0) & 1ull);
-    st = (uint32_t)(dl != 0) | rem;
-  }
-  const uint32_t lsb = (uint32_t)(readlane64(m, 0) & 1ull);
-  uint32_t ovf = 0;
-  if (rb && (st || lsb)) m = inc_mant(m, nl, ovf);
+  // Q = sum_t digit_t 2^(58 t), digit t = q of step K-1-t: a limb meets three
+  auto digit = [&](int t) -> uint64_t {
+    const int i = K - 1 - t;
+    const uint64_t x = shfl64(dq0, i & 63), y = K > 64 ? shfl64(dq1, i & 63) : 0ull;
+    return t < 0 || i < 0 ? 0ull : (i < 64 ? x : y);
+  };
+  auto limb = [&](int k, uint64_t &v, uint64_t &cy) {
+    const int th = (64 * k + 63) / DB;
+    v = 0;
+    cy = 0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int off = DB * (th - j) - 64 * k;
+      const uint64_t g = digit(th - j);
+      const uint64_t s = off >= 0 ? g << off : (off > -64 ? g >> -off : 0ull);
+      v += s;
+      cy += v < s ? 1ull : 0ull;
+    }
+  };
+  W2 Q, C;
+  limb(l, Q.lo, C.lo);
+  Q.hi = 0;
+  C.hi = 0;
+  if (DB * K + 64 > 64 * 64) limb(l + 64, Q.hi, C.hi);  // uniform
+  C = up_limb(C);
+  C.lo = l ? C.lo : (uint64_t)cnt;
+  uint32_t co;
+  Q = add2(Q, C, 0u, co);
+  int64_t bl;
   WF r;
-  r.m = m;
+  r.m = round_win(Q, rem, nl, bl);
+  r.e = (int32_t)(bl - (int64_t)DB * K + a.e - b.e);
+  r.s = (a.s ^ b.s) & 1u;
+  return r;
+}
+
+// RN_p(a / b) with y = RN_p(1 / b) at hand (CL > 0): two products instead of
+// the digit chain.  a y is the quotient's p bits to within two units; its
+// exact remainder corrects it and decides the rounding.
+template <int CL>
+LFP_FN WF div_by(const WF &a, const WF &b, const WF &y, int nl, uint8_t *buf) {
+  if (is_zero(a) || is_zero(b)) return wf_zero();
+  const int l = lane_id();
+  const bool act = l < nl;
+  // b a power of two: 1/b has another exponent
+  if (y.e + b.e != 1) return div(a, b, nl);
+  const uint32_t d0 = cmp_mant(a.m, b.m) >= 0 ? 1u : 0u;
+  // Q ~ floor(a 2^(p - d0) / b), taken two units low
+  uint64_t lo, hi;
+  prod_mfma<CL>(a.m, y.m, nl, buf, lo, hi);
+  const uint64_t lt = readlane64(lo, nl - 1);
+  uint64_t Q = hi;
+  if (!d0) {
+    const uint64_t up = up1_64(hi), below = l ? up : lt;
+    // a 2p-bit product: its rounding reached 2^p
+    Q = (readlane64(hi, nl - 1) >> 63) ? ~0ull : (hi << 1) | (below >> 63);
+    Q = act ? Q : 0ull;
+  }
+  uint32_t c;
+  Q = sub1(Q, l == 0 ? 2ull : 0ull, nl, 0u, c);
+  // R = a 2^(p - d0) - Q b, its part above limb nl-1 in rh
+  prod_mfma<CL>(Q, b.m, nl, buf, lo, hi);
+  const uint64_t a0 = readlane64(a.m, 0);
+  uint64_t al = 0, ah = a0;
+  if (d0) {
+    al = l == nl - 1 ? a0 << 63 : 0ull;
+    ah = (a0 >> 1) | ((nl > 1 ? readlane64(a.m, 1) : 0ull) << 63);
+  }
+  uint64_t R = sub1(al, lo, nl, 0u, c);
+  int64_t rh = (int64_t)(ah - readlane64(hi, 0) - c);
+  uint32_t cnt = 0;
+  for (int k = 0; k < 16 && (rh != 0 || cmp_mant(R, b.m) >= 0); ++k) {
+    R = sub1(R, b.m, nl, 0u, c);
+    rh -= c;
+    ++cnt;
+  }
+  Q = add1(Q, l == 0 ? (uint64_t)cnt : 0ull, nl, 0u, c);
+  // against half the divisor
+  const uint32_t over = (uint32_t)(readlane64(R, nl - 1) >> 63);
+  const uint64_t ru = up1_64(R), R2 = act ? (R << 1) | (ru >> 63) : 0ull;
+  const int h = over ? 1 : cmp_mant(R2, b.m);
+  uint32_t ovf = 0;
+  if (h > 0 || (h == 0 && (readlane64(Q, 0) & 1ull))) Q = inc_mant(Q, nl, ovf);
+  WF r;
+  r.m = Q;
   r.e = a.e - b.e + (int32_t)d0 + (int32_t)ovf;
   r.s = (a.s ^ b.s) & 1u;
   return r;
@@ -462,8 +665,9 @@ LFP_FN WF div(const WF &a, const WF &b, int nl) {
 
 // RN_p(c - RN_p(a b)): the multiply-subtract of the panel, the U12 solve
 // and the substitutions
-LFP_FN WF fms(const WF &c, const WF &a, const WF &b, int nl) {
-  return add(c, mul(a, b, nl), 1u, nl);
+template <int CL>
+LFP_FN WF fms(const WF &c, const WF &a, const WF &b, int nl, uint8_t *buf) {
+  return add(c, mul<CL>(a, b, nl, buf), 1u, nl);
 }
 
 }  // namespace lfp

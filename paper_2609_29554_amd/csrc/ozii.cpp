@@ -357,9 +357,11 @@ struct ozII_ctx {
   int *perm = nullptr, *moved = nullptr, *nmoved = nullptr;
   int64_t panel_n = 0;
   int panel_kb = 0;
-  // limb LU: pivot candidates of one panel column and the zero-pivot word
-  int64_t *lcand = nullptr;
+  // limb LU: the zero-pivot word
   int32_t *lflag = nullptr;
+  // packed limb numbers: the leaf of a panel, the reciprocals of a solve
+  uint64_t *lpack = nullptr;
+  size_t lpack_words = 0;
   // getrf look-ahead: a side stream (default priority) for the rest of each
   // Schur update while the next panel runs, and the fork / join events
   hipStream_t side = nullptr;
@@ -901,13 +903,34 @@ ozII_status gemm_limbs_impl(ozII_ctx *h, int mode, int nlimb, int64_t M, int64_t
   return OZII_OK;
 }
 
-// Pivot-candidate and zero-pivot scratch of the limb LU (allocated once).
+// Zero-pivot word of the limb LU (allocated once).
 ozII_status limb_scratch(ozII_ctx *h) {
-  if (h->lcand) return OZII_OK;
-  hipError_t e = hipMalloc((void **)&h->lcand, sizeof(int64_t) * ozl::LPIV_MAXGRID + 256);
+  if (h->lflag) return OZII_OK;
+  hipError_t e = hipMalloc((void **)&h->lflag, 256);
   if (e != hipSuccess) return hip_fail(h, e, "hipMalloc(limb pivot scratch)");
-  h->lflag = (int32_t *)(h->lcand + ozl::LPIV_MAXGRID);
   return OZII_OK;
+}
+
+// Scratch for `words` words of packed limb numbers, or null when it cannot be
+// had (no memory, or a growth inside a stream capture): the callers then work
+// on the caller's planes, with the same results.
+uint64_t *limb_pack(ozII_ctx *h, size_t words) {
+  if (words <= h->lpack_words) return h->lpack;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(h->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return nullptr;
+  if (h->lpack) {
+    if (hipStreamSynchronize(h->stream) != hipSuccess) return nullptr;
+    hipFree(h->lpack);
+    h->lpack = nullptr;
+    h->lpack_words = 0;
+  }
+  if (hipMalloc((void **)&h->lpack, words * 8) != hipSuccess) {
+    (void)hipGetLastError();
+    h->lpack = nullptr;
+    return nullptr;
+  }
+  h->lpack_words = words;
+  return h->lpack;
 }
 
 // the sub-matrix starting at element (i, j)
@@ -955,6 +978,7 @@ struct LimbLU {
   const ozII_opts *o;
   int64_t *ipiv;
   int32_t *info;
+  uint64_t *pack = nullptr;  // a packed panel leaf, or null: on the planes
 
   double el() const { return 8.0 * nl + 5.0; }
 
@@ -1003,12 +1027,22 @@ struct LimbLU {
       // interchanges inside the leaf per column, then on the rest of the
       // panel once per leaf (the same rows end up in the same places)
       ProfScope ps(h, OZ_STAGE_PANEL, el() * (double)(n - c0) * w, 0);
-      for (int64_t j = c0; j < c0 + w; ++j) {
-        const hipError_t e = ozl::launch_lpanel_column(M, nl, j, n, c0, c0 + w, c0 + w, h->lcand,
-                                                       ipiv, info, h->lflag, h->stream);
-        if (e != hipSuccess) return hip_fail(h, e, "limb panel");
+      hipError_t e = hipSuccess;
+      if (pack) {
+        const int64_t rows = n - c0;
+        const ozl::LimbMat P = ozl::packed_mat(pack, nl, rows);
+        e = ozl::launch_lpack(M, P, nl, c0, rows, c0, w, 0, h->stream);
+        for (int64_t j = 0; j < w && e == hipSuccess; ++j)
+          e = ozl::launch_lpanel_column(P, nl, j, rows, 0, w, w, c0, ipiv + c0, info, h->lflag,
+                                        h->stream);
+        if (e == hipSuccess) e = ozl::launch_lpack(M, P, nl, c0, rows, c0, w, 1, h->stream);
+      } else {
+        for (int64_t j = c0; j < c0 + w && e == hipSuccess; ++j)
+          e = ozl::launch_lpanel_column(M, nl, j, n, c0, c0 + w, c0 + w, 0, ipiv, info, h->lflag,
+                                        h->stream);
       }
-      const hipError_t e = ozl::launch_llaswp(M, nl, ipiv, c0, w, P0, c0, c0 + w, P1, h->stream);
+      if (e != hipSuccess) return hip_fail(h, e, "limb panel");
+      e = ozl::launch_llaswp(M, nl, ipiv, c0, w, P0, c0, c0 + w, P1, h->stream);
       return e == hipSuccess ? OZII_OK : hip_fail(h, e, "limb panel interchanges");
     }
     const int64_t w1 = limb_split(w, leaf);
@@ -1102,7 +1136,8 @@ ozII_status ozII_destroy(ozII_handle h) {
   if (h->batch) hipFree(h->batch);
   if (h->batch_queue) hipFree(h->batch_queue);
   if (h->batch_ws) hipFree(h->batch_ws);
-  if (h->lcand) hipFree(h->lcand);
+  if (h->lflag) hipFree(h->lflag);
+  if (h->lpack) hipFree(h->lpack);
   if (h->bar) {
     hipFree(h->bar);
     hipFree(h->lines);
@@ -1449,6 +1484,8 @@ ozII_status ozII_getrf_limbs(ozII_handle h, int32_t nlimb, int64_t n, ozII_limbs
       if ((st = get_plan(h, 64 * nlimb, K, o, &hp, &dp, true)) != OZII_OK) return st;
     }
   }
+  const int64_t leafw = std::min<int64_t>(n, L.leaf > 0 ? std::min<int64_t>(L.leaf, b) : b);
+  L.pack = limb_pack(h, (size_t)n * leafw * ozl::packed_words(nlimb));
   hipError_t e;
   if ((e = ozl::launch_lfill_i32(info, 0, 1, h->stream)) != hipSuccess) return hip_fail(h, e, "info");
   const double el = 8.0 * nlimb + 5.0;
@@ -1476,7 +1513,10 @@ ozII_status ozII_getrs_limbs(ozII_handle h, int32_t nlimb, int64_t n, int64_t nr
   if (!ipiv || !limbs_ok(LU, n, n) || !limbs_ok(B, n, nrhs))
     return fail(h, OZII_EINVAL, "bad limb matrix descriptor or null pointer");
   ProfScope ps(h, OZ_STAGE_GETRS, (8.0 * nlimb + 5.0) * ((double)n * n + 2.0 * n * nrhs), 0);
-  const hipError_t e = ozl::launch_lgetrs(limb_mat(LU), nlimb, n, ipiv, limb_mat(B), nrhs, h->stream);
+  uint64_t *recip =
+      ozl::lgetrs_wants_recip(nlimb) ? limb_pack(h, (size_t)n * ozl::packed_words(nlimb)) : nullptr;
+  const hipError_t e =
+      ozl::launch_lgetrs(limb_mat(LU), nlimb, n, ipiv, limb_mat(B), nrhs, recip, h->stream);
   return e == hipSuccess ? OZII_OK : hip_fail(h, e, "limb solve");
 }
 

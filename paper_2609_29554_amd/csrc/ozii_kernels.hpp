@@ -171,20 +171,39 @@ hipError_t launch_batch_oz(const ozII_batch_item *items, int count, int *queue, 
                            hipStream_t s);
 
 // LU on limb matrices outside the Ozaki-II product (k_limb_lu.hip): limb q
-// of element (i, j) at limb[q plane + i + j ld]
+// of element (i, j), e = i + j ld, at limb[q plane + e es], its exponent at
+// exp[e xs] and sign at sign[e ss].  The caller's matrices have one plane
+// per limb (es = xs = ss = 1); packed ones keep an element's limbs together
+// (plane = 1), followed by a word with its exponent and sign.
 struct LimbMat {
   uint64_t *limb;
   int32_t *exp;
   uint8_t *sign;
   int64_t ld, plane;
+  int64_t es = 1, xs = 1, ss = 1;
 };
-// pivot-candidate workgroups per panel column (the size of `cand`)
-constexpr int LPIV_MAXGRID = 64;
+inline int64_t packed_words(int nl) { return nl + 1; }  // per element
+inline LimbMat packed_mat(uint64_t *buf, int nl, int64_t rows) {
+  LimbMat m;
+  m.limb = buf;
+  m.exp = (int32_t *)(buf + nl);
+  m.sign = (uint8_t *)(buf + nl) + 4;
+  m.ld = rows;
+  m.plane = 1;
+  m.es = packed_words(nl);
+  m.xs = 2 * m.es;
+  m.ss = 8 * m.es;
+  return m;
+}
+// P = A[i0 : i0+rows, c0 : c0+w] (unpack = 0), or the other way (unpack = 1)
+hipError_t launch_lpack(LimbMat A, LimbMat P, int nl, int64_t i0, int64_t rows, int64_t c0,
+                        int64_t w, int unpack, hipStream_t s);
 // one panel column j: pivot search over rows [j, n), ipiv[j], info, the
 // interchange on columns [s0, s1), division, rank-1 update of columns
-// (j, c1); zflag: one word
+// (j, c1); zflag: one word.  Row and column 0 of A are number base of the
+// whole matrix, which ipiv and info count in (ipiv points at entry base).
 hipError_t launch_lpanel_column(LimbMat A, int nl, int64_t j, int64_t n, int64_t s0, int64_t s1,
-                                int64_t c1, int64_t *cand, int64_t *ipiv, int32_t *info,
+                                int64_t c1, int64_t base, int64_t *ipiv, int32_t *info,
                                 int32_t *zflag, hipStream_t s);
 // interchanges ipiv[k0 .. k0+kb) on columns [ca0, ca1) and [cb0, cb1)
 hipError_t launch_llaswp(LimbMat A, int nl, const int64_t *ipiv, int64_t k0, int64_t kb,
@@ -195,8 +214,11 @@ hipError_t launch_ltrsm(LimbMat A, int nl, int64_t r0, int64_t h, int64_t b0, in
 // A[i0:i1, c0:c1] -= A[i0:i1, k0:k0+K] A[k0:k0+K, c0:c1] by multiply-subtracts
 hipError_t launch_lschur_naive(LimbMat A, int nl, int64_t i0, int64_t i1, int64_t c0, int64_t c1,
                                int64_t k0, int64_t K, hipStream_t s);
+// recip: n packed numbers of scratch for the reciprocals of the diagonal, or
+// null (each division then runs its digit chain)
+bool lgetrs_wants_recip(int nl);
 hipError_t launch_lgetrs(LimbMat LU, int nl, int64_t n, const int64_t *ipiv, LimbMat X,
-                         int64_t nrhs, hipStream_t s);
+                         int64_t nrhs, uint64_t *recip, hipStream_t s);
 hipError_t launch_larith(int op, int nl, int64_t cnt, LimbMat A, LimbMat B, LimbMat C,
                          hipStream_t s);
 hipError_t launch_lfill_i32(int32_t *p, int32_t v, int count, hipStream_t s);
