@@ -67,11 +67,12 @@ __device__ __forceinline__ double join_f64(uint64_t lo, uint64_t hi) {
 
 // One step of a bounded wait: true when it has to be given up, because about
 // a second has passed (100 MHz real-time counter) or another wait failed.
-__device__ __forceinline__ bool wait_expired(uint32_t &spins, uint64_t t0, int *err) {
+__device__ __forceinline__ bool wait_expired(uint32_t &spins, uint64_t t0, int *err,
+                                             int code = 1) {
   if ((++spins & 63u) != 0) return false;
   if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return true;
   if (__builtin_amdgcn_s_memrealtime() - t0 <= 100000000ull) return false;
-  __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(err, code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return true;
 }
 
@@ -639,20 +640,29 @@ __global__ __launch_bounds__(256) void k_trsm_lower_unit(const double *Lp, int64
   }
 }
 
-// U12 solve for kb <= 64 WPC: each column is held by WPC wavefronts, row
-// 64 p + l in lane l of the column's wavefront p (4 / WPC columns per
+// Triangular solves for kb <= 64 WPC: each column is held by WPC wavefronts,
+// row 64 p + l in lane l of the column's wavefront p (4 / WPC columns per
 // 256-thread workgroup).  Wavefront p first applies the values of rows
 // 0 .. 64 p - 1 as the wavefronts before it publish them (LDS, one counter
 // per column), then solves its own 64 rows with no barrier: row h's final
 // value is read from lane h - 64 p into scalar registers, published for
 // the wavefronts after it, and applied to the later rows.  Every element
 // receives its multiply-subtracts in ascending k, the order of
-// k_trsm_lower_unit.
-template <int NC, int WPC>
-__global__ __launch_bounds__(256) void k_trsm_lower_unit_w(const double *Lp, int64_t lda,
-                                                           double *Xp, int64_t ldx, int kb,
-                                                           int64_t ncols) {
-  constexpr int CPB = 4 / WPC;
+// k_trsm_lower_unit.  UPPER: the same with the rows counted from the last
+// and each value divided by its diagonal entry once its updates are in
+// (x_h <- x_h / u_hh, then x_i -= u_ih x_h, h descending).  Bound by the chain
+// of one multiply-subtract (UPPER: and a division) per row; a barrier and a
+// division per row took 1.49 ms for 256 QD rows, this 1.2.
+// factor entries in flight per lane: a DD multiply-subtract is much shorter
+// than a load's latency, a QD one about as long.  The queue is shifted, not
+// unrolled: the body runs from few cache lines of code.
+template <int NC>
+constexpr int trsm_pf() { return NC == 2 ? 4 : 2; }
+
+template <int NC, int WPC, bool UPPER>
+__global__ __launch_bounds__(256) void k_trsm_w(const double *Fp, int64_t lda, double *Xp,
+                                                int64_t ldx, int kb, int64_t ncols) {
+  constexpr int CPB = 4 / WPC, PF = trsm_pf<NC>();
   __shared__ double xs[CPB][WPC > 1 ? 64 * (WPC - 1) : 1][NC];
   __shared__ int done[CPB];
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
@@ -661,131 +671,60 @@ __global__ __launch_bounds__(256) void k_trsm_lower_unit_w(const double *Lp, int
   if (tid < CPB) done[tid] = 0;
   __syncthreads();
   if (c >= ncols) return;  // whole wavefronts of a column past the end
-  const int i = 64 * part + lane;
+  const int i = 64 * part + lane;  // position: row i, or UPPER row kb-1-i
   const bool mine = i < kb;
-  auto L = [&](int r, int k) { return Lp + (r + (int64_t)k * lda) * NC; };
-  double x[NC], l[NC];
-#pragma unroll
-  for (int q = 0; q < NC; ++q) {
-    x[q] = 0.0;
-    l[q] = 0.0;
+  auto row = [&](int p) { return UPPER ? kb - 1 - p : p; };
+  auto F = [&](int p, int h) { return Fp + (row(p) + (int64_t)row(h) * lda) * NC; };
+  double x[NC] = {}, d[NC] = {}, f[PF][NC] = {};
+  if (mine) {
+    ozx::load<NC>(Xp + (row(i) + c * ldx) * NC, x);
+    if (UPPER) ozx::load<NC>(F(i, i), d);
   }
-  if (mine) ozx::load<NC>(Xp + (i + c * ldx) * NC, x);
   const int h0 = 64 * part, h1 = kb < h0 + 64 ? kb : h0 + 64;
   if (h0 >= kb) return;
-  // factor entry l_(i,h) of the next step is loaded while this one computes
-  if (mine && i > 0) ozx::load<NC>(L(i, 0), l);
-  for (int h = 0; h < h0; ++h) {
-    double ln[NC] = {}, y[NC], o[NC];
-    if (mine && h + 1 < i) ozx::load<NC>(L(i, h + 1), ln);
-    // the value of row h, published by an earlier wavefront of this column
-    // (it never waits itself before publishing, so this ends)
-    while (__hip_atomic_load(&done[cc], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= h)
-      __builtin_amdgcn_s_sleep(1);
 #pragma unroll
-    for (int q = 0; q < NC; ++q) y[q] = xs[cc][h][q];
-    if (mine) {
-      ozx::fms<NC>(x, l, y, o);
+  for (int t = 0; t < PF; ++t)
+    if (mine && t < i) ozx::load<NC>(F(i, t), f[t]);
+  for (int h = 0; h < h1; ++h) {
+    double y[NC], fn[NC] = {};
+    if (mine && h + PF < i) ozx::load<NC>(F(i, h + PF), fn);
+    if (h < h0) {
+      // published by an earlier wavefront of this column (it never waits for
+      // this one, so this ends)
+      while (__hip_atomic_load(&done[cc], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= h)
+        __builtin_amdgcn_s_sleep(1);
 #pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        x[q] = o[q];
-        l[q] = ln[q];
+      for (int q = 0; q < NC; ++q) y[q] = xs[cc][h][q];
+    } else {
+      if (UPPER) {
+        double o[NC];
+        ozx::div<NC>(x, d, o);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) x[q] = lane == h - h0 ? o[q] : x[q];
       }
-    }
-  }
-  for (int h = h0; h < h1; ++h) {
-    double ln[NC] = {}, y[NC], o[NC];
-    if (mine && h + 1 < i) ozx::load<NC>(L(i, h + 1), ln);
-    // row h is final
+      // position h is final
 #pragma unroll
-    for (int q = 0; q < NC; ++q) y[q] = readlane_f64(x[q], h - h0);
-    if (part + 1 < WPC && lane == h - h0) {
+      for (int q = 0; q < NC; ++q) y[q] = readlane_f64(x[q], h - h0);
+      if (part + 1 < WPC && lane == h - h0) {
 #pragma unroll
-      for (int q = 0; q < NC; ++q) xs[cc][h][q] = y[q];
-      __hip_atomic_store(&done[cc], h + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        for (int q = 0; q < NC; ++q) xs[cc][h][q] = y[q];
+        __hip_atomic_store(&done[cc], h + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
     }
     if (mine && i > h) {
-      ozx::fms<NC>(x, l, y, o);
+      double o[NC];
+      ozx::fms<NC>(x, f[0], y, o);
 #pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        x[q] = o[q];
-        l[q] = ln[q];
-      }
+      for (int q = 0; q < NC; ++q) x[q] = o[q];
+    }
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+#pragma unroll
+      for (int t = 0; t + 1 < PF; ++t) f[t][q] = f[t + 1][q];
+      f[PF - 1][q] = fn[q];
     }
   }
-  if (mine) ozx::store<NC>(Xp + (i + c * ldx) * NC, x);
-}
-
-// X <- U^{-1} X for an upper-triangular kb x kb block: for h = kb-1 .. 0,
-// x_h <- x_h / u_hh (expansion division), then x_i -= u_ih x_h for i < h
-// (descending order).
-template <int NC, int CPB, int RPT>
-__global__ __launch_bounds__(256) void k_trsm_upper(const double *Up, int64_t lda, double *Xp,
-                                                    int64_t ldx, int kb, int64_t ncols) {
-  __shared__ double xs[2][CPB][NC];
-  const int tid = threadIdx.x;
-  const int64_t cbase = (int64_t)blockIdx.x * CPB;
-  double x[RPT][CPB][NC];
-#pragma unroll
-  for (int rr = 0; rr < RPT; ++rr) {
-    const int i = tid + 256 * rr;
-#pragma unroll
-    for (int cc = 0; cc < CPB; ++cc) {
-      const int64_t c = cbase + cc;
-      if (i < kb && c < ncols) ozx::load<NC>(Xp + (i + c * ldx) * NC, x[rr][cc]);
-      else
-#pragma unroll
-        for (int q = 0; q < NC; ++q) x[rr][cc][q] = 0.0;
-    }
-  }
-  for (int h = kb - 1; h >= 0; --h) {
-    const int b = h & 1;
-    if (tid == (h & 255)) {
-#pragma unroll
-      for (int rr = 0; rr < RPT; ++rr)
-        if (rr == h / 256) {
-          double d[NC];
-          ozx::load<NC>(Up + (h + (int64_t)h * lda) * NC, d);
-#pragma unroll
-          for (int cc = 0; cc < CPB; ++cc) {
-            double o[NC];
-            ozx::div<NC>(x[rr][cc], d, o);
-#pragma unroll
-            for (int q = 0; q < NC; ++q) {
-              x[rr][cc][q] = o[q];
-              xs[b][cc][q] = o[q];
-            }
-          }
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int rr = 0; rr < RPT; ++rr) {
-      const int i = tid + 256 * rr;
-      if (i < h) {
-        double u[NC];
-        ozx::load<NC>(Up + (i + (int64_t)h * lda) * NC, u);
-#pragma unroll
-        for (int cc = 0; cc < CPB; ++cc) {
-          double xh[NC], o[NC];
-#pragma unroll
-          for (int q = 0; q < NC; ++q) xh[q] = xs[b][cc][q];
-          ozx::fms<NC>(x[rr][cc], u, xh, o);
-#pragma unroll
-          for (int q = 0; q < NC; ++q) x[rr][cc][q] = o[q];
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int rr = 0; rr < RPT; ++rr) {
-    const int i = tid + 256 * rr;
-#pragma unroll
-    for (int cc = 0; cc < CPB; ++cc) {
-      const int64_t c = cbase + cc;
-      if (i < kb && c < ncols) ozx::store<NC>(Xp + (i + c * ldx) * NC, x[rr][cc]);
-    }
-  }
+  if (mine) ozx::store<NC>(Xp + (row(i) + c * ldx) * NC, x);
 }
 
 // ---------------------------------------------------------------------------
@@ -896,8 +835,8 @@ __global__ __launch_bounds__(256) void k_apply_ipiv(double *B, int64_t ldb, int6
 }
 
 // ---------------------------------------------------------------------------
-// Triangular solves of getrs for one right-hand side, pipelined over the
-// whole grid (one ordinary launch per direction).  A workgroup takes its
+// Triangular solves of getrs for one or a few right-hand sides, pipelined
+// over the whole grid (one ordinary launch per direction).  A workgroup takes its
 // block of rows from an atomic ticket when it starts, so block t belongs to
 // the t-th workgroup to run: every block it waits for is owned by a
 // workgroup that is already running, whatever order the hardware dispatches
@@ -918,26 +857,38 @@ __global__ __launch_bounds__(256) void k_apply_ipiv(double *B, int64_t ldb, int6
 // values in groups of TRSV_PUB rows (stores, agent release, then the count
 // of finished positions), so the critical chain of the solve never waits
 // for a store.  Waits are bounded like the panel's.
-constexpr int TRSV_R = 32;    // rows per workgroup (lanes of wavefront 0)
-constexpr int TRSV_B = 32;    // solution values applied per batch
+//
+// NR = 2: a workgroup takes two right-hand sides, lanes 0 .. 31 and 32 .. 63
+// of wavefront 0, which share the factor entries and the division chain's
+// issue slots; blockIdx.y = pair, each with its own count and ticket.
+constexpr int TRSV_R = 32;    // rows per workgroup
 constexpr int TRSV_PUB = 4;   // rows of the diagonal block published at a time
+// solution values applied per batch; half of them where two right-hand sides
+// of QD products would leave room for one workgroup per CU
+template <int NC, int NR>
+constexpr int trsv_b() { return NC * NR > 6 ? 16 : 32; }
 
-template <int NC, bool FWD>
-__global__ __launch_bounds__(256) void k_trsv(const double *LU, int64_t lda, double *x,
-                                              int64_t n, uint32_t *ready, uint32_t *ticket,
-                                              int *err) {
-  __shared__ double dg[TRSV_R][TRSV_R][NC];  // dg[q][r]: factor entry of row r, column q
-  __shared__ double pr[TRSV_B][TRSV_R][NC];  // negated products of one batch
-  __shared__ double ys[TRSV_B][NC];          // published values of one batch
-  __shared__ double xs[TRSV_R][NC];          // final values of the block
+template <int NC, bool FWD, int NR>
+__global__ __launch_bounds__(256) void k_trsv(const double *LU, int64_t lda, double *X, int64_t ldx,
+                                              int64_t nrhs, int64_t n, uint32_t *sync, int *err) {
+  constexpr int TRSV_B = trsv_b<NC, NR>();
+  __shared__ double dg[TRSV_R][TRSV_R][NC];      // dg[q][r]: factor entry of row r, column q
+  __shared__ double pr[NR][TRSV_B][TRSV_R][NC];  // negated products of one batch
+  __shared__ double ys[NR][TRSV_B][NC];          // published values of one batch
+  __shared__ double xs[NR][TRSV_R][NC];          // final values of the block
   __shared__ int s_avail, s_fail, s_blk, s_done;
+  uint32_t *ready = sync + 2 * blockIdx.y, *ticket = ready + 1;
   const int tid = threadIdx.x;
   if (tid == 0) s_blk = (int)atomicAdd(ticket, 1u);
   __syncthreads();
   const int64_t p0 = (int64_t)s_blk * TRSV_R;
   const int cnt = (int)(n - p0 < TRSV_R ? n - p0 : TRSV_R);
+  const int64_t f0 = (int64_t)blockIdx.y * NR;  // first right-hand side
+  const int nr = NR == 1 || nrhs - f0 >= NR ? NR : (int)(nrhs - f0);
   auto row = [&](int64_t p) { return FWD ? p : n - 1 - p; };
   auto L = [&](int64_t i, int64_t k) { return LU + (i + k * lda) * NC; };
+  double *const x0 = X + f0 * ldx * NC, *const x1 = x0 + (NR > 1 ? ldx * NC : 0);
+  auto x = [&](int f, int64_t i) { return (NR > 1 && f ? x1 : x0) + i * NC; };
   // the diagonal block (strict triangle, plus the diagonal backward); the
   // row index runs fastest, so each column is one contiguous read
   for (int e = tid; e < TRSV_R * TRSV_R * NC; e += 256) {
@@ -945,9 +896,12 @@ __global__ __launch_bounds__(256) void k_trsv(const double *LU, int64_t lda, dou
     if (q < cnt && r < cnt && (r > q || (!FWD && r == q)))
       dg[q][r][c] = L(row(p0 + r), row(p0 + q))[c];
   }
-  double v[NC];  // the row value of lane tid (wavefront 0, tid < cnt)
+  // lane: row rr of right-hand side f of this workgroup (wavefront 0)
+  const int rr = NR > 1 ? tid & (TRSV_R - 1) : tid, f = NR > 1 ? (tid >> 5) & 1 : 0;
+  const bool mine = NR > 1 ? tid < TRSV_R * NR && rr < cnt && f < nr : tid < cnt;
+  double v[NC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) v[c] = tid < cnt ? x[row(p0 + tid) * NC + c] : 0.0;
+  for (int c = 0; c < NC; ++c) v[c] = mine ? x(f, row(p0 + rr))[c] : 0.0;
   if (tid == 0) {
     s_fail = 0;
     s_done = 0;
@@ -959,12 +913,14 @@ __global__ __launch_bounds__(256) void k_trsv(const double *LU, int64_t lda, dou
       const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
       uint32_t spins = 0, w;
       while ((int64_t)(w = ld_dev_u32(ready)) <= applied) {
-        if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) { s_fail = 1; break; }
-        if ((++spins & 63u) == 0 && __builtin_amdgcn_s_memrealtime() - t0 > 100000000ull) {
-          __hip_atomic_store(err, 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (wait_expired(spins, t0, err, 3)) {
           s_fail = 1;
           break;
         }
+        // every waiting workgroup polls the same word, which holds up the one
+        // that advances it: rarely while the blocks before this one are many
+        if (p0 - (int64_t)w > 2 * TRSV_R) __builtin_amdgcn_s_sleep(32);
+        else __builtin_amdgcn_s_sleep(2);
       }
       s_avail = (int)((int64_t)w < p0 ? (int64_t)w : p0);
     }
@@ -974,25 +930,33 @@ __global__ __launch_bounds__(256) void k_trsv(const double *LU, int64_t lda, dou
     for (int64_t c0 = applied; c0 < avail; c0 += TRSV_B) {
       const int nb = (int)(avail - c0 < TRSV_B ? avail - c0 : TRSV_B);
       // published values: device-coherent loads, issued after the count was seen
-      if (tid < nb * NC) (&ys[0][0])[tid] = ld_dev_f64(x + row(c0 + tid / NC) * NC + tid % NC);
+      if (tid < nb * NC) {
+#pragma unroll
+        for (int g = 0; g < NR; ++g)
+          if (g < nr) (&ys[g][0][0])[tid] = ld_dev_f64(x(g, row(c0 + tid / NC)) + tid % NC);
+      }
       __syncthreads();
       for (int idx = tid; idx < cnt * nb; idx += 256) {
         const int q = idx % cnt, t = idx / cnt;
         double a[NC], y[NC], o[NC];
         ozx::load<NC>(L(row(p0 + q), row(c0 + t)), a);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) y[c] = ys[t][c];
-        ozx::mul<NC>(a, y, o);
+        for (int g = 0; g < NR; ++g) {
+          if (g >= nr) break;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) pr[t][q][c] = -o[c];
+          for (int c = 0; c < NC; ++c) y[c] = ys[g][t][c];
+          ozx::mul<NC>(a, y, o);
+#pragma unroll
+          for (int c = 0; c < NC; ++c) pr[g][t][q][c] = -o[c];
+        }
       }
       __syncthreads();
       // the subtractions, in order; the next batch's barrier waits for them
-      if (tid < cnt) {
+      if (mine) {
         for (int t = 0; t < nb; ++t) {
           double pv[NC], o[NC];
 #pragma unroll
-          for (int c = 0; c < NC; ++c) pv[c] = pr[t][tid][c];
+          for (int c = 0; c < NC; ++c) pv[c] = pr[f][t][rr][c];
           ozx::add<NC>(v, pv, o);
 #pragma unroll
           for (int c = 0; c < NC; ++c) v[c] = o[c];
@@ -1005,11 +969,10 @@ __global__ __launch_bounds__(256) void k_trsv(const double *LU, int64_t lda, dou
   if (tid < 64) {
     // wavefront 0: the diagonal block; the factor entries of the next step
     // are read from LDS while this one computes
-    const int lane = tid;
     double a[NC], u[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      a[c] = lane > 0 && lane < cnt ? dg[0][lane][c] : 0.0;
+      a[c] = rr > 0 && rr < cnt ? dg[0][rr][c] : 0.0;
       u[c] = FWD ? 0.0 : dg[0][0][c];
     }
     for (int q = 0; q < cnt; ++q) {
@@ -1017,10 +980,10 @@ __global__ __launch_bounds__(256) void k_trsv(const double *LU, int64_t lda, dou
       const int qn = q + 1 < cnt ? q + 1 : q;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        an[c] = lane > qn && lane < cnt ? dg[qn][lane][c] : 0.0;
+        an[c] = rr > qn && rr < cnt ? dg[qn][rr][c] : 0.0;
         un[c] = FWD ? 0.0 : dg[qn][qn][c];
       }
-      if (!FWD && lane == q) {
+      if (!FWD && rr == q && (NR == 1 || f < nr)) {
         double o[NC];
         ozx::div<NC>(v, u, o);
 #pragma unroll
@@ -1029,12 +992,18 @@ __global__ __launch_bounds__(256) void k_trsv(const double *LU, int64_t lda, dou
       // row q is final
       double y[NC];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) y[c] = readlane_f64(v[c], q);
-      if (lane == q) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) xs[q][c] = v[c];
+      for (int c = 0; c < NC; ++c) {
+        y[c] = readlane_f64(v[c], q);
+        if (NR > 1) {
+          const double y1 = readlane_f64(v[c], q + TRSV_R);
+          y[c] = f ? y1 : y[c];
+        }
       }
-      if (lane > q && lane < cnt) {
+      if (rr == q && (NR == 1 || f < nr)) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) xs[f][q][c] = v[c];
+      }
+      if (rr > q && rr < cnt && (NR == 1 || f < nr)) {
         double o[NC];
         ozx::fms<NC>(v, a, y, o);
 #pragma unroll
@@ -1042,7 +1011,7 @@ __global__ __launch_bounds__(256) void k_trsv(const double *LU, int64_t lda, dou
       }
       if ((q + 1) % TRSV_PUB == 0 || q + 1 == cnt) {
         // the group's values are in LDS before the count is raised
-        if (lane == 0)
+        if (tid == 0)
           __hip_atomic_store(&s_done, q + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
 #pragma unroll
@@ -1066,10 +1035,13 @@ __global__ __launch_bounds__(256) void k_trsv(const double *LU, int64_t lda, dou
         __builtin_amdgcn_s_sleep(1);
         continue;
       }
-      for (int e = lane; e < (d - done) * NC; e += 64) {
-        const int q = done + e / NC, c = e % NC;
-        x[row(p0 + q) * NC + c] = xs[q][c];
-      }
+#pragma unroll
+      for (int g = 0; g < NR; ++g)
+        if (g < nr)
+          for (int e = lane; e < (d - done) * NC; e += 64) {
+            const int q = done + e / NC, c = e % NC;
+            (g ? x1 : x0)[row(p0 + q) * NC + c] = xs[g][q][c];
+          }
       // this wavefront's stores complete before the count is raised
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       if (lane == 0)
@@ -1142,13 +1114,13 @@ template <int NC>
 static void trsm_l(int kb, dim3 g, hipStream_t s, const double *L, int64_t lda, double *X,
                    int64_t ldx, int64_t ncols) {
   if (kb <= 64)
-    hipLaunchKernelGGL((k_trsm_lower_unit_w<NC, 1>), dim3((unsigned)((ncols + 3) / 4)), dim3(256),
+    hipLaunchKernelGGL((k_trsm_w<NC, 1, false>), dim3((unsigned)((ncols + 3) / 4)), dim3(256),
                        0, s, L, lda, X, ldx, kb, ncols);
   else if (kb <= 128)
-    hipLaunchKernelGGL((k_trsm_lower_unit_w<NC, 2>), dim3((unsigned)((ncols + 1) / 2)),
+    hipLaunchKernelGGL((k_trsm_w<NC, 2, false>), dim3((unsigned)((ncols + 1) / 2)),
                        dim3(256), 0, s, L, lda, X, ldx, kb, ncols);
   else if (kb <= 256)
-    hipLaunchKernelGGL((k_trsm_lower_unit_w<NC, 4>), dim3((unsigned)ncols), dim3(256), 0, s, L,
+    hipLaunchKernelGGL((k_trsm_w<NC, 4, false>), dim3((unsigned)ncols), dim3(256), 0, s, L,
                        lda, X, ldx, kb, ncols);
   else
     hipLaunchKernelGGL((k_trsm_lower_unit<NC, 1, 2>), g, dim3(256), 0, s, L, lda, X, ldx, kb, ncols);
@@ -1167,20 +1139,24 @@ hipError_t launch_trsm_lower_unit(int nc, const double *L, int64_t lda, double *
 }
 
 template <int NC>
-static void trsm_u(int kb, dim3 g, hipStream_t s, const double *U, int64_t lda, double *X,
-                   int64_t ldx, int64_t ncols) {
-  if (kb <= 256) hipLaunchKernelGGL((k_trsm_upper<NC, 1, 1>), g, dim3(256), 0, s, U, lda, X, ldx, kb, ncols);
-  else hipLaunchKernelGGL((k_trsm_upper<NC, 1, 2>), g, dim3(256), 0, s, U, lda, X, ldx, kb, ncols);
+static void trsm_u(int kb, hipStream_t s, const double *U, int64_t lda, double *X, int64_t ldx,
+                   int64_t ncols) {
+#define OZ_TRSMU(WPC_)                                                                          \
+  hipLaunchKernelGGL((k_trsm_w<NC, WPC_, true>), dim3((unsigned)((ncols * WPC_ + 3) / 4)),      \
+                     dim3(256), 0, s, U, lda, X, ldx, kb, ncols)
+  if (kb <= 64) OZ_TRSMU(1);
+  else if (kb <= 128) OZ_TRSMU(2);
+  else OZ_TRSMU(4);
+#undef OZ_TRSMU
 }
 
 hipError_t launch_trsm_upper(int nc, const double *U, int64_t lda, double *X, int64_t ldx, int kb,
                              int64_t ncols, hipStream_t s) {
   if (ncols <= 0 || kb <= 0) return hipSuccess;
-  if (kb > 512) return hipErrorInvalidValue;
-  dim3 g((unsigned)ncols);
-  if (nc == 2) trsm_u<2>(kb, g, s, U, lda, X, ldx, ncols);
-  else if (nc == 3) trsm_u<3>(kb, g, s, U, lda, X, ldx, ncols);
-  else trsm_u<4>(kb, g, s, U, lda, X, ldx, ncols);
+  if (kb > 256) return hipErrorInvalidValue;
+  if (nc == 2) trsm_u<2>(kb, s, U, lda, X, ldx, ncols);
+  else if (nc == 3) trsm_u<3>(kb, s, U, lda, X, ldx, ncols);
+  else trsm_u<4>(kb, s, U, lda, X, ldx, ncols);
   return hipGetLastError();
 }
 
@@ -1225,21 +1201,36 @@ hipError_t launch_apply_ipiv(int nc, double *B, int64_t ldb, int64_t n, int64_t 
   return hipGetLastError();
 }
 
-hipError_t launch_trsv(int nc, int fwd, const double *LU, int64_t lda, double *x, int64_t n,
-                       uint32_t *sync, int *err, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  const int G = (int)((n + TRSV_R - 1) / TRSV_R);
-  // sync[0]: finished positions, sync[1]: ticket of the next row block
-  hipLaunchKernelGGL(k_fill_int, dim3(1), dim3(256), 0, s, (int *)sync, 0, (int64_t)2);
-#define OZ_TRSV(NC_, F_)                                                                      \
-  hipLaunchKernelGGL((k_trsv<NC_, F_>), dim3((unsigned)G), dim3(256), 0, s, LU, lda, x, n, sync, \
-                     sync + 1, err)
-  if (fwd) {
-    if (nc == 2) OZ_TRSV(2, true); else if (nc == 3) OZ_TRSV(3, true); else OZ_TRSV(4, true);
+bool trsv_fits(int64_t n, int64_t nrhs) {
+  return (n + TRSV_R - 1) / TRSV_R * ((nrhs + 1) / 2) <= TRSV_MAXGROUPS;
+}
+
+template <int NC>
+static void trsv_nc(int fwd, dim3 g, int nr, hipStream_t s, const double *LU, int64_t lda,
+                    double *X, int64_t ldx, int64_t nrhs, int64_t n, uint32_t *sync, int *err) {
+#define OZ_TRSV(F_, NR_)                                                                         \
+  hipLaunchKernelGGL((k_trsv<NC, F_, NR_>), g, dim3(256), 0, s, LU, lda, X, ldx, nrhs, n, sync, err)
+  if (nr == 1) {
+    if (fwd) OZ_TRSV(true, 1);
+    else OZ_TRSV(false, 1);
   } else {
-    if (nc == 2) OZ_TRSV(2, false); else if (nc == 3) OZ_TRSV(3, false); else OZ_TRSV(4, false);
+    if (fwd) OZ_TRSV(true, 2);
+    else OZ_TRSV(false, 2);
   }
 #undef OZ_TRSV
+}
+
+hipError_t launch_trsv(int nc, int fwd, const double *LU, int64_t lda, double *X, int64_t ldx,
+                       int64_t nrhs, int64_t n, uint32_t *sync, int *err, hipStream_t s) {
+  if (n <= 0 || nrhs <= 0) return hipSuccess;
+  const int nr = nrhs > 1 ? 2 : 1;
+  const dim3 g((unsigned)((n + TRSV_R - 1) / TRSV_R), (unsigned)((nrhs + nr - 1) / nr));
+  // per group: finished positions and the ticket of the next row block
+  hipLaunchKernelGGL(k_fill_int, dim3((2 * g.y + 255) / 256), dim3(256), 0, s, (int *)sync, 0,
+                     (int64_t)2 * g.y);
+  if (nc == 2) trsv_nc<2>(fwd, g, nr, s, LU, lda, X, ldx, nrhs, n, sync, err);
+  else if (nc == 3) trsv_nc<3>(fwd, g, nr, s, LU, lda, X, ldx, nrhs, n, sync, err);
+  else trsv_nc<4>(fwd, g, nr, s, LU, lda, X, ldx, nrhs, n, sync, err);
   return hipGetLastError();
 }
 

@@ -151,12 +151,16 @@ hipError_t launch_limb_sub(uint64_t *climb, int32_t *cexp, uint8_t *csign, int64
                            hipStream_t s);
 hipError_t launch_limb_zero(uint64_t *limb, int32_t *lexp, uint8_t *lsign, int64_t ld,
                             int64_t plane, int nlimb, int64_t M, int64_t N, hipStream_t s);
-// pipelined triangular solve of one right-hand side (fwd: unit lower,
-// ascending; else upper, descending, dividing by the diagonal); sync: two
-// device words owned by the caller (finished-position counter and row-block
-// ticket), reset by the launcher
-hipError_t launch_trsv(int nc, int fwd, const double *LU, int64_t lda, double *x, int64_t n,
-                       uint32_t *sync, int *err, hipStream_t s);
+// pipelined triangular solve (fwd: unit lower, ascending; else upper,
+// descending, dividing by the diagonal); sync: two device words owned by the
+// caller per right-hand side, or per pair of them (finished-position counter
+// and row-block ticket), reset by the launcher
+hipError_t launch_trsv(int nc, int fwd, const double *LU, int64_t lda, double *X, int64_t ldx,
+                       int64_t nrhs, int64_t n, uint32_t *sync, int *err, hipStream_t s);
+// row blocks x pairs of right-hand sides that are on the chip at once (two
+// workgroups per CU); beyond it the pipelines would run in turns
+constexpr int TRSV_MAXGROUPS = 512;
+bool trsv_fits(int64_t n, int64_t nrhs);
 
 // batched LU + solve (k_batch.hip); items in processing order, each with its
 // caller-order index in `reserved`
