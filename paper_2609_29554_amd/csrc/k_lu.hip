@@ -228,8 +228,10 @@ __global__ __launch_bounds__(PANEL_NT) void k_panel(double *A, int64_t lda, int6
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   // the panel is the critical path of the factorisation, and with
   // look-ahead the previous step's Schur update runs beside it on the same
-  // CUs: its wavefronts take the SIMDs' issue slots first
-  __builtin_amdgcn_s_setprio(3);
+  // CUs: its wavefronts take the SIMDs' issue slots first, and wavefront 0,
+  // which walks the chain, before the one it shares a SIMD with
+  if (threadIdx.x < 64) __builtin_amdgcn_s_setprio(3);
+  else __builtin_amdgcn_s_setprio(2);
   const int nr = (int)(n - k);
   const int G = gridDim.x, wg = blockIdx.x, tid = threadIdx.x;
   double *rows = (double *)smem_raw;                 // R * kb * NC
@@ -327,6 +329,18 @@ __global__ __launch_bounds__(PANEL_NT) void k_panel(double *A, int64_t lda, int6
         const bool two = g0 + 64 < G;
         const uint64_t *la = LINE(buf, g0), *lb = LINE(buf, two ? g0 + 64 : g0);
         uint64_t wa[2 + 2 * NC], wb[2 + 2 * NC];
+        // many lines: only the last word of each until it is there, since the
+        // readers' traffic grows with the square of the workgroups (getrf QD n
+        // = 2048 25.5 -> 25.0 ms; DD n = 130, 8 workgroups, 0.82 -> 0.85)
+        while (G > 32) {
+          const uint64_t ea = ld_dev_u64(la + 1 + 2 * NC), eb = ld_dev_u64(lb + 1 + 2 * NC);
+          if ((uint32_t)(ea >> 32) == tag && (uint32_t)(eb >> 32) == tag) break;
+          if (wait_expired(spins, t0, err)) {
+            expired = true;
+            break;
+          }
+        }
+        if (expired) break;
         for (;;) {
 #pragma unroll
           for (int q = 0; q < 2 + 2 * NC; ++q) wa[q] = ld_dev_u64(la + q);
