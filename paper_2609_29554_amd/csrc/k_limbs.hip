@@ -16,9 +16,9 @@
 //        per element in workspace (word k of element e at cw[k*E + e]): the
 //        groups arrive in increasing order, so each one rewrites only its own
 //        window and the sign extension above it is carried as a small integer;
-//   (S6) k_limb_round: c = RN_p(cbar 2^eps), ties to even; mode 1 then
-//        k_limb_sub: C = RN_p(C - c), the exact difference on a grid with a
-//        guard word and a sticky bit, rounded once.
+//   (S6) c = RN_p(cbar 2^eps), ties to even, and in mode 1 C = RN_p(C - c):
+//        k_limb_finish, or k_limb_round and k_limb_sub (the exact difference
+//        on a grid with a guard word and a sticky bit, rounded once).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,6 +28,8 @@
 #include "ozii_elem.hpp"
 #include "ozii_kernels.hpp"
 #include "ozii_stage.hpp"
+#include "lanes.hpp"
+#include "limbfp.hpp"
 
 using namespace ozk;
 using ozl::LimbOperand;
@@ -267,14 +269,15 @@ __global__ __launch_bounds__(256) void k_producer_limbs(LimbOperand A, LimbOpera
 }
 
 // ---------------------------------------------------------------------------
-// (S5): cbar = sum_gi Sbar_(g0+gi) 2^(w gi) per element, words in cw.
+// (S5) on the binary64 moduli: cbar = sum_gi Sbar_(g0+gi) 2^(w gi) per
+// element, words in cw.
 // Invariant after each group: cbar = sum_(k < hw) cw[k] 2^(32k) + pend 2^(32 hw)
 // with hw uniform.  Group gi adds V = Sbar 2^(b0) (nvw words, sign-extended
 // by fill) at word q0 = floor(w gi / 32).  After the last group the final
 // pend (0 or -1, the sign) is stored at word hw.
 // ---------------------------------------------------------------------------
-template <int ND, class TT>
-__global__ __launch_bounds__(256) void k_consumer_limbs(const TT *__restrict__ tpl,
+template <int ND>
+__global__ __launch_bounds__(256) void k_consumer_limbs(const uint32_t *__restrict__ tpl,
                                                         int64_t Mp, int64_t Np, int64_t M,
                                                         int64_t N, const DevPlan *__restrict__ pl,
                                                         int nvw, uint32_t *__restrict__ cw,
@@ -292,11 +295,7 @@ __global__ __launch_bounds__(256) void k_consumer_limbs(const TT *__restrict__ t
   int32_t pend = 0;
   for (int gi = 0; gi < ng; ++gi) {
     int32_t d[ND];
-    const TT *tg = tpl + ((int64_t)gi * nmod * Np + j) * Mp + i;
-    if constexpr (sizeof(TT) == 1)
-      crt_group_bytes<2 * ND>(tg, ps, nmod, pl, d);  // byte back-ends
-    else
-      crt_digits<ND, TT>(tg, ps, pl, d);              // binary64 moduli
+    crt_digits<ND, uint32_t>(tpl + ((int64_t)gi * nmod * Np + j) * Mp + i, ps, pl, d);
     const uint32_t fill = d[ND - 1] < 0 ? 0xffffffffu : 0u;
     uint32_t st[ND / 2];
 #pragma unroll
@@ -337,6 +336,69 @@ __global__ __launch_bounds__(256) void k_consumer_limbs(const TT *__restrict__ t
     hw = kend;
   }
   AT(hw) = (uint32_t)pend;
+}
+
+// ---------------------------------------------------------------------------
+// (S5) on the byte back-ends, one wavefront per 64 consecutive elements of a
+// column: the digits of each group come from the matrix-core CRT of the
+// expansion consumer, and the sum slides through a window of NR registers.
+// Group gi adds Sbar 2^(w gi mod 32) at the window's word 0, which stands for
+// word q = floor(w gi / 32); the words below the next group's q are final and
+// leave the window, each stored once.  |Sbar| < 2^(16 ND - 1), the shift is
+// below 32 and the earlier groups add less than one more bit, so 32 NR >= 16
+// ND + 64 bits hold the two's complement sum.  Bound by the CRT's integer
+// work and the t-planes.  p = 4096, 768 x 768 outputs: dot-product CRT and
+// a sum in memory, read and rewritten by every group, 883 us -> 591 us.
+// ---------------------------------------------------------------------------
+template <int ND>
+__global__ __launch_bounds__(64) void k_consumer_limbs_mx(const uint8_t *__restrict__ tpl,
+                                                          int64_t Mp, int64_t Np, int64_t M,
+                                                          int64_t N,
+                                                          const DevPlan *__restrict__ pl,
+                                                          uint32_t *__restrict__ cw, int64_t E) {
+  constexpr int NR = ND / 2 + 2;
+  __shared__ __attribute__((aligned(16))) int32_t buf[32 * MX_CBS];
+  const int lane = (int)threadIdx.x;
+  int64_t bx, j;
+  xcd_block(bx, j);
+  const int64_t i0 = bx * 64, i = i0 + lane;
+  const int nmod = pl->nmod, w = pl->w, ng = pl->ng;
+  mxv4 tab[MX_BLK];
+#pragma unroll
+  for (int b = 0; b < MX_BLK; ++b) tab[b] = *(const mxv4 *)&pl->crtm[b][lane][0];
+  const bool valid = i < M;
+  uint32_t *col = cw + (valid ? i + j * M : 0);
+  const int64_t ps = Np * Mp;
+  uint32_t win[NR];
+#pragma unroll
+  for (int k = 0; k < NR; ++k) win[k] = 0u;
+  int q0 = 0;
+  for (int gi = 0; gi < ng; ++gi) {
+    int32_t d[ND];
+    crt_group_mx<2 * ND>(tpl + (int64_t)gi * nmod * ps + j * Mp + i0, ps, nmod, pl, tab, buf, lane, d);
+    const uint32_t fill = d[ND - 1] < 0 ? 0xffffffffu : 0u;
+    const uint32_t b0 = (uint32_t)(w * gi) & 31u;
+    uint32_t prev = 0u, carry = 0u;
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const uint32_t cur = k < ND / 2 ? ((uint32_t)d[2 * k < ND ? 2 * k : 0] & 0xffffu) |
+                                            ((uint32_t)d[2 * k < ND ? 2 * k + 1 : 0] << 16)
+                                      : fill;
+      const uint32_t v = b0 ? __builtin_amdgcn_alignbit(cur, prev, 32u - b0) : cur;
+      unsigned co;
+      win[k] = __builtin_addc(win[k], v, carry, &co);
+      carry = co;
+      prev = cur;
+    }
+    const int qn = gi + 1 < ng ? (w * (gi + 1)) >> 5 : q0 + NR;
+    for (; q0 < qn; ++q0) {
+      if (valid) col[(int64_t)q0 * E] = win[0];
+      const uint32_t sg = (uint32_t)((int32_t)win[NR - 1] >> 31);
+#pragma unroll
+      for (int k = 0; k + 1 < NR; ++k) win[k] = win[k + 1];
+      win[NR - 1] = sg;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -546,6 +608,103 @@ __global__ __launch_bounds__(256) void k_limb_sub(uint64_t *__restrict__ climb,
   round_to_limbs(DM, nwd, sticky, nlimb, (int64_t)ex - p - 32, sx, climb, planec, ci, cexp, csign);
 }
 
+// ---------------------------------------------------------------------------
+// (S6) and the update in one pass, nl <= 64: c = RN_p(cbar 2^eps), then C = c
+// (mode 0) or C = RN_p(C - c) (mode 1), in the lane-distributed arithmetic of
+// limbfp.hpp.  A workgroup takes FE consecutive elements of a column: the
+// sum's words and C's limbs come in whole lines, plane by plane, and are
+// turned in LDS so that a wavefront has one element with a limb per lane; the
+// results leave the same way.  Reads and writes everything once.  p = 4096,
+// 768 x 768 update: rounding into a temporary, then a subtraction through a
+// second one, 934 us -> 422 us.
+// ---------------------------------------------------------------------------
+constexpr int FE = 32;
+__global__ __launch_bounds__(256) void k_limb_finish(
+    const uint32_t *__restrict__ cw, int64_t E, int nwords, int64_t M, const int32_t *__restrict__ ea,
+    const int32_t *__restrict__ eb, int w, int g0, int Q, int nl, int mode, uint64_t *climb,
+    int32_t *cexp, uint8_t *csign, int64_t ldc, int64_t planec) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int ws = nwords | 1, ls = nl | 1;  // odd strides
+  uint64_t *sc = (uint64_t *)smem_raw;     // FE * ls limbs
+  int32_t *sx = (int32_t *)(sc + FE * ls);  // exponents
+  int32_t *ss = sx + FE;                    // signs
+  uint32_t *sw = (uint32_t *)(ss + FE);     // FE * ws words
+  const int t = threadIdx.x, wv = t >> 6, l = lfp::lane_id();
+  const int64_t i0 = (int64_t)blockIdx.x * FE, j = blockIdx.y;
+  const int cnt = (int)(M - i0 < FE ? M - i0 : FE);
+  const int e0 = t & (FE - 1), k0 = t / FE;
+  const uint32_t *src = cw + i0 + e0 + j * M;
+  const int64_t ci = i0 + e0 + j * ldc;
+  if (e0 < cnt) {
+#pragma unroll 8
+    for (int k = k0; k < nwords; k += 256 / FE) sw[e0 * ws + k] = src[(int64_t)k * E];
+    if (mode) {
+#pragma unroll 8
+      for (int q = k0; q < nl; q += 256 / FE) sc[e0 * ls + q] = climb[(int64_t)q * planec + ci];
+      if (k0 == 0) {
+        sx[e0] = cexp[ci];
+        ss[e0] = csign[ci];
+      }
+    }
+  }
+  __syncthreads();
+  const int32_t ej = eb[j];
+  for (int e = wv; e < cnt; e += 4) {
+    const int32_t ei = ea[i0 + e];
+    const uint32_t *we = sw + e * ws;
+    const uint32_t sign = __builtin_amdgcn_readfirstlane((int)we[nwords - 1]) < 0 ? 1u : 0u;
+    const uint32_t ext = sign ? 0xffffffffu : 0u;
+    auto limb = [&](int q) -> uint64_t {
+      const int k = 2 * q;
+      const uint32_t a = k < nwords ? we[k] : ext, b = k + 1 < nwords ? we[k + 1] : ext;
+      return ((uint64_t)b << 32) | a;
+    };
+    lfp::W2 v;
+    v.lo = limb(l);
+    v.hi = limb(l + 64);
+    if (sign) {
+      lfp::W2 z;
+      z.lo = 0;
+      z.hi = 0;
+      v.lo = ~v.lo;
+      v.hi = ~v.hi;
+      uint32_t co;
+      v = lfp::add2(v, z, 1u, co);
+    }
+    lfp::WF r = lfp::wf_zero();
+    if (ei != EXP_ZERO && ej != EXP_ZERO && lfp::ballot((v.lo | v.hi) != 0) != 0) {
+      const int64_t eps = (int64_t)w * g0 - (Q - 1 - (int64_t)ei) - (Q - 1 - (int64_t)ej);
+      int64_t bl;
+      r.m = lfp::round_win(v, 0u, nl, bl);
+      r.e = (int32_t)(bl + eps);
+      r.s = sign;
+    }
+    if (mode) {
+      // C - 0 leaves C as it is
+      if (lfp::is_zero(r)) continue;
+      lfp::WF c;
+      c.m = l < nl ? sc[e * ls + l] : 0ull;
+      c.e = __builtin_amdgcn_readfirstlane(sx[e]);
+      c.s = (uint32_t)__builtin_amdgcn_readfirstlane(ss[e]) & 1u;
+      if (!(lfp::ballot(c.m != 0) >> (nl - 1))) c = lfp::wf_zero();  // top limb 0
+      r = lfp::add(c, r, 1u, nl);
+    }
+    if (l < nl) sc[e * ls + l] = r.m;
+    if (l == 0) {
+      sx[e] = r.e;
+      ss[e] = (int32_t)r.s;
+    }
+  }
+  __syncthreads();
+  if (e0 < cnt) {
+    for (int q = k0; q < nl; q += 256 / FE) climb[(int64_t)q * planec + ci] = sc[e0 * ls + q];
+    if (k0 == 0) {
+      cexp[ci] = sx[e0];
+      csign[ci] = (uint8_t)ss[e0];
+    }
+  }
+}
+
 __global__ void k_limb_zero(uint64_t *limb, int32_t *lexp, uint8_t *lsign, int64_t ld,
                             int64_t plane, int nlimb, int64_t M, int64_t N) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -627,26 +786,63 @@ hipError_t launch_producer_limbs(const LimbOperand &A, const LimbOperand &B, int
   return hipGetLastError();
 }
 
+int limb_sum_words(int nd, int tbytes, int w, int ng, int nvw_words) {
+  if (tbytes != 1) return nvw_words;
+  return ((w * (ng - 1)) >> 5) + (nd <= 18 ? 18 : 24) / 2 + 2;
+}
+
 hipError_t launch_consumer_limbs(const void *tpl, int tbytes, int64_t Mp, int64_t Np, int64_t M,
                                  int64_t N, const DevPlan *pl, int nd, int nvw, uint32_t *cw,
                                  hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  dim3 g((unsigned)((M + 255) / 256), (unsigned)N);
   const int ndc = nd <= 18 ? 18 : (nd <= 24 ? 24 : 32);
-  if (nd > 32 || (tbytes == 1 && nd > 24) || (tbytes != 1 && tbytes != 4) ||
-      nvw > ndc / 2 + 1)
-    return hipErrorInvalidValue;
-#define OZ_CONSL(ND_, TT_)                                                                       \
-  hipLaunchKernelGGL((k_consumer_limbs<ND_, TT_>), g, dim3(256), 0, s, (const TT_ *)tpl, Mp, Np, \
-                     M, N, pl, nvw, cw, M * N)
+  if (nd > 32 || (tbytes == 1 && nd > 24) || (tbytes != 1 && tbytes != 4)) return hipErrorInvalidValue;
   if (tbytes == 1) {
-    if (ndc == 18) OZ_CONSL(18, uint8_t);
-    else OZ_CONSL(24, uint8_t);
-  } else {
-    if (ndc == 18) OZ_CONSL(18, uint32_t);
-    else OZ_CONSL(32, uint32_t);
+    // 64-element wavefronts read whole plane rows
+    if ((M + 63) / 64 * 64 > Mp) return hipErrorInvalidValue;
+    const dim3 gx((unsigned)((M + 63) / 64), (unsigned)N);
+    if (ndc == 18)
+      hipLaunchKernelGGL(k_consumer_limbs_mx<18>, gx, dim3(64), 0, s, (const uint8_t *)tpl, Mp, Np, M,
+                         N, pl, cw, M * N);
+    else
+      hipLaunchKernelGGL(k_consumer_limbs_mx<24>, gx, dim3(64), 0, s, (const uint8_t *)tpl, Mp, Np, M,
+                         N, pl, cw, M * N);
+    return hipGetLastError();
   }
+  if (nvw > ndc / 2 + 1) return hipErrorInvalidValue;
+  dim3 g((unsigned)((M + 255) / 256), (unsigned)N);
+#define OZ_CONSL(ND_)                                                                              \
+  hipLaunchKernelGGL(k_consumer_limbs<ND_>, g, dim3(256), 0, s, (const uint32_t *)tpl, Mp, Np, M, \
+                     N, pl, nvw, cw, M * N)
+  if (ndc == 18) OZ_CONSL(18);
+  else OZ_CONSL(32);
 #undef OZ_CONSL
+  return hipGetLastError();
+}
+
+// One wavefront per element costs 0.2 ns an element whatever nl; a thread per
+// element costs less than that for few limbs, but walks its words one by one.
+// Measured (whole product, us, separate kernels / one pass), 640 x 640 x 64 and
+// 40 x 30 x 40: mode 0  nl 4: 100 / 173, 35.2 / 34.5   nl 16: 305 / 362, 80 / 70
+// nl 32: 653 / 655, 144 / 119   nl 49: 1050 / 1037, 217 / 181; mode 1  nl 4:
+// 131 / 245, 52.4 / 46.8   nl 16: 422 / 457, 117 / 84   nl 32: 886 / 770,
+// 204 / 134.  The break-even counts of elements between the two sizes grow
+// about as nl^2.
+bool limb_finish_fits(int nl, int nwords, int64_t M, int64_t N, int mode) {
+  if (nl > 64 || nwords > 256) return false;
+  return nl >= 32 || (double)M * (double)N <= (mode ? 768.0 : 256.0) * nl * nl;
+}
+
+hipError_t launch_limb_finish(const uint32_t *cw, int nwords, int64_t M, int64_t N,
+                              const int32_t *ea, const int32_t *eb, int w, int g0, int Q, int nlimb,
+                              int mode, uint64_t *climb, int32_t *cexp, uint8_t *csign, int64_t ldc,
+                              int64_t planec, hipStream_t s) {
+  if (M <= 0 || N <= 0) return hipSuccess;
+  // at most 49.4 KiB (nl 64, 256 words)
+  const size_t lds = (size_t)FE * ((nlimb | 1) * 8 + 8 + (nwords | 1) * 4);
+  hipLaunchKernelGGL(k_limb_finish, dim3((unsigned)((M + FE - 1) / FE), (unsigned)N), dim3(256),
+                     (unsigned)lds, s, cw, M * N, nwords, M, ea, eb, w, g0, Q, nlimb, mode, climb, cexp,
+                     csign, ldc, planec);
   return hipGetLastError();
 }
 

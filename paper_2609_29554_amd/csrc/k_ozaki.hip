@@ -900,19 +900,6 @@ __global__ __launch_bounds__(256) void k_consumer(const TT *__restrict__ tpl, in
 }
 
 
-// Block (x, y) of a 2-D grid in an XCD-aware order: workgroups are dispatched
-// to the 8 XCDs in turn, so each XCD is given a contiguous range of logical
-// blocks; neighbouring 64-element blocks of a column then share an L2 and
-// each 128-byte line of a t-plane row is fetched from HBM once.
-__device__ __forceinline__ void xcd_block(int64_t &bx, int64_t &by) {
-  const int64_t gx = gridDim.x, nb = gx * gridDim.y;
-  const int64_t pid = blockIdx.x + gx * blockIdx.y;
-  const int64_t xcd = pid & 7, loc = pid >> 3, qd = nb >> 3, rm = nb & 7;
-  const int64_t lt = (xcd < rm ? xcd * (qd + 1) : rm * (qd + 1) + (xcd - rm) * qd) + loc;
-  bx = lt % gx;
-  by = lt / gx;
-}
-
 template <int NC, int NWC, int NB>
 __global__ __launch_bounds__(64) void k_consumer_mx(const uint8_t *__restrict__ tpl, int64_t Mp,
                                                     int64_t Np, double *__restrict__ C,
@@ -1105,26 +1092,8 @@ __global__ __launch_bounds__(256) void k_crt_export(const TT *__restrict__ tpl, 
   }
 }
 
-// byte back-ends (INT8, FP8): the group sums of crt_group_bytes<NB>, the
-// CRT that k_consumer_limbs and the fused kernel run (k_consumer_mx forms
-// the same digits on the matrix cores), with the same NB
-template <int NB>
-__global__ __launch_bounds__(256) void k_crt_export_b(const uint8_t *__restrict__ tpl, int64_t Mp,
-                                                      int64_t Np, int64_t M, int64_t N,
-                                                      const DevPlan *__restrict__ pl,
-                                                      uint64_t *out, int nlimb) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t j = blockIdx.y;
-  if (i >= M || j >= N) return;
-  const int nmod = pl->nmod;
-  for (int gi = 0; gi < pl->ng; ++gi) {
-    int32_t d[NB / 2];
-    crt_group_bytes<NB>(tpl + ((int64_t)gi * nmod * Np + j) * Mp + i, Np * Mp, nmod, pl, d);
-    store_sbar_limbs<NB / 2>(d, out + (((int64_t)gi * N + j) * M + i) * nlimb, nlimb);
-  }
-}
-
-// The group sums of k_consumer_mx's own route, exported like k_crt_export_b.
+// byte back-ends (INT8, FP8): the group sums by the route of k_consumer_mx and
+// k_consumer_limbs_mx, with the same NB
 template <int NB>
 __global__ __launch_bounds__(64) void k_crt_export_mx(const uint8_t *__restrict__ tpl, int64_t Mp,
                                                       int64_t Np, int64_t M, int64_t N,
@@ -1398,11 +1367,9 @@ hipError_t launch_fused_b(int nc, int nwc, int nd, const int8_t *pa, const int8_
 
 hipError_t launch_crt_export(const void *tpl, int tbytes, int nd, int64_t Mp, int64_t Np,
                              int64_t M, int64_t N, const DevPlan *pl, uint64_t *out, int nlimb,
-                             int mx, hipStream_t s) {
+                             hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  dim3 g((unsigned)((M + 255) / 256), (unsigned)N);
-  if (tbytes == 1 && mx) {
-    // the route of k_consumer_mx (expansion products)
+  if (tbytes == 1) {
     if (nd > 24 || (M + 63) / 64 * 64 > Mp) return hipErrorInvalidValue;
     dim3 gx((unsigned)((M + 63) / 64), (unsigned)N);
     if (nd <= 18)
@@ -1413,20 +1380,9 @@ hipError_t launch_crt_export(const void *tpl, int tbytes, int nd, int64_t Mp, in
                          N, pl, out, nlimb);
     return hipGetLastError();
   }
-  if (tbytes == 1) {
-    // the byte-column count of the consumers (launch_consumer, the limb
-    // consumer): 36 up to 18 digits, else 48
-    if (nd > 24) return hipErrorInvalidValue;
-    if (nd <= 18)
-      hipLaunchKernelGGL(k_crt_export_b<36>, g, dim3(256), 0, s, (const uint8_t *)tpl, Mp, Np, M,
-                         N, pl, out, nlimb);
-    else
-      hipLaunchKernelGGL(k_crt_export_b<48>, g, dim3(256), 0, s, (const uint8_t *)tpl, Mp, Np, M,
-                         N, pl, out, nlimb);
-  } else {
-    hipLaunchKernelGGL(k_crt_export<uint32_t>, g, dim3(256), 0, s, (const uint32_t *)tpl, Mp, Np,
-                       M, N, pl, out, nlimb);
-  }
+  dim3 g((unsigned)((M + 255) / 256), (unsigned)N);
+  hipLaunchKernelGGL(k_crt_export<uint32_t>, g, dim3(256), 0, s, (const uint32_t *)tpl, Mp, Np, M,
+                     N, pl, out, nlimb);
   return hipGetLastError();
 }
 

@@ -753,7 +753,7 @@ ozII_status gemm_impl(ozII_ctx *h, int mode, int nc, int64_t M, int64_t N, int64
     return hip_fail(h, e, "copy planesB");
   if (tpl_out && (e = hipMemcpyAsync(tpl_out, tpl, (size_t)L.tplBytes, hipMemcpyDeviceToDevice, s)) != hipSuccess)
     return hip_fail(h, e, "copy tpl");
-  if (sbar_out && (e = ozl::launch_crt_export(tpl, hp->t_bytes(), hp->nd, L.Mp, L.Np, M, N, dp, sbar_out, nlimb, 1, s)) != hipSuccess)
+  if (sbar_out && (e = ozl::launch_crt_export(tpl, hp->t_bytes(), hp->nd, L.Mp, L.Np, M, N, dp, sbar_out, nlimb, s)) != hipSuccess)
     return hip_fail(h, e, "crt_export");
   {
     ProfScope ps(h, OZ_STAGE_CONSUMER, (double)M * N * (t_bytes + 8.0 * nc * (mode ? 2 : 1)), 0, s);
@@ -813,9 +813,12 @@ ozII_status gemm_limbs_impl(ozII_ctx *h, int mode, int nlimb, int64_t M, int64_t
   int nvw = 0, nwords = 0;
   limb_words(*hp, &nvw, &nwords);
   if (nvw > hp->nd / 2 + 1) return fail(h, OZII_EUNSUPPORTED, "group sum wider than its digits");
+  nwords = ozl::limb_sum_words(hp->nd, hp->t_bytes(), hp->w, hp->ng, nwords);
+  const bool finish = ozl::limb_finish_fits(nlimb, nwords, M, N, mode);
   GemmLayout L = gemm_layout(*hp, M, N, K, o ? o->gemm_tile : 0);
-  // after the planes and t-planes: the group-sum columns (reused as the
-  // update's scratch), then the rounded product of mode 1
+  // after the planes and t-planes: the group-sum columns; where the last two
+  // steps are kernels of their own, these are the update's scratch too and
+  // the rounded product of mode 1 follows
   const int64_t MN = M * N;
   const size_t cw_words = (size_t)std::max(nwords, 2 * nlimb + 2);
   const size_t off_cw = (L.total + 255) / 256 * 256;
@@ -823,7 +826,7 @@ ozII_status gemm_limbs_impl(ozII_ctx *h, int mode, int nlimb, int64_t M, int64_t
   const size_t off_te = off_tl + ((size_t)nlimb * MN * 8 + 255) / 256 * 256;
   const size_t off_ts = off_te + ((size_t)MN * 4 + 255) / 256 * 256;
   const size_t total = off_ts + ((size_t)MN + 255) / 256 * 256;
-  st = ensure_ws(h, mode ? total : off_tl);
+  st = ensure_ws(h, mode && !finish ? total : off_tl);
   if (st != OZII_OK) return st;
   int32_t *ea = (int32_t *)(h->ws + L.off_ea);
   int32_t *eb = (int32_t *)(h->ws + L.off_eb);
@@ -868,15 +871,23 @@ ozII_status gemm_limbs_impl(ozII_ctx *h, int mode, int nlimb, int64_t M, int64_t
     if (e != hipSuccess) return hip_fail(h, e, "modular gemm");
   }
   if (sbar_out && (e = ozl::launch_crt_export(tpl, hp->t_bytes(), hp->nd, L.Mp, L.Np, M, N, dp,
-                                              sbar_out, nlimb_out, 0, s)) != hipSuccess)
+                                              sbar_out, nlimb_out, s)) != hipSuccess)
     return hip_fail(h, e, "crt_export");
   {
-    // t-planes read once, each group's window of the sum read and written
+    // t-planes read once, the sum written (binary64: each group's window of
+    // it read and written)
     ProfScope ps(h, OZ_STAGE_CONSUMER,
-                 (double)M * N * (t_bytes + 8.0 * nvw * hp->ng), 0);
+                 (double)M * N * (t_bytes + (f64 ? 8.0 * nvw * hp->ng : 4.0 * nwords)), 0);
     if ((e = ozl::launch_consumer_limbs(tpl, hp->t_bytes(), L.Mp, L.Np, M, N, dp, hp->nd, nvw, cw,
                                         s)) != hipSuccess)
       return hip_fail(h, e, "limb consumer");
+  }
+  if (finish) {  // sum read, C written, and read for the update
+    ProfScope ps(h, OZ_STAGE_ROUND, (double)M * N * (4.0 * nwords + (mode ? 2.0 : 1.0) * in_bytes), 0);
+    if ((e = ozl::launch_limb_finish(cw, nwords, M, N, ea, eb, hp->w, hp->g0, hp->Q, nlimb, mode,
+                                     C->limb, C->exp, C->sign, C->ld, C->plane, s)) != hipSuccess)
+      return hip_fail(h, e, "limb finish");
+    return OZII_OK;
   }
   // rounding: the group-sum column read, the p-bit product written (to C, or
   // to the temporary product of mode 1); update: C and the product read, the

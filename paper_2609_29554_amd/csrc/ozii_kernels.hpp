@@ -87,12 +87,11 @@ hipError_t launch_consumer(int nc, int nwc, int nd, const void *tpl, int tbytes,
                            const int32_t *ea, const int32_t *eb, const DevPlan *pl, int mode,
                            hipStream_t s);
 // group sums exported by the CRT routine of the consumer that reads these
-// t-planes (byte back-ends: mx = 1 the matrix-core route of the expansion
-// consumer, mx = 0 crt_group_bytes of the limb consumer, with the consumer's
+// t-planes (byte back-ends: the matrix-core route, with the consumer's
 // byte-column count for nd digits; binary64 moduli: crt_digits)
 hipError_t launch_crt_export(const void *tpl, int tbytes, int nd, int64_t Mp, int64_t Np,
                              int64_t M, int64_t N, const DevPlan *pl, uint64_t *out, int nlimb,
-                             int mx, hipStream_t s);
+                             hipStream_t s);
 
 // LU pieces
 size_t panel_lds_bytes(int nc, int kb, int R, int64_t nr);
@@ -138,6 +137,16 @@ bool producer_limbs_owns_exponents(const LimbOperand &A, const LimbOperand &B, i
 hipError_t launch_producer_limbs(const LimbOperand &A, const LimbOperand &B, int nlimb, int64_t K,
                                  int64_t Kp, const DevPlan *pl, int nmod, int nwt, int kind,
                                  hipStream_t s);
+// words per element of the exact sum that launch_consumer_limbs writes; words:
+// the number of the binary64 back-end's walk
+int limb_sum_words(int nd, int tbytes, int w, int ng, int words);
+// whether launch_limb_finish takes numbers of nlimb limbs from sums of nwords
+// words (else launch_limb_round and launch_limb_sub)
+bool limb_finish_fits(int nlimb, int nwords, int64_t M, int64_t N, int mode);
+hipError_t launch_limb_finish(const uint32_t *cw, int nwords, int64_t M, int64_t N,
+                              const int32_t *ea, const int32_t *eb, int w, int g0, int Q, int nlimb,
+                              int mode, uint64_t *climb, int32_t *cexp, uint8_t *csign, int64_t ldc,
+                              int64_t planec, hipStream_t s);
 hipError_t launch_consumer_limbs(const void *tpl, int tbytes, int64_t Mp, int64_t Np, int64_t M,
                                  int64_t N, const DevPlan *pl, int nd, int nvw, uint32_t *cw,
                                  hipStream_t s);

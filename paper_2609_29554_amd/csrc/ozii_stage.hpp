@@ -231,6 +231,19 @@ __device__ __forceinline__ void consume_element_b(const uint8_t *tbase, int64_t 
   }
 }
 
+// Block (x, y) of a 2-D grid in an XCD-aware order: workgroups are dispatched
+// to the 8 XCDs in turn, so each XCD is given a contiguous range of logical
+// blocks; neighbouring 64-element blocks of a column then share an L2 and
+// each 128-byte line of a t-plane row is fetched from HBM once.
+__device__ __forceinline__ void xcd_block(int64_t &bx, int64_t &by) {
+  const int64_t gx = gridDim.x, nb = gx * gridDim.y;
+  const int64_t pid = blockIdx.x + gx * blockIdx.y;
+  const int64_t xcd = pid & 7, loc = pid >> 3, qd = nb >> 3, rm = nb & 7;
+  const int64_t lt = (xcd < rm ? xcd * (qd + 1) : rm * (qd + 1) + (xcd - rm) * qd) + loc;
+  bx = lt % gx;
+  by = lt / gx;
+}
+
 // ---------------------------------------------------------------------------
 // (S5)+(S6) consumer of the byte back-ends with the CRT's column sums on the
 // matrix cores.  One wavefront (a workgroup of its own) takes 64 consecutive
