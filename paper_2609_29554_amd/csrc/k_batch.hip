@@ -2,7 +2,8 @@
 // (the batched configuration: 256 independent DD / QD systems of order 64 to
 // 512).  Every workgroup takes matrices from a device work queue -- the host
 // orders the batch by decreasing cost (longest-processing-time first) -- and
-// factors and solves each one alone with the expansion arithmetic of
+// factors and solves each one alone (with the Ozaki-II update: helped by the
+// workgroups that have none left) with the expansion arithmetic of
 // expansion.hpp: unblocked right-looking LU with partial pivoting (LAPACK's
 // i?amax, whole-row interchanges), then the solve with the factors.  Per
 // element the operations come in exactly the order of ozII_getrf with b = 1
@@ -11,6 +12,8 @@
 // with a kernel, so it can be captured in a hipGraph.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "../../include/ozii.h"
 #include "expansion.hpp"
@@ -240,6 +243,43 @@ __device__ void solve_one(const ozII_batch_item &it) {
   }
 }
 
+// a <- a - l u over the mr x mc elements (i, c) of one step (where(i, c) gives
+// the three operands; a is updated in place), two elements per thread in
+// flight: both elements' loads are issued before the first multiply-subtract,
+// so one memory round trip serves two of them (the Ozaki-II workgroup has half
+// the wavefronts of the native one).  Each element is updated once, so the
+// order of its updates is the caller's.
+template <int NC, int NT, typename W>
+__device__ __forceinline__ void fms_sweep(int32_t mr, int32_t mc, W where) {
+  if (mr <= 0 || mc <= 0) return;
+  const int32_t total = mr * mc;
+  ColWalk<NT> wk(mr, threadIdx.x);
+  for (int32_t idx = threadIdx.x; idx < total; idx += 2 * NT) {
+    const bool two = idx + NT < total;
+    double *pa0, *pa1 = nullptr;
+    const double *pl0, *pu0, *pl1 = nullptr, *pu1 = nullptr;
+    where(wk.i, wk.c, pa0, pl0, pu0);
+    wk.next();
+    if (two) where(wk.i, wk.c, pa1, pl1, pu1);
+    wk.next();
+    double a0[NC], l0[NC], u0[NC], a1[NC] = {}, l1[NC] = {}, u1[NC] = {}, o[NC];
+    ozx::load<NC>(pa0, a0);
+    ozx::load<NC>(pl0, l0);
+    ozx::load<NC>(pu0, u0);
+    if (two) {
+      ozx::load<NC>(pa1, a1);
+      ozx::load<NC>(pl1, l1);
+      ozx::load<NC>(pu1, u1);
+    }
+    ozx::fms<NC>(a0, l0, u0, o);
+    ozx::store<NC>(pa0, o);
+    if (two) {
+      ozx::fms<NC>(a1, l1, u1, o);
+      ozx::store<NC>(pa1, o);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Blocked LU with the Ozaki-II Schur update, one system per workgroup
 // (Sec. 3.4, Eq. (schur), with the product of Sec. 3.1-3.3 at K = b).  Per
@@ -263,185 +303,255 @@ __device__ void solve_one(const ozII_batch_item &it) {
 // residues (Mp x Kp bytes each), ng nmod t-planes (Mp x Mp bytes each).
 // ---------------------------------------------------------------------------
 template <int NC, int NWM, int NT>
-__device__ __forceinline__ void oz_update(double *A, int64_t n, int64_t k0, int64_t k1, const DevPlan *pl,
-                          uint8_t *ws, uint32_t *stage) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int64_t K = k1 - k0, m2 = n - k1;
-  const int64_t Mp = (m2 + 63) & ~(int64_t)63, Kp = (K + 63) & ~(int64_t)63, KB = Kp / 64;
-  const int S = pl->S, nmod = pl->nmod, ng = pl->ng, g0 = pl->g0, Q = pl->Q, w = pl->w;
-  int32_t *ea = (int32_t *)ws;
-  int32_t *eb = ea + Mp;
-  const int64_t plane = Mp * Kp;
-  uint8_t *pa = (uint8_t *)(eb + Mp);
-  uint8_t *pb = pa + (int64_t)S * nmod * plane;
-  uint8_t *tpl = pb + (int64_t)S * nmod * plane;
-  const double *L21 = A + (k1 + k0 * n) * NC;  // m2 x K, leading dimension n
-  const double *U12 = A + (k0 + k1 * n) * NC;  // K x m2
-  double *A22 = A + (k1 + k1 * n) * NC;
-
-  // (S1)
-  for (int64_t i = tid; i < Mp; i += NT) {
-    int32_t be = EXP_ZERO, bf = EXP_ZERO;
-    if (i < m2)
-      for (int64_t h = 0; h < K; ++h) {
-        const int32_t u = exponent_of<NC>(L21 + (i + h * n) * NC);
-        const int32_t v = exponent_of<NC>(U12 + (h + i * n) * NC);
-        be = u > be ? u : be;
-        bf = v > bf ? v : bf;
-      }
-    ea[i] = be;
-    eb[i] = bf;
+struct OzUpdate {
+  double *A;
+  int64_t n, k0, k1, K, m2, Mp, Kp, KB, plane;
+  const DevPlan *pl;
+  int32_t *ea, *eb;
+  uint8_t *pa, *pb, *tpl;
+  __device__ __forceinline__ OzUpdate(double *A_, int64_t n_, int64_t k0_, int64_t k1_, const DevPlan *pl_,
+                                      uint8_t *ws)
+      : A(A_), n(n_), k0(k0_), k1(k1_), K(k1_ - k0_), m2(n_ - k1_), pl(pl_) {
+    Mp = (m2 + 63) & ~(int64_t)63;
+    Kp = (K + 63) & ~(int64_t)63;
+    KB = Kp / 64;
+    plane = Mp * Kp;
+    ea = (int32_t *)ws;
+    eb = ea + Mp;
+    pa = (uint8_t *)(eb + Mp);
+    pb = pa + (int64_t)pl->S * pl->nmod * plane;
+    tpl = pb + (int64_t)pl->S * pl->nmod * plane;
   }
-  __syncthreads();
 
-  // (S2)+(S3)
-  {
-    const int T = tid & 255;
-    const int64_t NBLK = Mp / 16 * KB;  // blocks per operand
-    for (int64_t q = tid >> 8; q < 2 * NBLK; q += NT / 256) {
-      const bool isA = q < NBLK;
-      const int64_t r = isA ? q : q - NBLK;
-      produce_block_b<NC, 8, NWM, PL_I8>(isA ? L21 : U12, n, isA ? 1 : 0, m2, K, KB,
-                                         isA ? ea : eb, pl, isA ? pa : pb, plane, r % KB, r / KB,
-                                         T, 0, pl->nmod);
+  // U12 = L11^-1 A12, forward in k, columns c0 .. c1-1 of the trailing matrix
+  __device__ __forceinline__ void solve_u12(int64_t c0, int64_t c1) const {
+    double *P = A;
+    const int64_t ld = n, kb = k1;
+    for (int64_t k = k0; k + 1 < k1; ++k) {
+      fms_sweep<NC, NT>((int32_t)(k1 - k - 1), (int32_t)(c1 - c0),
+                        [&](int32_t i, int32_t c, double *&pa_, const double *&pl_, const double *&pu_) {
+                          double *col = P + (kb + c0 + c) * ld * NC;
+                          pa_ = col + (k + 1 + i) * NC;
+                          pl_ = P + (k + 1 + i + k * ld) * NC;
+                          pu_ = col + k * NC;
+                        });
+      __syncthreads();
     }
   }
-  __syncthreads();
 
-  // (S4)
-  {
-    const int64_t TM = Mp / 64;
-    const int64_t items = (int64_t)ng * nmod * TM * TM;
-    for (int64_t q = wv; q < items; q += NT / 64) {
-      const int64_t tn = q % TM, tm = (q / TM) % TM;
-      const int gl = (int)(q / (TM * TM));
-      const int l = gl % nmod, g = g0 + gl / nmod;
-      const int ta0 = g - (S - 1) > 0 ? g - (S - 1) : 0;
-      const int ta1 = g < S - 1 ? g : S - 1;
-      v4i acc[4][4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = v4i{0, 0, 0, 0};
-      for (int ta = ta0; ta <= ta1; ++ta) {
-        const uint8_t *A0 = pa + (int64_t)(ta * nmod + l) * plane + tm * 4 * KB * 1024 + lane * 16;
-        const uint8_t *B0 =
-            pb + (int64_t)((g - ta) * nmod + l) * plane + tn * 4 * KB * 1024 + lane * 16;
-        for (int64_t kb = 0; kb < KB; ++kb) {
-          v4i af[4], bf[4];
-#pragma unroll
-          for (int a = 0; a < 4; ++a) af[a] = *(const v4i *)(A0 + (a * KB + kb) * 1024);
-#pragma unroll
-          for (int b = 0; b < 4; ++b) bf[b] = *(const v4i *)(B0 + (b * KB + kb) * 1024);
-#pragma unroll
-          for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-              acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[a], bf[b], acc[a][b], 0, 0, 0);
+  // (S1) to (S3) of rows r0 .. r1-1 of L21 (isA) or columns r0 .. r1-1 of U12;
+  // multiples of 16, r1 <= Mp
+  __device__ __forceinline__ void residues(bool isA, int64_t r0, int64_t r1) const {
+    const double *X = isA ? A + (k1 + k0 * n) * NC : A + (k0 + k1 * n) * NC;
+    const int64_t so = isA ? 1 : n, sh = isA ? n : 1;
+    int32_t *ex = isA ? ea : eb;
+    for (int64_t i = r0 + threadIdx.x; i < r1; i += NT) {
+      int32_t be = EXP_ZERO;
+      if (i < m2)
+        for (int64_t h = 0; h < K; ++h) {
+          const int32_t u = exponent_of<NC>(X + (i * so + h * sh) * NC);
+          be = u > be ? u : be;
         }
-      }
-      const uint32_t m = (uint32_t)pl->m[l];
-      const double md = (double)m, yd = (double)pl->y[l], im = pl->inv_m[l];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          uint32_t packed = 0;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) packed |= mod_times_y(acc[a][b][r], md, yd, im, m) << (8 * r);
-          const int64_t row = tm * 64 + 16 * a + 4 * (lane >> 4);
-          const int64_t col = tn * 64 + 16 * b + (lane & 15);
-          *(uint32_t *)(tpl + ((int64_t)gl * Mp + col) * Mp + row) = packed;
-        }
+      ex[i] = be;
     }
+    __syncthreads();
+    for (int64_t q = r0 / 16 * KB + (threadIdx.x >> 8); q < r1 / 16 * KB; q += NT / 256)
+      produce_block_b<NC, 8, NWM, PL_I8>(X, n, isA ? 1 : 0, m2, K, KB, ex, pl, isA ? pa : pb, plane,
+                                         q % KB, q / KB, threadIdx.x & 255, 0, pl->nmod);
   }
-  __syncthreads();
 
-  // (S5)+(S6) and A22 -= c: each wavefront takes 64 consecutive elements of
-  // a column at a time through the matrix-core CRT, on its own slice of the
-  // staging LDS (the route and results of k_consumer_mx)
-  {
-    constexpr int NB = 36, NWC = 12, ND = NB / 2, STG = stage_words<ND>();
-    static_assert(64 * MX_TBS <= 32 * MX_CBS * 4 && 64 * STG <= 32 * MX_CBS, "LDS reuse");
-    static_assert(NT / 64 * 32 * MX_CBS <= NT * CST, "one column-sum buffer per wavefront");
-    int32_t *buf = (int32_t *)stage + wv * 32 * MX_CBS;
-    uint32_t *st = (uint32_t *)buf + lane * STG;
-    mxv4 tab[MX_BLK];
-#pragma unroll
-    for (int b = 0; b < MX_BLK; ++b) tab[b] = *(const mxv4 *)&pl->crtm[b][lane][0];
-    const int64_t TMB = Mp / 64, ps = Mp * Mp;
-    for (int64_t ch = wv; ch < m2 * TMB; ch += NT / 64) {
-      const int64_t j = ch / TMB, i0 = (ch % TMB) * 64, i = i0 + lane;
-      const bool valid = i < m2;
-      const int32_t ej = eb[j], ei = valid ? ea[i] : EXP_ZERO;
-      const bool zero = ei == EXP_ZERO || ej == EXP_ZERO;
-      const int eps = zero ? 0 : w * g0 - (Q - 1 - ei) - (Q - 1 - ej);
-      uint32_t cb[NWC];
-#pragma unroll
-      for (int k = 0; k < NWC; ++k) cb[k] = 0u;
-      for (int gi = 0; gi < ng; ++gi) {
-        int32_t d[ND];
-        crt_group_mx<NB, true>(tpl + (int64_t)gi * nmod * ps + j * Mp + i0, ps, nmod, pl, tab, buf,
-                               lane, d);
-        add_shifted_digits<NWC, ND, STG>(cb, d, w * gi, st);
-        mx_sync<true>();  // the buffer takes the next group's t-bytes
+  // (S4) to (S6) and A22 -= c over the 64 x 64 tiles tm0 .. tm1-1 by tn0 .. tn1-1
+  __device__ __forceinline__ void tiles(int64_t tm0, int64_t tm1, int64_t tn0, int64_t tn1,
+                                        uint32_t *stage) const {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int S = pl->S, nmod = pl->nmod, ng = pl->ng, g0 = pl->g0, Q = pl->Q, w = pl->w;
+    double *A22 = A + (k1 + k1 * n) * NC;
+
+    // (S4)
+    {
+      const int TMc = (int)(tm1 - tm0), TNc = (int)(tn1 - tn0);
+      const int items = ng * nmod * TMc * TNc;
+      for (int q = wv; q < items; q += NT / 64) {
+        const int64_t tn = tn0 + q % TNc, tm = tm0 + (q / TNc) % TMc;
+        const int gl = q / (TMc * TNc);
+        const int l = gl % nmod, g = g0 + gl / nmod;
+        const int ta0 = g - (S - 1) > 0 ? g - (S - 1) : 0;
+        const int ta1 = g < S - 1 ? g : S - 1;
+        v4i acc[4][4];
+  #pragma unroll
+        for (int a = 0; a < 4; ++a)
+  #pragma unroll
+          for (int b = 0; b < 4; ++b) acc[a][b] = v4i{0, 0, 0, 0};
+        for (int ta = ta0; ta <= ta1; ++ta) {
+          const uint8_t *A0 = pa + (int64_t)(ta * nmod + l) * plane + tm * 4 * KB * 1024 + lane * 16;
+          const uint8_t *B0 =
+              pb + (int64_t)((g - ta) * nmod + l) * plane + tn * 4 * KB * 1024 + lane * 16;
+          for (int64_t kb = 0; kb < KB; ++kb) {
+            v4i af[4], bf[4];
+  #pragma unroll
+            for (int a = 0; a < 4; ++a) af[a] = *(const v4i *)(A0 + (a * KB + kb) * 1024);
+  #pragma unroll
+            for (int b = 0; b < 4; ++b) bf[b] = *(const v4i *)(B0 + (b * KB + kb) * 1024);
+  #pragma unroll
+            for (int a = 0; a < 4; ++a)
+  #pragma unroll
+              for (int b = 0; b < 4; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(af[a], bf[b], acc[a][b], 0, 0, 0);
+          }
+        }
+        const uint32_t m = (uint32_t)pl->m[l];
+        const double md = (double)m, yd = (double)pl->y[l], im = pl->inv_m[l];
+  #pragma unroll
+        for (int a = 0; a < 4; ++a)
+  #pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            uint32_t packed = 0;
+  #pragma unroll
+            for (int r = 0; r < 4; ++r) packed |= mod_times_y(acc[a][b][r], md, yd, im, m) << (8 * r);
+            const int64_t row = tm * 64 + 16 * a + 4 * (lane >> 4);
+            const int64_t col = tn * 64 + 16 * b + (lane & 15);
+            *(uint32_t *)(tpl + ((int64_t)gl * Mp + col) * Mp + row) = packed;
+          }
       }
-      if (!valid) continue;
-      double c[NC];
-      if (zero) {
-#pragma unroll
-        for (int q = 0; q < NC; ++q) c[q] = 0.0;
-      } else {
-        round_out_n<NWC, NC>(cb, eps, c);
-      }
-      double *dst = A22 + (i + j * n) * NC;
-      double a[NC], nc_[NC], r[NC];
-      ozx::load<NC>(dst, a);
-#pragma unroll
-      for (int q = 0; q < NC; ++q) nc_[q] = -c[q];
-      ozx::add<NC>(a, nc_, r);
-      ozx::store<NC>(dst, r);
     }
+    __syncthreads();
+
+    // (S5)+(S6) and A22 -= c: each wavefront takes 64 consecutive elements of
+    // a column at a time through the matrix-core CRT, on its own slice of the
+    // staging LDS (the route and results of k_consumer_mx)
+    {
+      constexpr int NB = 36, NWC = 12, ND = NB / 2, STG = stage_words<ND>();
+      static_assert(64 * MX_TBS <= 32 * MX_CBS * 4 && 64 * STG <= 32 * MX_CBS, "LDS reuse");
+      static_assert(NT / 64 * 32 * MX_CBS <= NT * CST, "one column-sum buffer per wavefront");
+      int32_t *buf = (int32_t *)stage + wv * 32 * MX_CBS;
+      uint32_t *st = (uint32_t *)buf + lane * STG;
+      mxv4 tab[MX_BLK];
+  #pragma unroll
+      for (int b = 0; b < MX_BLK; ++b) tab[b] = *(const mxv4 *)&pl->crtm[b][lane][0];
+      const int64_t ps = Mp * Mp;
+      const int TMc = (int)(tm1 - tm0), chunks = (int)(tn1 - tn0) * 64 * TMc;
+      for (int ch = wv; ch < chunks; ch += NT / 64) {
+        const int64_t j = tn0 * 64 + ch / TMc, i0 = (tm0 + ch % TMc) * 64, i = i0 + lane;
+        if (j >= m2) break;
+        const bool valid = i < m2;
+        const int32_t ej = eb[j], ei = valid ? ea[i] : EXP_ZERO;
+        const bool zero = ei == EXP_ZERO || ej == EXP_ZERO;
+        const int eps = zero ? 0 : w * g0 - (Q - 1 - ei) - (Q - 1 - ej);
+        uint32_t cb[NWC];
+  #pragma unroll
+        for (int k = 0; k < NWC; ++k) cb[k] = 0u;
+        for (int gi = 0; gi < ng; ++gi) {
+          int32_t d[ND];
+          crt_group_mx<NB, true>(tpl + (int64_t)gi * nmod * ps + j * Mp + i0, ps, nmod, pl, tab, buf,
+                                 lane, d);
+          add_shifted_digits<NWC, ND, STG>(cb, d, w * gi, st);
+          mx_sync<true>();  // the buffer takes the next group's t-bytes
+        }
+        if (!valid) continue;
+        double c[NC];
+        if (zero) {
+  #pragma unroll
+          for (int q = 0; q < NC; ++q) c[q] = 0.0;
+        } else {
+          round_out_n<NWC, NC>(cb, eps, c);
+        }
+        double *dst = A22 + (i + j * n) * NC;
+        double a[NC], nc_[NC], r[NC];
+        ozx::load<NC>(dst, a);
+  #pragma unroll
+        for (int q = 0; q < NC; ++q) nc_[q] = -c[q];
+        ozx::add<NC>(a, nc_, r);
+        ozx::store<NC>(dst, r);
+      }
+    }
+    __syncthreads();
   }
+};
+
+// ---------------------------------------------------------------------------
+// Shared work.  A workgroup that finds the queue empty stays and helps those
+// still factoring: once one is idle, the owner of a system offers U12 and the
+// update of a step as tasks on its line of the board, takes tasks itself and
+// goes on when all are done.  The tasks of phase 0 are U12 and its residues in
+// chunks of 32 columns and the residues of L21 in chunks of 64 rows, those of
+// phase 1 the 64 x 64 tiles of the update; each element sees the operations it
+// would see without help.  A task is taken by an atomic increment of
+// Board::job, total << 16 | next, and runs to its end without waiting for
+// anything, an owner waits only for tasks that were taken, and a helper leaves
+// when every item is finished: no workgroup waits for one that does not run.
+// The owner's data reach the helpers, and the helpers' results the owner,
+// through an agent-scope release by every wavefront before the increment (or
+// the offer) and an acquire by every wavefront after it: the XCDs' L2s are not
+// coherent.  The last and largest systems bound the launch, each on one CU of
+// 256: 256 DD / QD systems of order 64 to 512, b = 64, 73.1 -> 36.0 ms, 16 of
+// order 100 to 400 33.1 -> 17.6 ms; with more work than CUs to the end (1000 of
+// order 150 to 256) 33.2 -> 32.1 ms.
+// ---------------------------------------------------------------------------
+struct BatchSlot {  // a line of its own for each owner
+  int32_t done, item, k0, phase;
+  int32_t pad[28];
+};
+struct Board {
+  int32_t next, idle, finished, owners;  // items taken, helpers, items done, scratch slots taken
+  int32_t pad[60];
+  // followed by nslot job words (rounded up to 64) and nslot slots
+  __device__ uint32_t *jobs() { return (uint32_t *)(this + 1); }
+  __device__ BatchSlot *slots(int nslot) { return (BatchSlot *)(jobs() + ((nslot + 63) & ~63)); }
+};
+static_assert(sizeof(BatchSlot) == 128 && sizeof(Board) == 256, "board layout");
+
+template <class T>
+__device__ __forceinline__ T ld_agent(const T *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void st_agent(T *p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ T add_agent(T *p, T v) {
+  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// by all threads: what the workgroup wrote is visible to an acquirer
+__device__ __forceinline__ void wg_release() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
   __syncthreads();
 }
+// by all threads, after thread 0 saw the other side's word
+__device__ __forceinline__ void wg_acquire() {
+  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
 
-// a <- a - l u for the elements idx = 0 .. total-1 of one step (where(idx)
-// gives the three operands; a is updated in place), two elements per
-// thread in flight: both elements' loads are issued before the first
-// multiply-subtract, so one memory round trip serves two of them (the
-// Ozaki-II workgroup has half the wavefronts of the native one).  Each
-// element is updated once, so the order of its updates is the caller's.
-template <int NC, int NT, typename W>
-__device__ __forceinline__ void fms_sweep(int64_t total, W where) {
-  for (int64_t idx = threadIdx.x; idx < total; idx += 2 * NT) {
-    const bool two = idx + NT < total;
-    double *pa0, *pa1 = nullptr;
-    const double *pl0, *pu0, *pl1 = nullptr, *pu1 = nullptr;
-    where(idx, pa0, pl0, pu0);
-    if (two) where(idx + NT, pa1, pl1, pu1);
-    double a0[NC], l0[NC], u0[NC], a1[NC] = {}, l1[NC] = {}, u1[NC] = {}, o[NC];
-    ozx::load<NC>(pa0, a0);
-    ozx::load<NC>(pl0, l0);
-    ozx::load<NC>(pu0, u0);
-    if (two) {
-      ozx::load<NC>(pa1, a1);
-      ozx::load<NC>(pl1, l1);
-      ozx::load<NC>(pu1, u1);
+constexpr int UCH = 32, ACH = 64;  // columns of U12, rows of L21 of a task
+
+template <int NC, int NWM, int NT>
+__device__ __forceinline__ int tasks_of(const OzUpdate<NC, NWM, NT> &u, int phase) {
+  return phase == 0 ? (int)(u.Mp / UCH + u.Mp / ACH) : (int)((u.Mp / 64) * (u.Mp / 64));
+}
+
+template <int NC, int NWM, int NT>
+__device__ __forceinline__ void run_task(const OzUpdate<NC, NWM, NT> &u, int phase, int t,
+                                         uint32_t *stage) {
+  if (phase == 0) {
+    const int nu = (int)(u.Mp / UCH);
+    if (t < nu) {
+      const int64_t c0 = (int64_t)t * UCH, c1 = c0 + UCH;
+      if (c0 < u.m2) u.solve_u12(c0, c1 < u.m2 ? c1 : u.m2);
+      u.residues(false, c0, c1);
+    } else {
+      u.residues(true, (int64_t)(t - nu) * ACH, (int64_t)(t - nu + 1) * ACH);
     }
-    ozx::fms<NC>(a0, l0, u0, o);
-    ozx::store<NC>(pa0, o);
-    if (two) {
-      ozx::fms<NC>(a1, l1, u1, o);
-      ozx::store<NC>(pa1, o);
-    }
+  } else {
+    const int tb = (int)(u.Mp / 64), tm = t % tb, tn = t / tb;
+    u.tiles(tm, tm + 1, tn, tn + 1, stage);
   }
 }
 
 template <int NC, int NWM, int NT>
-__device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, double (*rkey)[4], int64_t *ridx,
-                            int *s_info, const DevPlan *pl, uint8_t *ws, int b,
-                            uint32_t *stage) {
+__device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item, double (*rkey)[4],
+                            int64_t *ridx, int *s_info, const DevPlan *pl, uint8_t *ws, int b,
+                            uint32_t *stage, Board *bd, uint32_t *job, BatchSlot *sl, int *s_task) {
   const int tid = threadIdx.x;
   const int64_t n = it.n;
   double *A = it.A;
@@ -455,31 +565,52 @@ __device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, double (*
       // exactly zero pivot (the column is left as it is, as in LAPACK's
       // unblocked panel)
       const bool zero = pivot_column<NC, NT>(it, j, rkey, ridx, s_info);
-      const int64_t mr = zero ? 0 : n - j - 1, mc = k1 - j - 1;
-      fms_sweep<NC, NT>(mr * mc, [&](int64_t idx, double *&pa, const double *&pl,
-                                     const double *&pu) {
-        const int64_t i = j + 1 + idx % mr, c = j + 1 + idx / mr;
-        pa = E(i, c);
-        pl = E(i, j);
-        pu = E(j, c);
-      });
+      fms_sweep<NC, NT>(zero ? 0 : (int32_t)(n - j - 1), (int32_t)(k1 - j - 1),
+                        [&](int32_t i, int32_t c, double *&pa, const double *&pl_, const double *&pu) {
+                          pa = E(j + 1 + i, j + 1 + c);
+                          pl_ = E(j + 1 + i, j);
+                          pu = E(j, j + 1 + c);
+                        });
       __syncthreads();
     }
-    if (k1 < n) {
-      // U12 = L11^-1 A12, forward in k
-      const int64_t ncol = n - k1;
-      for (int64_t k = k0; k + 1 < k1; ++k) {
-        const int64_t mr = k1 - k - 1;
-        fms_sweep<NC, NT>(mr * ncol, [&](int64_t idx, double *&pa, const double *&pl,
-                                         const double *&pu) {
-          const int64_t i = k + 1 + idx % mr, c = k1 + idx / mr;
-          pa = E(i, c);
-          pl = E(i, k);
-          pu = E(k, c);
-        });
+    if (k1 >= n) break;
+    const OzUpdate<NC, NWM, NT> u(A, n, k0, k1, pl, ws);
+    // one tile: nothing to share
+    if (tid == 0) *s_task = u.m2 > 64 ? ld_agent(&bd->idle) : 0;
+    __syncthreads();
+    const bool share = *s_task > 0;
+    __syncthreads();
+    if (!share) {
+      u.solve_u12(0, u.m2);
+      u.residues(true, 0, u.Mp);
+      u.residues(false, 0, u.Mp);
+      __syncthreads();
+      u.tiles(0, u.Mp / 64, 0, u.Mp / 64, stage);
+      continue;
+    }
+    for (int phase = 0; phase < 2; ++phase) {
+      const int total = tasks_of(u, phase);
+      if (tid == 0) {
+        st_agent(&sl->done, 0);
+        st_agent(&sl->item, item);
+        st_agent(&sl->k0, (int32_t)k0);
+        st_agent(&sl->phase, phase);
+      }
+      wg_release();
+      if (tid == 0) st_agent(job, (uint32_t)total << 16);
+      int mine = 0;
+      for (;; ++mine) {
+        if (tid == 0) *s_task = (int)(add_agent(job, 1u) & 0xffffu);
+        __syncthreads();
+        const int t = *s_task;
+        __syncthreads();
+        if (t >= total) break;
+        run_task(u, phase, t, stage);
         __syncthreads();
       }
-      oz_update<NC, NWM, NT>(A, n, k0, k1, pl, ws, stage);
+      if (tid == 0)
+        while (ld_agent(&sl->done) + mine < total) __builtin_amdgcn_s_sleep(4);
+      wg_acquire();
     }
   }
   if (tid == 0) *it.info = *s_info;
@@ -491,7 +622,7 @@ __device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, double (*
 // consumer's per-thread staging shares the LDS with the pivot search (never
 // live at the same time).
 __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *items, int count,
-                                                    int *queue, uint64_t *times,
+                                                    Board *bd, int nslot, uint64_t *times,
                                                     const DevPlan *pl2, const DevPlan *pl3,
                                                     const DevPlan *pl4, uint8_t *ws, int64_t slot,
                                                     int b) {
@@ -499,24 +630,88 @@ __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *item
   static_assert(BTZ * CST * 4 >= BTZ * (32 + 8), "pivot search arrays fit the staging");
   double(*rkey)[4] = (double(*)[4])lds;
   int64_t *ridx = (int64_t *)(lds + BTZ * 8);
-  __shared__ int s_item, s_info;
-  uint8_t *myws = ws + (int64_t)blockIdx.x * slot;
+  __shared__ int s_item, s_info, s_task;
+  __shared__ int s_slot;
+  BatchSlot *slots = bd->slots(nslot);
+  if (threadIdx.x == 0) s_slot = -1;
   for (;;) {
-    if (threadIdx.x == 0) s_item = atomicAdd(queue, 1);
-    __syncthreads();
-    const int q = s_item;
-    __syncthreads();
-    if (q >= count) break;  // every workgroup leaves once the queue is empty
-    const ozII_batch_item it = items[q];
-    if (times && threadIdx.x == 0) times[2 * it.reserved] = __builtin_amdgcn_s_memrealtime();
-    if (it.nc == 2) lu_solve_oz<2, 6, BTZ>(it, rkey, ridx, &s_info, pl2, myws, b, lds);
-    else if (it.nc == 3) lu_solve_oz<3, 4, BTZ>(it, rkey, ridx, &s_info, pl3, myws, b, lds);
-    else lu_solve_oz<4, 4, BTZ>(it, rkey, ridx, &s_info, pl4, myws, b, lds);
-    __syncthreads();
-    if (times && threadIdx.x == 0) {
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-      times[2 * it.reserved + 1] = __builtin_amdgcn_s_memrealtime();
+    if (threadIdx.x == 0) {
+      s_item = add_agent(&bd->next, 1);
+      // at most min(count, workgroups) = nslot workgroups ever own an item
+      if (s_item < count && s_slot < 0) s_slot = add_agent(&bd->owners, 1);
     }
+    __syncthreads();
+    const int q = s_item, ms = s_slot;
+    __syncthreads();
+    if (q >= count) break;
+    const ozII_batch_item it = items[q];
+    uint8_t *myws = ws + (int64_t)ms * slot;
+    if (times && threadIdx.x == 0) times[2 * it.reserved] = __builtin_amdgcn_s_memrealtime();
+#define OZ_LU(NC_, NWM_, PL_)                                                                        \
+  lu_solve_oz<NC_, NWM_, BTZ>(it, q, rkey, ridx, &s_info, PL_, myws, b, lds, bd, bd->jobs() + ms, \
+                              slots + ms, &s_task)
+    if (it.nc == 2) OZ_LU(2, 6, pl2);
+    else if (it.nc == 3) OZ_LU(3, 4, pl3);
+    else OZ_LU(4, 4, pl4);
+#undef OZ_LU
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      if (times) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        times[2 * it.reserved + 1] = __builtin_amdgcn_s_memrealtime();
+      }
+      add_agent(&bd->finished, 1);
+    }
+  }
+  // the queue is empty: help until every item is finished
+  if (threadIdx.x == 0) add_agent(&bd->idle, 1);
+  const int lane = threadIdx.x & 63;
+  for (;;) {
+    if (threadIdx.x < 64) {
+      int got = -1;
+      while (got < 0) {
+        const bool over = ld_agent(&bd->finished) >= count;
+        for (int s0 = 0; s0 < nslot && got < 0; s0 += 64) {
+          // helpers start their search at different slots
+          int s = s0 + lane;
+          bool open = false;
+          if (s < nslot) {
+            s = (s + (int)blockIdx.x) % nslot;
+            const uint32_t v = ld_agent(bd->jobs() + s);
+            open = (v & 0xffffu) < (v >> 16);
+          }
+          const uint64_t m = __builtin_amdgcn_ballot_w64(open);
+          if (m == 0) continue;
+          const int pick = __builtin_amdgcn_readlane(s, __builtin_ctzll(m));
+          uint32_t v = 0;
+          if (lane == 0) v = add_agent(bd->jobs() + pick, 1u);
+          v = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+          if ((v & 0xffffu) < (v >> 16)) {
+            got = pick;
+            if (lane == 0) s_task = (int)(v & 0xffffu);
+          }
+        }
+        if (got < 0) {
+          if (over) break;
+          __builtin_amdgcn_s_sleep(32);
+        }
+      }
+      if (lane == 0) s_slot = got;
+    }
+    wg_acquire();
+    const int hs = s_slot, t = s_task;
+    __syncthreads();
+    if (hs < 0) break;
+    const int q = ld_agent(&slots[hs].item), phase = ld_agent(&slots[hs].phase);
+    const int64_t k0 = ld_agent(&slots[hs].k0);
+    const ozII_batch_item it = items[q];
+    const int64_t k1 = k0 + b;  // a step that is shared has columns after it
+    uint8_t *hws = ws + (int64_t)hs * slot;
+    if (it.nc == 2) run_task(OzUpdate<2, 6, BTZ>(it.A, it.n, k0, k1, pl2, hws), phase, t, lds);
+    else if (it.nc == 3) run_task(OzUpdate<3, 4, BTZ>(it.A, it.n, k0, k1, pl3, hws), phase, t, lds);
+    else run_task(OzUpdate<4, 4, BTZ>(it.A, it.n, k0, k1, pl4, hws), phase, t, lds);
+    wg_release();
+    if (threadIdx.x == 0) add_agent(&slots[hs].done, 1);
   }
 }
 
@@ -545,8 +740,8 @@ __global__ __launch_bounds__(BT) void k_batch_lu(const ozII_batch_item *items, i
   }
 }
 
-__global__ void k_batch_clear(int *queue) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *queue = 0;
+__global__ void k_batch_clear(int *words, int count) {
+  for (int i = threadIdx.x; i < count; i += blockDim.x) words[i] = 0;
 }
 
 }  // namespace
@@ -555,18 +750,23 @@ namespace ozl {
 hipError_t launch_batch(const ozII_batch_item *items, int count, int *queue, uint64_t *times,
                         int grid, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_batch_clear, dim3(1), dim3(64), 0, s, queue);
+  hipLaunchKernelGGL(k_batch_clear, dim3(1), dim3(64), 0, s, queue, 1);
   hipLaunchKernelGGL(k_batch_lu, dim3((unsigned)grid), dim3(BT), 0, s, items, count, queue, times);
   return hipGetLastError();
 }
-hipError_t launch_batch_oz(const ozII_batch_item *items, int count, int *queue, uint64_t *times,
-                          int grid, const DevPlan *pl2, const DevPlan *pl3, const DevPlan *pl4,
-                          uint8_t *ws, int64_t slot, int b, hipStream_t s) {
+size_t batch_board_bytes(int nslot) {
+  return sizeof(Board) + (size_t)((nslot + 63) / 64 * 64) * 4 + (size_t)nslot * sizeof(BatchSlot);
+}
+
+hipError_t launch_batch_oz(const ozII_batch_item *items, int count, void *board, int nslot,
+                          uint64_t *times, int grid, const DevPlan *pl2, const DevPlan *pl3,
+                          const DevPlan *pl4, uint8_t *ws, int64_t slot, int b, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  if (b < 1 || b > 256) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_batch_clear, dim3(1), dim3(64), 0, s, queue);
-  hipLaunchKernelGGL(k_batch_lu_oz, dim3((unsigned)grid), dim3(BTZ), 0, s, items, count, queue,
-                     times, pl2, pl3, pl4, ws, slot, b);
+  if (b < 1 || b > 256 || nslot < std::min(count, grid)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_batch_clear, dim3(1), dim3(256), 0, s, (int *)board,
+                     (int)(sizeof(Board) / 4) + (nslot + 63) / 64 * 64);
+  hipLaunchKernelGGL(k_batch_lu_oz, dim3((unsigned)grid), dim3(BTZ), 0, s, items, count,
+                     (Board *)board, nslot, times, pl2, pl3, pl4, ws, slot, b);
   return hipGetLastError();
 }
 }  // namespace ozl

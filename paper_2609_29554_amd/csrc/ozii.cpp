@@ -368,8 +368,8 @@ struct ozII_ctx {
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // batched LU: the uploaded item table (processing order) and its queue
   ozII_batch_item *batch = nullptr;
-  int batch_cap = 0, batch_count = 0, batch_grid = 1;
-  int *batch_queue = nullptr;
+  int batch_cap = 0, batch_count = 0, batch_grid = 1, batch_cus = 1;
+  int *batch_queue = nullptr;  // (Ozaki-II update: the board of shared work)
   // batched LU with the Ozaki-II update: panel width (0: native unblocked
   // path), plans per nc = 2, 3, 4 and the per-workgroup scratch
   int batch_b = 0;
@@ -1623,19 +1623,21 @@ ozII_status ozII_batch_prepare_ex(ozII_handle h, int32_t count, const ozII_batch
       return fail(h, OZII_ENOMEM, "batch table allocation failed");
     h->batch_cap = count;
   }
-  if (!h->batch_queue && (e = hipMalloc((void **)&h->batch_queue, 256)) != hipSuccess)
-    return fail(h, OZII_ENOMEM, "batch queue allocation failed");
   if (count > 0 &&
       (e = hipMemcpyAsync(h->batch, v.data(), sizeof(ozII_batch_item) * count, hipMemcpyHostToDevice,
                           h->stream)) != hipSuccess)
     return hip_fail(h, e, "batch upload");
   if ((e = hipStreamSynchronize(h->stream)) != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
-  // persistent grid: one workgroup per CU, at most one per item
+  // persistent grid: one workgroup per CU; at most one per item on the native
+  // update, where none could help another
   int dev = 0, ncu = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess ||
       (e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
     return hip_fail(h, e, "device query");
   const int grid = std::max(1, std::min(count, ncu));
+  if (!h->batch_queue &&
+      (e = hipMalloc((void **)&h->batch_queue, ozl::batch_board_bytes(ncu))) != hipSuccess)
+    return fail(h, OZII_ENOMEM, "batch queue allocation failed");
   if (oz && (size_t)(slot * grid) > h->batch_ws_bytes) {
     if (h->batch_ws) hipFree(h->batch_ws);
     h->batch_ws = nullptr;
@@ -1646,6 +1648,7 @@ ozII_status ozII_batch_prepare_ex(ozII_handle h, int32_t count, const ozII_batch
   }
   h->batch_count = count;
   h->batch_grid = grid;
+  h->batch_cus = ncu;
   h->batch_b = b;
   h->batch_slot = slot;
   for (int c = 0; c < 3; ++c) h->batch_pl[c] = pls[c];
@@ -1657,9 +1660,9 @@ ozII_status ozII_batch_run(ozII_handle h, uint64_t *times) {
   if (h->batch_count == 0) return OZII_OK;
   hipError_t e =
       h->batch_b > 0
-          ? ozl::launch_batch_oz(h->batch, h->batch_count, h->batch_queue, times, h->batch_grid,
-                                 h->batch_pl[0], h->batch_pl[1], h->batch_pl[2], h->batch_ws,
-                                 h->batch_slot, h->batch_b, h->stream)
+          ? ozl::launch_batch_oz(h->batch, h->batch_count, h->batch_queue, h->batch_grid, times,
+                                 h->batch_cus, h->batch_pl[0], h->batch_pl[1], h->batch_pl[2],
+                                 h->batch_ws, h->batch_slot, h->batch_b, h->stream)
           : ozl::launch_batch(h->batch, h->batch_count, h->batch_queue, times, h->batch_grid,
                               h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "batched LU");
