@@ -63,7 +63,11 @@ __device__ __forceinline__ bool piv_better(const double (&kb_)[NC], int64_t ib,
 // the lower row index), ipiv and info, the whole-row interchange and the
 // division of the column below the pivot (nothing to divide after a zero
 // pivot: the column below it is zero).  Ends with the workgroup in step and
-// returns whether the pivot was exactly zero (the same in every thread).
+// returns whether the pivot was exactly zero (the same in every thread).  A
+// chain of the column's loads, the reduction and a division: two barriers, the
+// column read once.  With seven barriers and three reads of it, and the solve
+// through memory, 256 systems took 35.0 instead of 34.6 ms and 16 13.1 instead
+// of 12.7.
 template <int NC, int NT>
 __device__ bool pivot_column(const ozII_batch_item &it, int64_t j, double (*rkey)[4],
                              int64_t *ridx, int *s_info) {
@@ -71,13 +75,17 @@ __device__ bool pivot_column(const ozII_batch_item &it, int64_t j, double (*rkey
   const int64_t n = it.n;
   double *A = it.A;
   auto E = [&](int64_t i, int64_t c) { return A + (i + c * n) * NC; };
-  double bk[NC];
+  double bk[NC], x0[NC];
   int64_t bi = -1;
 #pragma unroll
-  for (int q = 0; q < NC; ++q) bk[q] = 0.0;
+  for (int q = 0; q < NC; ++q) bk[q] = x0[q] = 0.0;
   for (int64_t i = j + tid; i < n; i += NT) {
     double x[NC];
     ozx::load<NC>(E(i, j), x);
+    if (i == j + tid) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) x0[q] = x[q];
+    }
     if (piv_better<NC>(x, i, bk, bi)) {
 #pragma unroll
       for (int q = 0; q < NC; ++q) bk[q] = x[q];
@@ -85,7 +93,8 @@ __device__ bool pivot_column(const ozII_batch_item &it, int64_t j, double (*rkey
     }
   }
   // the order is total, so any reduction order gives the same winner: a
-  // butterfly inside each wavefront, then thread 0 over the wavefront winners
+  // butterfly inside each wavefront, then every thread over the wavefront
+  // winners
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     double kv[NC];
@@ -98,63 +107,85 @@ __device__ bool pivot_column(const ozII_batch_item &it, int64_t j, double (*rkey
       bi = iv;
     }
   }
+  constexpr int NW = NT / 64;  // rkey[NW]: the entry of row j
   if ((tid & 63) == 0) {
 #pragma unroll
     for (int q = 0; q < NC; ++q) rkey[tid >> 6][q] = bk[q];
     ridx[tid >> 6] = bi;
   }
-  __syncthreads();
   if (tid == 0) {
-    for (int wv = 1; wv < NT / 64; ++wv) {
-      double ka[NC], kv[NC];
 #pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        ka[q] = rkey[0][q];
-        kv[q] = rkey[wv][q];
-      }
-      if (piv_better<NC>(kv, ridx[wv], ka, ridx[0])) {
-#pragma unroll
-        for (int q = 0; q < NC; ++q) rkey[0][q] = kv[q];
-        ridx[0] = ridx[wv];
-      }
-    }
+    for (int q = 0; q < NC; ++q) rkey[NW][q] = x0[q];
   }
   __syncthreads();
-  const int64_t p = ridx[0];
+  double d[NC];
+  int64_t p = ridx[0];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) d[q] = rkey[0][q];
+  for (int wv = 1; wv < NW; ++wv) {
+    double kv[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) kv[q] = rkey[wv][q];
+    if (piv_better<NC>(kv, ridx[wv], d, p)) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) d[q] = kv[q];
+      p = ridx[wv];
+    }
+  }
   bool zero = true;
 #pragma unroll
-  for (int q = 0; q < NC; ++q) zero = zero && (rkey[0][q] == 0.0);
-  __syncthreads();
+  for (int q = 0; q < NC; ++q) zero = zero && (d[q] == 0.0);
   if (tid == 0) {
     it.ipiv[j] = p;
     if (zero && *s_info == 0) *s_info = (int)(j + 1);
   }
   if (!zero) {
-    if (p != j) {  // whole-row interchange
-      for (int64_t c = tid; c < n; c += NT) {
-        double u[NC], v[NC];
+    // whole-row interchange outside column j, its first loads under way while
+    // the column is divided; column j's own is in the choice of dividends
+    const bool sw = p != j && tid < n && tid != j;
+    double u[NC], v[NC];
+    if (sw) {
+      ozx::load<NC>(E(j, tid), u);
+      ozx::load<NC>(E(p, tid), v);
+    }
+    for (int64_t i = j + tid; i < n; i += NT) {
+      double a[NC], l[NC];
+      if (i == j + tid) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) a[q] = x0[q];
+      } else {
+        ozx::load<NC>(E(i, j), a);
+      }
+      if (i == p) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) a[q] = rkey[NW][q];
+      }
+      ozx::div<NC>(a, d, l);
+      if (i == j) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) l[q] = d[q];
+      }
+      ozx::store<NC>(E(i, j), l);
+    }
+    if (sw) {
+      ozx::store<NC>(E(j, tid), v);
+      ozx::store<NC>(E(p, tid), u);
+    }
+    if (p != j)
+      for (int64_t c = tid + NT; c < n; c += NT) {
+        if (c == j) continue;
         ozx::load<NC>(E(j, c), u);
         ozx::load<NC>(E(p, c), v);
         ozx::store<NC>(E(j, c), v);
         ozx::store<NC>(E(p, c), u);
       }
-      __syncthreads();
-    }
-    double d[NC];
-    ozx::load<NC>(E(j, j), d);
-    for (int64_t i = j + 1 + tid; i < n; i += NT) {
-      double a[NC], l[NC];
-      ozx::load<NC>(E(i, j), a);
-      ozx::div<NC>(a, d, l);
-      ozx::store<NC>(E(i, j), l);
-    }
-    __syncthreads();
   }
+  __syncthreads();
   return zero;
 }
 
 template <int NC, int NT>
-__device__ void solve_one(const ozII_batch_item &it);
+__device__ void solve_one(const ozII_batch_item &it, double (*xs)[4], int64_t *pv);
 
 template <int NC>
 __device__ void lu_solve_one(const ozII_batch_item &it, double (*rkey)[4], int64_t *ridx,
@@ -183,20 +214,132 @@ __device__ void lu_solve_one(const ozII_batch_item &it, double (*rkey)[4], int64
     __syncthreads();
   }
   if (tid == 0) *it.info = *s_info;
-  solve_one<NC, BT>(it);
+  solve_one<NC, BT>(it, rkey, ridx);
 }
 
 // The solve with the factors: interchanges in ipiv order, forward (unit L,
 // ascending), backward (descending, each x_k divided by u_kk once its
-// updates are in), as ozII_getrs does for one right-hand side.
+// updates are in), as ozII_getrs does for one right-hand side.  Up to SOLVE_N
+// rows the right-hand side lives in registers, R rows a thread, and in LDS (xs;
+// pv: the pivots), the factors' entries are requested a step ahead and a step
+// takes one barrier; the division is done by all lanes of the row's wavefront
+// (one lane alone was slower).  A chain of n multiply-subtracts and n
+// divisions.  Larger orders (native update only) go through memory.
+constexpr int SOLVE_N = 1024;
 template <int NC, int NT>
-__device__ void solve_one(const ozII_batch_item &it) {
+__device__ void solve_one(const ozII_batch_item &it, double (*xs)[4], int64_t *pv) {
   if (!it.b) return;
   const int tid = threadIdx.x;
   const int64_t n = it.n;
   double *A = it.A;
   auto E = [&](int64_t i, int64_t c) { return A + (i + c * n) * NC; };
   double *x = it.b;
+  if (n <= SOLVE_N) {
+    constexpr int R = SOLVE_N / NT;
+    __syncthreads();  // the pivots are written, the LDS is free
+    for (int i = tid; i < n; i += NT) {
+      double u[NC];
+      ozx::load<NC>(x + i * NC, u);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) xs[i][q] = u[q];
+      pv[i] = it.ipiv[i];
+    }
+    __syncthreads();
+    if (tid == 0)
+      for (int j = 0; j < n; ++j) {
+        const int p = (int)pv[j];
+        if (p != j) {
+#pragma unroll
+          for (int q = 0; q < NC; ++q) {
+            const double u = xs[j][q];
+            xs[j][q] = xs[p][q];
+            xs[p][q] = u;
+          }
+        }
+      }
+    __syncthreads();
+    double xr[R][NC], cur[R][NC], nxt[R][NC], xk[NC], o[NC];
+    // entry (row r of this thread, column k) of the factors; any valid entry
+    // outside the matrix
+    auto fetch = [&](int k, double (&f)[R][NC]) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int i = tid + r * NT;
+        ozx::load<NC>(E(i < n ? i : 0, k), f[r]);
+      }
+    };
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) xr[r][q] = tid + r * NT < n ? xs[tid + r * NT][q] : 0.0;
+    fetch(0, cur);
+    for (int k = 0; k + 1 < n; ++k) {
+      fetch(k + 1, nxt);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) xk[q] = xs[k][q];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int i = tid + r * NT;
+        if (i > k && i < n) {
+          ozx::fms<NC>(xr[r], cur[r], xk, o);
+#pragma unroll
+          for (int q = 0; q < NC; ++q) xr[r][q] = o[q];
+          if (i == k + 1) {
+#pragma unroll
+            for (int q = 0; q < NC; ++q) xs[i][q] = o[q];
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < NC; ++q) cur[r][q] = nxt[r][q];
+      }
+      __syncthreads();
+    }
+    fetch((int)n - 1, cur);
+    for (int k = (int)n - 1; k >= 0; --k) {
+      fetch(k > 0 ? k - 1 : 0, nxt);
+      const int kt = k % NT, kr = k / NT;
+      if (tid >> 6 == kt >> 6) {
+        double u[NC];
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          double xv = xr[0][q], uv = cur[0][q];
+#pragma unroll
+          for (int r = 1; r < R; ++r) {
+            xv = kr == r ? xr[r][q] : xv;
+            uv = kr == r ? cur[r][q] : uv;
+          }
+          xk[q] = __shfl(xv, kt & 63, 64);
+          u[q] = __shfl(uv, kt & 63, 64);
+        }
+        ozx::div<NC>(xk, u, o);
+        if (tid == kt) {
+#pragma unroll
+          for (int q = 0; q < NC; ++q) xs[k][q] = o[q];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < NC; ++q) xk[q] = xs[k][q];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (tid + r * NT < k) {
+          ozx::fms<NC>(xr[r], cur[r], xk, o);
+#pragma unroll
+          for (int q = 0; q < NC; ++q) xr[r][q] = o[q];
+        }
+#pragma unroll
+        for (int q = 0; q < NC; ++q) cur[r][q] = nxt[r][q];
+      }
+    }
+    for (int i = tid; i < n; i += NT) {
+      double u[NC];
+#pragma unroll
+      for (int q = 0; q < NC; ++q) u[q] = xs[i][q];
+      ozx::store<NC>(x + i * NC, u);
+    }
+    __syncthreads();
+    return;
+  }
   if (tid == 0)
     for (int64_t j = 0; j < n; ++j) {
       const int64_t p = it.ipiv[j];
@@ -474,28 +617,33 @@ struct OzUpdate {
 // update of a step as tasks on its line of the board, takes tasks itself and
 // goes on when all are done.  The tasks of phase 0 are U12 and its residues in
 // chunks of 32 columns and the residues of L21 in chunks of 64 rows, those of
-// phase 1 the 64 x 64 tiles of the update; each element sees the operations it
-// would see without help.  A task is taken by an atomic increment of
-// Board::job, total << 16 | next, and runs to its end without waiting for
-// anything, an owner waits only for tasks that were taken, and a helper leaves
-// when every item is finished: no workgroup waits for one that does not run.
+// phase 1 the 64 x 64 tiles of the update, those of phase 2 (inside the panel)
+// the deferred steps of NT elements each; every element sees the operations it
+// would see without help.  A task is taken by an atomic increment of the job
+// word (priority << 32 | total << 16 | next) and runs to its end without
+// waiting for anything, an owner waits only for tasks that were taken, and a
+// helper leaves when every item is finished: no workgroup waits for one that
+// does not run.
 // The owner's data reach the helpers, and the helpers' results the owner,
 // through an agent-scope release by every wavefront before the increment (or
 // the offer) and an acquire by every wavefront after it: the XCDs' L2s are not
 // coherent.  The last and largest systems bound the launch, each on one CU of
-// 256: 256 DD / QD systems of order 64 to 512, b = 64, 73.1 -> 36.0 ms, 16 of
-// order 100 to 400 33.1 -> 17.6 ms; with more work than CUs to the end (1000 of
-// order 150 to 256) 33.2 -> 32.1 ms.
+// 256, so helpers take the job of the owner with the most work left (33.0 ms
+// below; 34.6 in the order of the slots).  256 DD / QD systems of order 64 to
+// 512, b = 64: 73.1 -> 33.0 ms, 16 of order 100 to 400 33.1 -> 12.7 ms, one of
+// order 512 (QD) 66.7 -> 17.4 ms; with more work than CUs to the end (1000 of
+// order 150 to 256) 33.2 -> 31.4 ms.
 // ---------------------------------------------------------------------------
 struct BatchSlot {  // a line of its own for each owner
   int32_t done, item, k0, phase;
-  int32_t pad[28];
+  int32_t j0, j1, zeros;  // phase 2
+  int32_t pad[25];
 };
 struct Board {
   int32_t next, idle, finished, owners;  // items taken, helpers, items done, scratch slots taken
   int32_t pad[60];
   // followed by nslot job words (rounded up to 64) and nslot slots
-  __device__ uint32_t *jobs() { return (uint32_t *)(this + 1); }
+  __device__ uint64_t *jobs() { return (uint64_t *)(this + 1); }
   __device__ BatchSlot *slots(int nslot) { return (BatchSlot *)(jobs() + ((nslot + 63) & ~63)); }
 };
 static_assert(sizeof(BatchSlot) == 128 && sizeof(Board) == 256, "board layout");
@@ -548,39 +696,150 @@ __device__ __forceinline__ void run_task(const OzUpdate<NC, NWM, NT> &u, int pha
   }
 }
 
+constexpr int SB = 8;  // columns of a panel's sub-block when steps are deferred
+
+// Task t of the deferred steps j0 .. j1-1 on the panel's columns j1 .. k1-1,
+// rows from j1 on: NT elements, one per thread, kept in registers through all
+// steps; zeros: the steps with an exactly zero pivot, which update nothing.
+template <int NC, int NT>
+__device__ __forceinline__ void deferred_task(double *A, int64_t n, int j0, int j1, int k1,
+                                              uint32_t zeros, int t) {
+  const int mr = (int)n - j1, idx = t * NT + (int)threadIdx.x;
+  if (idx >= mr * (k1 - j1)) return;
+  const int i = j1 + idx % mr, c = j1 + idx / mr;
+  const double *pl_ = A + (i + (int64_t)j0 * n) * NC, *pu = A + (j0 + (int64_t)c * n) * NC;
+  double *dst = A + (i + (int64_t)c * n) * NC;
+  double a[NC], l[NC], u[NC];
+  ozx::load<NC>(dst, a);
+  ozx::load<NC>(pl_, l);
+  ozx::load<NC>(pu, u);
+  for (int k = j0; k < j1; ++k) {
+    double ln[NC], un[NC], o[NC];
+    const bool more = k + 1 < j1;
+    pl_ += more ? n * NC : 0;
+    pu += more ? NC : 0;
+    ozx::load<NC>(pl_, ln);
+    ozx::load<NC>(pu, un);
+    if (!((zeros >> (k - j0)) & 1u)) {
+      ozx::fms<NC>(a, l, u, o);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) a[q] = o[q];
+    }
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      l[q] = ln[q];
+      u[q] = un[q];
+    }
+  }
+  ozx::store<NC>(dst, a);
+}
+
+// By the owner: the tasks 0 .. total-1, shared when there is a helper (share),
+// else one after the other.  put() writes what the helpers need to the slot.
+template <class P, class F>
+__device__ __forceinline__ void offer(bool share, int total, uint32_t prio, uint64_t *job, BatchSlot *sl, int *s_task,
+                                      P put, F run) {
+  if (!share) {
+    for (int t = 0; t < total; ++t) run(t);
+    __syncthreads();
+    return;
+  }
+  const int tid = threadIdx.x;
+  if (tid == 0) {
+    st_agent(&sl->done, 0);
+    put();
+  }
+  wg_release();
+  if (tid == 0) st_agent(job, (uint64_t)prio << 32 | (uint32_t)total << 16);
+  int mine = 0;
+  for (;; ++mine) {
+    if (tid == 0) *s_task = (int)(add_agent(job, (uint64_t)1) & 0xffffu);
+    __syncthreads();
+    const int t = *s_task;
+    __syncthreads();
+    if (t >= total) break;
+    run(t);
+    __syncthreads();
+  }
+  if (tid == 0)
+    while (ld_agent(&sl->done) + mine < total) __builtin_amdgcn_s_sleep(4);
+  wg_acquire();
+}
+
 template <int NC, int NWM, int NT>
 __device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item, double (*rkey)[4],
                             int64_t *ridx, int *s_info, const DevPlan *pl, uint8_t *ws, int b,
-                            uint32_t *stage, Board *bd, uint32_t *job, BatchSlot *sl, int *s_task) {
+                            uint32_t *stage, double (*xs)[4], int64_t *pv, Board *bd, uint64_t *job, BatchSlot *sl, int *s_task) {
   const int tid = threadIdx.x;
   const int64_t n = it.n;
   double *A = it.A;
   auto E = [&](int64_t i, int64_t c) { return A + (i + c * n) * NC; };
+  // idle workgroups (the same answer for every thread)
+  auto helpers = [&]() {
+    __syncthreads();
+    if (tid == 0) *s_task = ld_agent(&bd->idle);
+    __syncthreads();
+    const int h = *s_task;
+    __syncthreads();
+    return h;
+  };
   if (tid == 0) *s_info = 0;
   __syncthreads();
   for (int64_t k0 = 0; k0 < n; k0 += b) {
     const int64_t k1 = k0 + b < n ? k0 + b : n;
-    for (int64_t j = k0; j < k1; ++j) {
-      // rank-1 update of the panel's own columns j+1 .. k1-1; none after an
-      // exactly zero pivot (the column is left as it is, as in LAPACK's
-      // unblocked panel)
-      const bool zero = pivot_column<NC, NT>(it, j, rkey, ridx, s_info);
-      fms_sweep<NC, NT>(zero ? 0 : (int32_t)(n - j - 1), (int32_t)(k1 - j - 1),
-                        [&](int32_t i, int32_t c, double *&pa, const double *&pl_, const double *&pu) {
-                          pa = E(j + 1 + i, j + 1 + c);
-                          pl_ = E(j + 1 + i, j);
-                          pu = E(j, j + 1 + c);
-                        });
-      __syncthreads();
+    const float rem = (float)(n - k0);  // work left, for the helpers' choice
+    const uint32_t left = (uint32_t)((float)(NC * NC) * rem * rem * rem * 0.25f) + 1u;
+    // deferring steps shortens the owner's work only where others take it:
+    // 16 systems of order 100 to 400 17.6 -> 13.0 ms; without helpers it is 2 to
+    // 3 % slower (700 of order 64 to 200, 12.25 -> 12.5 ms), and 256 systems
+    // take 33.0 ms with the line at an eighth, a quarter or half of the
+    // workgroups idle, 33.3 at three quarters
+    const bool many = helpers() * 2 > (int)gridDim.x;
+    const int64_t sb = many ? SB : b;
+    for (int64_t j0 = k0; j0 < k1; j0 += sb) {
+      // sub-block: its own columns see each step at once, the panel's other
+      // columns all its steps together afterwards
+      const int64_t j1 = j0 + sb < k1 ? j0 + sb : k1;
+      uint32_t zeros = 0;
+      for (int64_t j = j0; j < j1; ++j) {
+        // no update after an exactly zero pivot (the column is left as it is,
+        // as in LAPACK's unblocked panel)
+        const bool zero = pivot_column<NC, NT>(it, j, rkey, ridx, s_info);
+        zeros |= (uint32_t)zero << ((j - j0) & 31);
+        fms_sweep<NC, NT>(zero ? 0 : (int32_t)(n - j - 1), (int32_t)(j1 - j - 1),
+                          [&](int32_t i, int32_t c, double *&pa, const double *&pl_, const double *&pu) {
+                            pa = E(j + 1 + i, j + 1 + c);
+                            pl_ = E(j + 1 + i, j);
+                            pu = E(j, j + 1 + c);
+                          });
+        __syncthreads();
+      }
+      if (j1 == k1) break;
+      // the sub-block's rows of the other columns step by step, then the rest
+      for (int64_t k = j0; k + 1 < j1; ++k) {
+        fms_sweep<NC, NT>((zeros >> (k - j0)) & 1u ? 0 : (int32_t)(j1 - k - 1), (int32_t)(k1 - j1),
+                          [&](int32_t i, int32_t c, double *&pa, const double *&pl_, const double *&pu) {
+                            pa = E(k + 1 + i, j1 + c);
+                            pl_ = E(k + 1 + i, k);
+                            pu = E(k, j1 + c);
+                          });
+        __syncthreads();
+      }
+      const int total = (int)(((n - j1) * (k1 - j1) + NT - 1) / NT);
+      offer(total > 1, total, left, job, sl, s_task,
+            [&]() {
+              st_agent(&sl->item, item);
+              st_agent(&sl->k0, (int32_t)k0);
+              st_agent(&sl->j0, (int32_t)j0);
+              st_agent(&sl->j1, (int32_t)j1);
+              st_agent(&sl->zeros, (int32_t)zeros);
+              st_agent(&sl->phase, 2);
+            },
+            [&](int t) { deferred_task<NC, NT>(A, n, (int)j0, (int)j1, (int)k1, zeros, t); });
     }
     if (k1 >= n) break;
     const OzUpdate<NC, NWM, NT> u(A, n, k0, k1, pl, ws);
-    // one tile: nothing to share
-    if (tid == 0) *s_task = u.m2 > 64 ? ld_agent(&bd->idle) : 0;
-    __syncthreads();
-    const bool share = *s_task > 0;
-    __syncthreads();
-    if (!share) {
+    if (u.m2 <= 64 || helpers() == 0) {  // one tile: nothing to share
       u.solve_u12(0, u.m2);
       u.residues(true, 0, u.Mp);
       u.residues(false, 0, u.Mp);
@@ -588,33 +847,29 @@ __device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item,
       u.tiles(0, u.Mp / 64, 0, u.Mp / 64, stage);
       continue;
     }
-    for (int phase = 0; phase < 2; ++phase) {
-      const int total = tasks_of(u, phase);
-      if (tid == 0) {
-        st_agent(&sl->done, 0);
-        st_agent(&sl->item, item);
-        st_agent(&sl->k0, (int32_t)k0);
-        st_agent(&sl->phase, phase);
-      }
-      wg_release();
-      if (tid == 0) st_agent(job, (uint32_t)total << 16);
-      int mine = 0;
-      for (;; ++mine) {
-        if (tid == 0) *s_task = (int)(add_agent(job, 1u) & 0xffffu);
-        __syncthreads();
-        const int t = *s_task;
-        __syncthreads();
-        if (t >= total) break;
-        run_task(u, phase, t, stage);
-        __syncthreads();
-      }
-      if (tid == 0)
-        while (ld_agent(&sl->done) + mine < total) __builtin_amdgcn_s_sleep(4);
-      wg_acquire();
-    }
+    for (int phase = 0; phase < 2; ++phase)
+      offer(true, tasks_of(u, phase), left, job, sl, s_task,
+            [&]() {
+              st_agent(&sl->item, item);
+              st_agent(&sl->k0, (int32_t)k0);
+              st_agent(&sl->phase, phase);
+            },
+            [&](int t) { run_task(u, phase, t, stage); });
   }
   if (tid == 0) *it.info = *s_info;
-  solve_one<NC, NT>(it);
+  solve_one<NC, NT>(it, xs, pv);
+}
+
+template <int NC, int NWM, int NT>
+__device__ __forceinline__ void help(const ozII_batch_item &it, BatchSlot *sl, const DevPlan *pl,
+                                     uint8_t *ws, int b, int t, uint32_t *stage) {
+  const int phase = ld_agent(&sl->phase);
+  const int64_t k0 = ld_agent(&sl->k0), k1 = k0 + b < it.n ? k0 + b : it.n;
+  if (phase == 2)
+    deferred_task<NC, NT>(it.A, it.n, ld_agent(&sl->j0), ld_agent(&sl->j1), (int)k1,
+                          (uint32_t)ld_agent(&sl->zeros), t);
+  else
+    run_task(OzUpdate<NC, NWM, NT>(it.A, it.n, k0, k1, pl, ws), phase, t, stage);
 }
 
 // One workgroup of BTZ threads per CU (the update's stages need more than
@@ -630,6 +885,10 @@ __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *item
   static_assert(BTZ * CST * 4 >= BTZ * (32 + 8), "pivot search arrays fit the staging");
   double(*rkey)[4] = (double(*)[4])lds;
   int64_t *ridx = (int64_t *)(lds + BTZ * 8);
+  // the solve's right-hand side and pivots too
+  static_assert(BTZ * CST * 4 >= SOLVE_N * (32 + 8), "solve arrays fit the staging");
+  double(*xs)[4] = (double(*)[4])lds;
+  int64_t *pv = (int64_t *)(lds + SOLVE_N * 8);
   __shared__ int s_item, s_info, s_task;
   __shared__ int s_slot;
   BatchSlot *slots = bd->slots(nslot);
@@ -648,7 +907,8 @@ __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *item
     uint8_t *myws = ws + (int64_t)ms * slot;
     if (times && threadIdx.x == 0) times[2 * it.reserved] = __builtin_amdgcn_s_memrealtime();
 #define OZ_LU(NC_, NWM_, PL_)                                                                        \
-  lu_solve_oz<NC_, NWM_, BTZ>(it, q, rkey, ridx, &s_info, PL_, myws, b, lds, bd, bd->jobs() + ms, \
+  lu_solve_oz<NC_, NWM_, BTZ>(it, q, rkey, ridx, &s_info, PL_, myws, b, lds, xs, pv, bd,          \
+                              bd->jobs() + ms,                                                      \
                               slots + ms, &s_task)
     if (it.nc == 2) OZ_LU(2, 6, pl2);
     else if (it.nc == 3) OZ_LU(3, 4, pl3);
@@ -671,29 +931,40 @@ __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *item
       int got = -1;
       while (got < 0) {
         const bool over = ld_agent(&bd->finished) >= count;
-        for (int s0 = 0; s0 < nslot && got < 0; s0 += 64) {
-          // helpers start their search at different slots
-          int s = s0 + lane;
-          bool open = false;
-          if (s < nslot) {
-            s = (s + (int)blockIdx.x) % nslot;
-            const uint32_t v = ld_agent(bd->jobs() + s);
-            open = (v & 0xffffu) < (v >> 16);
+        // the open job of the owner with the most work left
+        uint32_t best = 0;
+        int bs = -1;
+        for (int s = lane; s < nslot; s += 64) {
+          const uint64_t v = ld_agent(bd->jobs() + s);
+          const uint32_t pr = (uint32_t)(v >> 32);
+          if (((uint32_t)v & 0xffffu) < ((uint32_t)v >> 16) && pr > best) {
+            best = pr;
+            bs = s;
           }
-          const uint64_t m = __builtin_amdgcn_ballot_w64(open);
-          if (m == 0) continue;
-          const int pick = __builtin_amdgcn_readlane(s, __builtin_ctzll(m));
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+          const uint32_t ob = (uint32_t)__shfl_xor((int)best, off, 64);
+          const int os = __shfl_xor(bs, off, 64);
+          if (ob > best || (ob == best && os > bs)) {
+            best = ob;
+            bs = os;
+          }
+        }
+        bs = __builtin_amdgcn_readfirstlane(bs);
+        if (bs >= 0) {
           uint32_t v = 0;
-          if (lane == 0) v = add_agent(bd->jobs() + pick, 1u);
+          if (lane == 0) v = (uint32_t)add_agent(bd->jobs() + bs, (uint64_t)1);
           v = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
           if ((v & 0xffffu) < (v >> 16)) {
-            got = pick;
+            got = bs;
             if (lane == 0) s_task = (int)(v & 0xffffu);
           }
         }
         if (got < 0) {
           if (over) break;
-          __builtin_amdgcn_s_sleep(32);
+          if (bs < 0) __builtin_amdgcn_s_sleep(32);
+          else __builtin_amdgcn_s_sleep(4);
         }
       }
       if (lane == 0) s_slot = got;
@@ -702,14 +973,11 @@ __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *item
     const int hs = s_slot, t = s_task;
     __syncthreads();
     if (hs < 0) break;
-    const int q = ld_agent(&slots[hs].item), phase = ld_agent(&slots[hs].phase);
-    const int64_t k0 = ld_agent(&slots[hs].k0);
-    const ozII_batch_item it = items[q];
-    const int64_t k1 = k0 + b;  // a step that is shared has columns after it
+    const ozII_batch_item it = items[ld_agent(&slots[hs].item)];
     uint8_t *hws = ws + (int64_t)hs * slot;
-    if (it.nc == 2) run_task(OzUpdate<2, 6, BTZ>(it.A, it.n, k0, k1, pl2, hws), phase, t, lds);
-    else if (it.nc == 3) run_task(OzUpdate<3, 4, BTZ>(it.A, it.n, k0, k1, pl3, hws), phase, t, lds);
-    else run_task(OzUpdate<4, 4, BTZ>(it.A, it.n, k0, k1, pl4, hws), phase, t, lds);
+    if (it.nc == 2) help<2, 6, BTZ>(it, slots + hs, pl2, hws, b, t, lds);
+    else if (it.nc == 3) help<3, 4, BTZ>(it, slots + hs, pl3, hws, b, t, lds);
+    else help<4, 4, BTZ>(it, slots + hs, pl4, hws, b, t, lds);
     wg_release();
     if (threadIdx.x == 0) add_agent(&slots[hs].done, 1);
   }
@@ -755,7 +1023,7 @@ hipError_t launch_batch(const ozII_batch_item *items, int count, int *queue, uin
   return hipGetLastError();
 }
 size_t batch_board_bytes(int nslot) {
-  return sizeof(Board) + (size_t)((nslot + 63) / 64 * 64) * 4 + (size_t)nslot * sizeof(BatchSlot);
+  return sizeof(Board) + (size_t)((nslot + 63) / 64 * 64) * 8 + (size_t)nslot * sizeof(BatchSlot);
 }
 
 hipError_t launch_batch_oz(const ozII_batch_item *items, int count, void *board, int nslot,
@@ -764,7 +1032,7 @@ hipError_t launch_batch_oz(const ozII_batch_item *items, int count, void *board,
   if (count <= 0) return hipSuccess;
   if (b < 1 || b > 256 || nslot < std::min(count, grid)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_batch_clear, dim3(1), dim3(256), 0, s, (int *)board,
-                     (int)(sizeof(Board) / 4) + (nslot + 63) / 64 * 64);
+                     (int)(sizeof(Board) / 4) + (nslot + 63) / 64 * 128);
   hipLaunchKernelGGL(k_batch_lu_oz, dim3((unsigned)grid), dim3(BTZ), 0, s, items, count,
                      (Board *)board, nslot, times, pl2, pl3, pl4, ws, slot, b);
   return hipGetLastError();

@@ -2,7 +2,7 @@
 (few systems) and with none idle at first (more systems than workgroups), bit
 for bit against the oracle: trailing blocks and panels at the edges of a task,
 a zero column, widths that are no multiple of anything, and replays of a
-captured graph."""
+captured graph; orders above the threads of a workgroup."""
 import numpy as np
 import pytest
 
@@ -65,3 +65,37 @@ def test_more_than_workgroups():
         g.replay()
         torch.cuda.synchronize()
         _check(work, exp * 120, systems)
+
+
+@pytest.mark.parametrize("nc,n,b", [(2, 1024, 0), (3, 1025, 0), (2, 1030, 0), (2, 1024, 64),
+                                    (4, 513, 32), (3, 600, 128)])
+def test_several_rows_per_thread(nc, n, b):
+    """Orders above the threads of a workgroup: the factors and solution of
+    getrf / getrs at the same block (b = 0: unblocked, native update)."""
+    import torch
+    import paper_2609_29554_amd as Z
+    note(f"batch against getrf nc={nc} n={n} b={b}")
+    g = torch.Generator(device="cuda").manual_seed(n + nc)
+    A = torch.zeros(n, n, nc, dtype=torch.float64, device="cuda")
+    A[..., 0] = torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64)
+    A[..., 1] = A[..., 0] * 2.0 ** -56 * torch.rand(n, n, generator=g, device="cuda", dtype=torch.float64)
+    B = torch.zeros(1, n, nc, dtype=torch.float64, device="cuda")
+    B[..., 0] = torch.randn(1, n, generator=g, device="cuda", dtype=torch.float64)
+    LU, X = A.clone(), B.clone()
+    ip = torch.zeros(n, dtype=torch.int64, device="cuda")
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
+    c = ctx()
+    opts = Z.make_opts(block=b, method=Z.METHOD_OZAKI, backend=Z.BE_INT8) if b else None
+    c.batch_prepare([(LU, X, ip, info)], opts)
+    c.batch_run()
+    c.sync_check()
+    wLU, wX = A.clone(), B.clone()
+    if b:
+        wip, winfo = c.getrf(wLU, block=b, method=Z.METHOD_OZAKI, opts=opts)
+    else:
+        wip, winfo = c.getrf(wLU, block=1, method=Z.METHOD_NAIVE)
+    c.getrs(wLU, wip, wX)
+    c.sync_check()
+    assert torch.equal(ip, wip) and int(info) == int(winfo) == 0
+    assert torch.equal(LU, wLU)
+    assert torch.equal(X, wX)
