@@ -1096,6 +1096,9 @@ hipError_t launch_panel(int nc, double *A, int64_t lda, int64_t n, int64_t k, in
   hipLaunchKernelGGL(k_panel_begin, dim3(1), dim3(1), 0, s, epoch, nmoved);
   void *args[] = {&A, &lda, &n, &k, &kb, &R, &ipiv, &info, &lines, &err,
                   &crow, &epoch, &perm, &moved, &nmoved};
+  // one workgroup needs no others beside it: an ordinary launch, without the
+  // cooperative queue's 11 us before and after it
+  if (G == 1) return hipLaunchKernel(fn, dim3(1), dim3(PANEL_NT), args, (unsigned)lds, s);
   return hipLaunchCooperativeKernel(fn, dim3(G), dim3(PANEL_NT), args, (unsigned)lds, s);
 }
 

@@ -1338,7 +1338,9 @@ ozII_status ozII_getrf(ozII_handle h, int32_t nc, int64_t n, double *A, int64_t 
     // 26.2 ms.  More workgroups where the rows do not fit in LDS (the kernel's
     // static LDS is below 512 bytes).
     int G = 0, R = 0;
-    const int G20 = (int)std::min<int64_t>(128, std::max<int64_t>(8, (nr + 19) / 20));
+    // Up to 32 rows are one workgroup's, launched alone: n = b = 32 DD 151 -> 124
+    // us, QD 295 -> 252; n = 130, b = 32 (last panel 2 rows) 826 -> 810.
+    const int G20 = nr <= 32 ? 1 : (int)std::min<int64_t>(128, std::max<int64_t>(8, (nr + 19) / 20));
     for (int G0 : {G20, 128, 256}) {
       int g = G0, r = 0, maxb = 0;
       bool ok = false;

@@ -1,0 +1,37 @@
+"""getrf where a panel's rows fit one workgroup (up to 32) and just above, as
+the whole matrix and as the last panel, with ties and zero columns,
+bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+from tests.gpu_util import ctx, note, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nc,n,b", [(2, 1, 32), (4, 2, 32), (3, 31, 32), (4, 32, 32), (2, 33, 32),
+                                    (4, 34, 32), (2, 64, 32), (4, 65, 32), (3, 96, 64), (2, 32, 5)])
+@pytest.mark.parametrize("kind", ["random", "ties", "zero"])
+def test_small_panels(nc, n, b, kind):
+    import paper_2609_29554_amd as Z
+    note(f"getrf small panels nc={nc} n={n} b={b} {kind}")
+    A = W.graded(n, nc, 30.0, np.random.default_rng(n + nc))
+    if kind == "ties":
+        A[:, :, 0] = np.where(A[:, :, 0] < 0, -1.0, 1.0)
+        A[:, :, 1:] = 0.0
+        A[np.arange(n), np.arange(n), 0] = 3.0
+    if kind == "zero":
+        A[n // 2] = 0.0
+    LU, ipiv, info, _ = O.getrf(A, b, O.METHOD_OZAKI, O.make_plan(53 * nc, b))
+    src = to_dev(A)
+    dA = src.clone()
+    opts = Z.make_opts(block=b, method=Z.METHOD_OZAKI, backend=Z.BE_INT8)
+    for _ in range(2):
+        dA.copy_(src)
+        dip, dinfo = ctx().getrf(dA, block=b, method=Z.METHOD_OZAKI, opts=opts)
+        ctx().sync_check()
+        assert int(to_host(dinfo)[0]) == info
+        assert np.array_equal(to_host(dip), ipiv)
+        assert np.array_equal(to_host(dA), LU)
