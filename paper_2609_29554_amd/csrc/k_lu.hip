@@ -187,11 +187,11 @@ __device__ __forceinline__ int lead_winner(double lead, int nlead, int &w) {
 constexpr int PANEL_NT = 512;  // threads per panel workgroup
 constexpr int PANEL_NW = PANEL_NT - 64;  // of these, the ones that apply the updates
 
-// Before a panel: nothing moved yet, and a fresh range of tags (a panel has
-// at most 512 columns).
-__global__ void k_panel_begin(uint32_t *epoch, int *nmoved) {
-  *epoch += 1024u;
-  *nmoved = 0;
+// Before the panels of a factorisation: info, and a fresh range of tags for each
+// (a panel has at most 512 columns).
+__global__ void k_getrf_begin(uint32_t *epoch, uint32_t panels, int32_t *info) {
+  *epoch += 1024u * panels;
+  *info = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -223,8 +223,8 @@ template <int NC>
 __global__ __launch_bounds__(PANEL_NT) void k_panel(double *A, int64_t lda, int64_t n, int64_t k,
                                                     int kb, int R, int64_t *ipiv, int32_t *info,
                                                     uint64_t *lines, int *err, uint64_t *crow,
-                                                    const uint32_t *epoch, int *perm_out,
-                                                    int *moved, int *nmoved) {
+                                                    const uint32_t *epoch, int panel,
+                                                    int *perm_out, int *moved, int *nmoved) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   // the panel is the critical path of the factorisation, and with
   // look-ahead the previous step's Schur update runs beside it on the same
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(PANEL_NT) void k_panel(double *A, int64_t lda, int6
 
   const int r0 = wg * R;
   const int cnt = r0 < nr ? (nr - r0 < R ? nr - r0 : R) : 0;
-  const uint32_t tag0 = *epoch + 1u;  // tag of column 0
+  const uint32_t tag0 = *epoch - 1024u * (uint32_t)panel + 1u;  // tag of column 0
   auto RW = [&](int r, int c) { return rows + ((size_t)r * kb + c) * NC; };
   auto LINE = [&](int b, int w) { return lines + ((size_t)b * G + w) * LINE_WORDS; };
   auto CROW = [&](int b, int w) { return crow + ((size_t)b * G + w) * kb * NC * 2; };
@@ -471,7 +471,10 @@ __global__ __launch_bounds__(PANEL_NT) void k_panel(double *A, int64_t lda, int6
       }
     }
     __syncthreads();
-    if (s_fail) return;
+    if (s_fail) {
+      if (wg == 0 && tid == 0) *nmoved = 0;  // no interchange after a failed wait
+      return;
+    }
     if (last) break;
     const int zero = s_zero[buf];
     if (tid < 64) {
@@ -1086,16 +1089,21 @@ const void *panel_kernel_ptr(int nc) {
   return (const void *)k_panel<4>;
 }
 
+hipError_t launch_getrf_begin(uint32_t *epoch, int64_t panels, int32_t *info, hipStream_t s) {
+  hipLaunchKernelGGL(k_getrf_begin, dim3(1), dim3(1), 0, s, epoch, (uint32_t)panels, info);
+  return hipGetLastError();
+}
+
 hipError_t launch_panel(int nc, double *A, int64_t lda, int64_t n, int64_t k, int kb, int R, int G,
                         int64_t *ipiv, int32_t *info, uint64_t *lines, int *err, uint64_t *crow,
-                        uint32_t *epoch, int *perm, int *moved, int *nmoved, hipStream_t s) {
+                        uint32_t *epoch, int panel, int *perm, int *moved, int *nmoved,
+                        hipStream_t s) {
   const size_t lds = panel_lds_bytes(nc, kb, R, n - k);
   const void *fn = panel_kernel_ptr(nc);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_panel_begin, dim3(1), dim3(1), 0, s, epoch, nmoved);
   void *args[] = {&A, &lda, &n, &k, &kb, &R, &ipiv, &info, &lines, &err,
-                  &crow, &epoch, &perm, &moved, &nmoved};
+                  &crow, &epoch, &panel, &perm, &moved, &nmoved};
   // one workgroup needs no others beside it: an ordinary launch, without the
   // cooperative queue's 11 us before and after it
   if (G == 1) return hipLaunchKernel(fn, dim3(1), dim3(PANEL_NT), args, (unsigned)lds, s);
@@ -1242,18 +1250,16 @@ hipError_t launch_trsv(int nc, int fwd, const double *LU, int64_t lda, double *X
   if (n <= 0 || nrhs <= 0) return hipSuccess;
   const int nr = nrhs > 1 ? 2 : 1;
   const dim3 g((unsigned)((n + TRSV_R - 1) / TRSV_R), (unsigned)((nrhs + nr - 1) / nr));
-  // per group: finished positions and the ticket of the next row block
-  hipLaunchKernelGGL(k_fill_int, dim3((2 * g.y + 255) / 256), dim3(256), 0, s, (int *)sync, 0,
-                     (int64_t)2 * g.y);
+  // per group: finished positions and the ticket of the next row block, those
+  // of the backward solve behind those of the forward one
+  if (fwd)
+    hipLaunchKernelGGL(k_fill_int, dim3((4 * g.y + 255) / 256), dim3(256), 0, s, (int *)sync, 0,
+                       (int64_t)4 * g.y);
+  else
+    sync += 2 * g.y;
   if (nc == 2) trsv_nc<2>(fwd, g, nr, s, LU, lda, X, ldx, nrhs, n, sync, err);
   else if (nc == 3) trsv_nc<3>(fwd, g, nr, s, LU, lda, X, ldx, nrhs, n, sync, err);
   else trsv_nc<4>(fwd, g, nr, s, LU, lda, X, ldx, nrhs, n, sync, err);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_int(int *p, int v, int64_t cnt, hipStream_t s) {
-  if (cnt <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_int, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, p, v, cnt);
   return hipGetLastError();
 }
 

@@ -611,7 +611,7 @@ ozII_status ensure_panel(ozII_ctx *h, int64_t n, int kb) {
   if (!h->bar) {
     // barrier-free words of the panel and the solves: error flag, moved rows,
     // tag base, then the counters of the pipelined solves
-    const size_t bytes = 64 + 8 * (size_t)ozl::TRSV_MAXGROUPS;
+    const size_t bytes = 64 + 16 * (size_t)ozl::TRSV_MAXGROUPS;
     e = hipMalloc((void **)&h->bar, bytes);
     if (e == hipSuccess) e = hipMemset(h->bar, 0, bytes);
     if (e == hipSuccess) {
@@ -1323,7 +1323,8 @@ ozII_status ozII_getrf(ozII_handle h, int32_t nc, int64_t n, double *A, int64_t 
     const hipError_t ee = ozl::launch_trsm_lower_unit(nc, L11, lda, A12, lda, kb, nb, st_);
     return ee == hipSuccess ? OZII_OK : hip_fail(h, ee, "trsm");
   };
-  if ((e = ozl::launch_fill_int(info, 0, 1, s)) != hipSuccess) return hip_fail(h, e, "fill info");
+  if ((e = ozl::launch_getrf_begin(h->epoch, (n + b - 1) / b, info, s)) != hipSuccess)
+    return hip_fail(h, e, "getrf begin");
   bool side_busy = false;
   for (int64_t k = 0; k < n; k += b) {
     const int kb = (int)std::min<int64_t>(b, n - k);
@@ -1369,7 +1370,7 @@ ozII_status ozII_getrf(ozII_handle h, int32_t nc, int64_t n, double *A, int64_t 
       // the previous step's update on the columns right of it
       ProfScope ps(h, OZ_STAGE_PANEL, 16.0 * nc * (double)nr * kb, (double)nr * kb * kb / 2.0);
       if ((e = ozl::launch_panel(nc, A, lda, n, k, kb, R, G, ipiv, info, h->lines, h->err, h->crow,
-                                 h->epoch, h->perm, h->moved, h->nmoved, s)) != hipSuccess)
+                                 h->epoch, (int)(k / b), h->perm, h->moved, h->nmoved, s)) != hipSuccess)
         return hip_fail(h, e, "panel");
     }
     if (side_busy) {

@@ -98,11 +98,15 @@ size_t panel_lds_bytes(int nc, int kb, int R, int64_t nr);
 hipError_t panel_max_blocks(int nc, int kb, int R, int64_t nr, int *maxblocks);
 // bytes of a candidate row of up to kb expansions
 size_t panel_row_bytes(int kb);
+// before the panels 0 .. panels-1 of a factorisation: info = 0 and their tags
+hipError_t launch_getrf_begin(uint32_t *epoch, int64_t panels, int32_t *info, hipStream_t s);
 // lines: 2 * G candidate lines of 128 bytes; crow: 2 * G candidate rows; both
-// zeroed once when allocated, as is epoch, the base of the panels' tags
+// zeroed once when allocated, as is epoch, the base of the panels' tags; panel:
+// its number in the factorisation
 hipError_t launch_panel(int nc, double *A, int64_t lda, int64_t n, int64_t k, int kb, int R, int G,
                         int64_t *ipiv, int32_t *info, uint64_t *lines, int *err, uint64_t *crow,
-                        uint32_t *epoch, int *perm, int *moved, int *nmoved, hipStream_t s);
+                        uint32_t *epoch, int panel, int *perm, int *moved, int *nmoved,
+                        hipStream_t s);
 hipError_t launch_laswp(int nc, double *A, int64_t lda, int64_t k, int64_t c0, int64_t c1,
                         const int *perm, const int *moved, const int *nmoved, hipStream_t s);
 hipError_t launch_trsm_lower_unit(int nc, const double *L, int64_t lda, double *X, int64_t ldx,
@@ -114,7 +118,6 @@ hipError_t launch_naive_gemm(int nc, const double *A, int64_t lda, const double 
                              hipStream_t s);
 hipError_t launch_apply_ipiv(int nc, double *B, int64_t ldb, int64_t n, int64_t nrhs,
                              const int64_t *ipiv, hipStream_t s);
-hipError_t launch_fill_int(int *p, int v, int64_t cnt, hipStream_t s);
 
 // limb format (k_limbs.hip): exponents, producer (INT8 or binary64 planes), consumer
 // (exact group sums as nwords-word columns, word k of element i + j M at
@@ -161,9 +164,10 @@ hipError_t launch_limb_sub(uint64_t *climb, int32_t *cexp, uint8_t *csign, int64
 hipError_t launch_limb_zero(uint64_t *limb, int32_t *lexp, uint8_t *lsign, int64_t ld,
                             int64_t plane, int nlimb, int64_t M, int64_t N, hipStream_t s);
 // pipelined triangular solve (fwd: unit lower, ascending; else upper,
-// descending, dividing by the diagonal); sync: two device words owned by the
-// caller per right-hand side, or per pair of them (finished-position counter
-// and row-block ticket), reset by the launcher
+// descending, dividing by the diagonal); sync: four device words owned by
+// the caller per right-hand side, or per pair of them (finished-position counter
+// and row-block ticket of each direction), reset by the forward solve's launch
+// for the backward one after it too
 hipError_t launch_trsv(int nc, int fwd, const double *LU, int64_t lda, double *X, int64_t ldx,
                        int64_t nrhs, int64_t n, uint32_t *sync, int *err, hipStream_t s);
 // row blocks x pairs of right-hand sides that are on the chip at once (two
