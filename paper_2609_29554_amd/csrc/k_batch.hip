@@ -630,7 +630,7 @@ struct OzUpdate {
 // coherent.  The last and largest systems bound the launch, each on one CU of
 // 256, so helpers take the job of the owner with the most work left (33.0 ms
 // below; 34.6 in the order of the slots).  256 DD / QD systems of order 64 to
-// 512, b = 64: 73.1 -> 33.0 ms, 16 of order 100 to 400 33.1 -> 12.7 ms, one of
+// 512, b = 64: 73.1 -> 32.9 ms, 16 of order 100 to 400 33.1 -> 12.7 ms, one of
 // order 512 (QD) 66.7 -> 17.4 ms; with more work than CUs to the end (1000 of
 // order 150 to 256) 33.2 -> 31.4 ms.
 // ---------------------------------------------------------------------------
