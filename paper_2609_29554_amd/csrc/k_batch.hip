@@ -795,8 +795,11 @@ __device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item,
     // 16 systems of order 100 to 400 17.6 -> 13.0 ms; without helpers it is 2 to
     // 3 % slower (700 of order 64 to 200, 12.25 -> 12.5 ms), and 256 systems
     // take 33.0 ms with the line at an eighth, a quarter or half of the
-    // workgroups idle, 33.3 at three quarters
-    const bool many = helpers() * 2 > (int)gridDim.x;
+    // workgroups idle, 33.3 at three quarters.  A small panel's steps are not
+    // worth a task: with the line at 0 / 6 / 12 / 24 NT elements, 71 of order 36
+    // to 58 take 1.46 / 1.31 / 1.31 / 1.31 ms, 16 of order 100 to 400 12.8 / 12.6 /
+    // 12.7 / 13.4, 100 of order 150 to 300 (b = 32) 11.9 / 11.7 / 11.4 / 11.7
+    const bool many = (n - k0) * (k1 - k0) >= 12 * NT && helpers() * 2 > (int)gridDim.x;
     const int64_t sb = many ? SB : b;
     for (int64_t j0 = k0; j0 < k1; j0 += sb) {
       // sub-block: its own columns see each step at once, the panel's other
