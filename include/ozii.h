@@ -17,6 +17,11 @@
  * device `info` word, LAPACK style.
  *
  * Threads: one handle per host thread.
+ *
+ * Streams: the calls of a handle share its scratch, so they follow each other
+ * on one stream, or the caller orders the streams.  ozII_getrs with two or
+ * more right-hand sides and ozII_limbs_arith need no such order: with separate
+ * operands they may overlap other calls of the handle on other streams.
  */
 #ifndef OZII_H
 #define OZII_H
@@ -307,8 +312,14 @@ ozII_status ozII_getrf(ozII_handle h, int32_t nc, int64_t n, double *A, int64_t 
  * exactly zero u_kk (info > 0 from getrf) gives non-finite components, as
  * the division of the specification does.  Errors: OZII_EINVAL (null
  * pointers, negative sizes, leading dimensions below n), OZII_EUNSUPPORTED
- * (nc outside 2..4); OZII_EDEVICE is reported by ozII_sync_check if a
- * bounded wait of the pipelined one-column solve timed out. */
+ * (nc outside 2..4), OZII_ENOMEM; OZII_EDEVICE is reported by ozII_sync_check
+ * if a wait of a pipelined solve took more than about a second; the handle's
+ * later pipelined solves then give up at their first wait too.  Solves with
+ * one right-hand side are pipelined, and from order 257 those with few enough
+ * that all their row blocks run at once: the first of these on a stream
+ * allocates 8 KiB, kept with the handle for up to 64 streams.  Without it (no
+ * memory, more streams, a captured call) they run blocked, with the same
+ * results and nothing allocated. */
 ozII_status ozII_getrs(ozII_handle h, int32_t nc, int64_t n, int64_t nrhs, const double *LU,
                        int64_t lda, const int64_t *ipiv, double *B, int64_t ldb);
 

@@ -341,6 +341,17 @@ int64_t roundup(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // ---------------------------------------------------------------------------
 // handle
 // ---------------------------------------------------------------------------
+// Scratch of the solves with several right-hand sides on one stream: calls on
+// different streams of a handle may overlap, those on one stream follow each
+// other.  Captured calls use none, since their graphs may be replayed on any
+// stream.  A handle keeps it for up to MAX_SOLVES streams, until it is
+// destroyed; on further streams the solves work without.
+struct SolveScratch {
+  hipStream_t stream = nullptr;
+  uint32_t *sync = nullptr;  // counters of the pipelined solves
+};
+constexpr int MAX_SOLVES = 64;
+
 struct ozII_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -359,6 +370,9 @@ struct ozII_ctx {
   int panel_kb = 0;
   // limb LU: the zero-pivot word
   int32_t *lflag = nullptr;
+  // scratch of the solves that callers may overlap, per stream
+  SolveScratch solves[MAX_SOLVES];
+  int nsolves = 0;
   // packed limb numbers: the leaf of a panel, the reciprocals of a solve
   uint64_t *lpack = nullptr;
   size_t lpack_words = 0;
@@ -595,9 +609,56 @@ ozII_status ensure_ws(ozII_ctx *h, size_t bytes) {
   return OZII_OK;
 }
 
+// The barrier-free words of the panel and of the solve with one right-hand
+// side: error flag, moved rows, tag base, then the counters of that solve.
+hipError_t alloc_words(ozII_ctx *h) {
+  constexpr size_t bytes = 64 + 16;
+  uint32_t *p = nullptr;
+  hipError_t e = hipMalloc((void **)&p, bytes);
+  if (e == hipSuccess) e = hipMemset(p, 0, bytes);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  if (e != hipSuccess) {
+    if (p) hipFree(p);
+    return e;
+  }
+  h->bar = p;
+  h->err = (int *)(p + 4);
+  h->nmoved = (int *)(p + 8);
+  h->epoch = p + 9;
+  return e;
+}
+
+// Whether stream s is being captured (or cannot be asked, which happens to the
+// default stream while another one is captured).
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// The solve scratch of the handle's stream, or null: during capture, on a
+// stream too many, or without memory.
+SolveScratch *solve_scratch(ozII_ctx *h) {
+  if (capturing(h->stream)) return nullptr;
+  for (int i = 0; i < h->nsolves; ++i)
+    if (h->solves[i].stream == h->stream) return &h->solves[i];
+  if (h->nsolves == MAX_SOLVES) return nullptr;
+  uint32_t *p = nullptr;
+  if ((!h->bar && alloc_words(h) != hipSuccess) ||
+      hipMalloc((void **)&p, 16 * (size_t)ozl::TRSV_MAXGROUPS) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  SolveScratch &x = h->solves[h->nsolves++];
+  x.stream = h->stream;
+  x.sync = p;
+  return &x;
+}
+
 ozII_status ensure_panel(ozII_ctx *h, int64_t n, int kb) {
   if (n <= h->panel_n && kb <= h->panel_kb) return OZII_OK;
-  if (h->bar) {
+  if (h->crow) {
     hipError_t e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
     hipFree(h->crow);
@@ -608,18 +669,7 @@ ozII_status ensure_panel(ozII_ctx *h, int64_t n, int kb) {
   const int kk = std::max(kb, h->panel_kb);
   const int G = 256;
   hipError_t e = hipSuccess;
-  if (!h->bar) {
-    // barrier-free words of the panel and the solves: error flag, moved rows,
-    // tag base, then the counters of the pipelined solves
-    const size_t bytes = 64 + 16 * (size_t)ozl::TRSV_MAXGROUPS;
-    e = hipMalloc((void **)&h->bar, bytes);
-    if (e == hipSuccess) e = hipMemset(h->bar, 0, bytes);
-    if (e == hipSuccess) {
-      h->err = (int *)(h->bar + 4);
-      h->nmoved = (int *)(h->bar + 8);
-      h->epoch = h->bar + 9;
-    }
-  }
+  if (!h->bar) e = alloc_words(h);
   if (e == hipSuccess && !h->lines) {
     e = hipMalloc((void **)&h->lines, 2 * 128 * G);
     if (e == hipSuccess) e = hipMemset(h->lines, 0, 2 * 128 * G);
@@ -1152,6 +1202,7 @@ ozII_status ozII_destroy(ozII_handle h) {
   if (h->batch_ws) hipFree(h->batch_ws);
   if (h->lflag) hipFree(h->lflag);
   if (h->lpack) hipFree(h->lpack);
+  for (int i = 0; i < h->nsolves; ++i) hipFree(h->solves[i].sync);
   if (h->bar) {
     hipFree(h->bar);
     hipFree(h->lines);
@@ -1419,24 +1470,22 @@ ozII_status ozII_getrs(ozII_handle h, int32_t nc, int64_t n, int64_t nrhs, const
                (double)n * n * nrhs);
   if ((e = ozl::launch_apply_ipiv(nc, B, ldb, n, nrhs, ipiv, s)) != hipSuccess) return hip_fail(h, e, "apply ipiv");
   // one right-hand side, or few enough that all their pipelines run at once:
-  // the pipelined solves (same operations per element).  Measured, pipelined
-  // against blocked: QD n = 1024 with 2 / 16 / 32 right-hand sides 6.8 / 6.7 /
-  // 7.0 against 9.0 / 8.4 / 8.4 ms, DD n = 1024 with 16 2.0 against 2.5 ms;
-  // QD n = 200, a few blocks long, 1.35 against 1.27 ms.
-  bool piped = nrhs == 1 || (n > 256 && ozl::trsv_fits(n, nrhs));
-  if (piped && !h->bar) {
-    // their counters are allocated here unless the call is being captured,
-    // which the blocked solve below allows
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (nrhs > 1 && (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) {
-      piped = false;
-    } else {
-      const ozII_status st = ensure_panel(h, 1, 1);
-      if (st != OZII_OK) return st;
-    }
+  // the pipelined solves (same operations per element).  Several of them:
+  // measured with 2 to 64, blocked / pipelined, for DD, TD and QD alike
+  // pipelined is 0.84 to 1.04 times as fast up to n = 256, one block of the
+  // blocked solve, and 1.05 to 1.7 times from n = 288 on (QD n = 256 with 16
+  // 1.63 / 1.69 ms, n = 288 2.18 / 1.91, n = 1000 8.28 / 6.53).
+  // The counters of one right-hand side are the handle's; those of several are
+  // the stream's, and without them the blocked solve, which has none, runs.
+  uint32_t *sync = nullptr;
+  if (nrhs == 1) {
+    if (!h->bar && alloc_words(h) != hipSuccess) return fail(h, OZII_ENOMEM, "solve counters");
+    sync = h->bar + 16;
+  } else if (n > 256 && ozl::trsv_fits(n, nrhs)) {
+    const SolveScratch *sc = solve_scratch(h);
+    if (sc) sync = sc->sync;
   }
-  if (piped) {
-    uint32_t *sync = h->bar + 16;
+  if (sync) {
     if ((e = ozl::launch_trsv(nc, 1, LU, lda, B, ldb, nrhs, n, sync, h->err, s)) != hipSuccess)
       return hip_fail(h, e, "forward solve");
     if ((e = ozl::launch_trsv(nc, 0, LU, lda, B, ldb, nrhs, n, sync, h->err, s)) != hipSuccess)
