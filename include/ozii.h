@@ -20,8 +20,9 @@
  *
  * Streams: the calls of a handle share its scratch, so they follow each other
  * on one stream, or the caller orders the streams.  ozII_getrs with two or
- * more right-hand sides and ozII_limbs_arith need no such order: with separate
- * operands they may overlap other calls of the handle on other streams.
+ * more right-hand sides, ozII_getrs_limbs and ozII_limbs_arith need no such
+ * order: with separate operands they may overlap other calls of the handle on
+ * other streams.
  */
 #ifndef OZII_H
 #define OZII_H
@@ -247,6 +248,10 @@ ozII_status ozII_getrf_limbs(ozII_handle h, int32_t nlimb, int64_t n, ozII_limbs
  * u_kk) once its updates are in (an exactly zero u_kk gives x_k = 0).  LU
  * is the n x n factor matrix, B an n x nrhs limb matrix (element (i, r) at
  * index i + r ld), overwritten by X; device memory owned by the caller.
+ * From 4 limbs on the divisions use reciprocals of the diagonal in scratch of
+ * 8 n (nlimb + 1) bytes, which the handle allocates on first use and keeps for
+ * up to 64 streams; without it (no memory, more streams, a captured call) each
+ * runs its own division, with the same results and nothing allocated.
  * Errors: OZII_EINVAL (bad sizes, null pointers, bad descriptors,
  * nlimb outside 1..64), OZII_EHIP. */
 ozII_status ozII_getrs_limbs(ozII_handle h, int32_t nlimb, int64_t n, int64_t nrhs,

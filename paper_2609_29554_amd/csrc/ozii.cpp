@@ -341,14 +341,16 @@ int64_t roundup(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // ---------------------------------------------------------------------------
 // handle
 // ---------------------------------------------------------------------------
-// Scratch of the solves with several right-hand sides on one stream: calls on
-// different streams of a handle may overlap, those on one stream follow each
-// other.  Captured calls use none, since their graphs may be replayed on any
-// stream.  A handle keeps it for up to MAX_SOLVES streams, until it is
+// Scratch of one stream for the solves that callers may overlap (getrs with
+// several right-hand sides, getrs_limbs): calls on different streams of a
+// handle may run at once, those on one stream follow each other.  Captured
+// calls use none, since their graphs may be replayed on any stream.  A handle keeps it for up to MAX_SOLVES streams, until it is
 // destroyed; on further streams the solves work without.
 struct SolveScratch {
   hipStream_t stream = nullptr;
-  uint32_t *sync = nullptr;  // counters of the pipelined solves
+  uint32_t *sync = nullptr;   // counters of the pipelined solves
+  uint64_t *recip = nullptr;  // packed reciprocals of a limb factor's diagonal
+  size_t recip_words = 0;
 };
 constexpr int MAX_SOLVES = 64;
 
@@ -373,7 +375,7 @@ struct ozII_ctx {
   // scratch of the solves that callers may overlap, per stream
   SolveScratch solves[MAX_SOLVES];
   int nsolves = 0;
-  // packed limb numbers: the leaf of a panel, the reciprocals of a solve
+  // packed limb numbers: the leaf of a panel
   uint64_t *lpack = nullptr;
   size_t lpack_words = 0;
   // getrf look-ahead: a side stream (default priority) for the rest of each
@@ -637,23 +639,47 @@ bool capturing(hipStream_t s) {
   return true;
 }
 
-// The solve scratch of the handle's stream, or null: during capture, on a
-// stream too many, or without memory.
+// The solve scratch of the handle's stream, or null: during capture, or on a
+// stream too many.
 SolveScratch *solve_scratch(ozII_ctx *h) {
   if (capturing(h->stream)) return nullptr;
   for (int i = 0; i < h->nsolves; ++i)
     if (h->solves[i].stream == h->stream) return &h->solves[i];
   if (h->nsolves == MAX_SOLVES) return nullptr;
-  uint32_t *p = nullptr;
+  h->solves[h->nsolves].stream = h->stream;
+  return &h->solves[h->nsolves++];
+}
+
+// The stream's counters of the pipelined solves, or null: as above, or without
+// memory.
+uint32_t *solve_counters(ozII_ctx *h) {
+  SolveScratch *x = solve_scratch(h);
+  if (!x) return nullptr;
   if ((!h->bar && alloc_words(h) != hipSuccess) ||
-      hipMalloc((void **)&p, 16 * (size_t)ozl::TRSV_MAXGROUPS) != hipSuccess) {
+      (!x->sync && hipMalloc((void **)&x->sync, 16 * (size_t)ozl::TRSV_MAXGROUPS) != hipSuccess)) {
     (void)hipGetLastError();
+    x->sync = nullptr;
+  }
+  return x->sync;
+}
+
+// Room for the stream's reciprocals, or null: as above.
+uint64_t *solve_recip(ozII_ctx *h, size_t words) {
+  SolveScratch *x = solve_scratch(h);
+  if (!x) return nullptr;
+  if (words <= x->recip_words) return x->recip;
+  if (x->recip) {
+    if (hipStreamSynchronize(h->stream) != hipSuccess) return nullptr;
+    hipFree(x->recip);
+    x->recip_words = 0;
+  }
+  if (hipMalloc((void **)&x->recip, words * 8) != hipSuccess) {
+    (void)hipGetLastError();
+    x->recip = nullptr;
     return nullptr;
   }
-  SolveScratch &x = h->solves[h->nsolves++];
-  x.stream = h->stream;
-  x.sync = p;
-  return &x;
+  x->recip_words = words;
+  return x->recip;
 }
 
 ozII_status ensure_panel(ozII_ctx *h, int64_t n, int kb) {
@@ -980,8 +1006,7 @@ ozII_status limb_scratch(ozII_ctx *h) {
 // on the caller's planes, with the same results.
 uint64_t *limb_pack(ozII_ctx *h, size_t words) {
   if (words <= h->lpack_words) return h->lpack;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(h->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return nullptr;
+  if (capturing(h->stream)) return nullptr;
   if (h->lpack) {
     if (hipStreamSynchronize(h->stream) != hipSuccess) return nullptr;
     hipFree(h->lpack);
@@ -1202,7 +1227,10 @@ ozII_status ozII_destroy(ozII_handle h) {
   if (h->batch_ws) hipFree(h->batch_ws);
   if (h->lflag) hipFree(h->lflag);
   if (h->lpack) hipFree(h->lpack);
-  for (int i = 0; i < h->nsolves; ++i) hipFree(h->solves[i].sync);
+  for (int i = 0; i < h->nsolves; ++i) {
+    hipFree(h->solves[i].sync);
+    hipFree(h->solves[i].recip);
+  }
   if (h->bar) {
     hipFree(h->bar);
     hipFree(h->lines);
@@ -1482,8 +1510,7 @@ ozII_status ozII_getrs(ozII_handle h, int32_t nc, int64_t n, int64_t nrhs, const
     if (!h->bar && alloc_words(h) != hipSuccess) return fail(h, OZII_ENOMEM, "solve counters");
     sync = h->bar + 16;
   } else if (n > 256 && ozl::trsv_fits(n, nrhs)) {
-    const SolveScratch *sc = solve_scratch(h);
-    if (sc) sync = sc->sync;
+    sync = solve_counters(h);
   }
   if (sync) {
     if ((e = ozl::launch_trsv(nc, 1, LU, lda, B, ldb, nrhs, n, sync, h->err, s)) != hipSuccess)
@@ -1592,7 +1619,7 @@ ozII_status ozII_getrs_limbs(ozII_handle h, int32_t nlimb, int64_t n, int64_t nr
     return fail(h, OZII_EINVAL, "bad limb matrix descriptor or null pointer");
   ProfScope ps(h, OZ_STAGE_GETRS, (8.0 * nlimb + 5.0) * ((double)n * n + 2.0 * n * nrhs), 0);
   uint64_t *recip =
-      ozl::lgetrs_wants_recip(nlimb) ? limb_pack(h, (size_t)n * ozl::packed_words(nlimb)) : nullptr;
+      ozl::lgetrs_wants_recip(nlimb) ? solve_recip(h, (size_t)n * ozl::packed_words(nlimb)) : nullptr;
   const hipError_t e =
       ozl::launch_lgetrs(limb_mat(LU), nlimb, n, ipiv, limb_mat(B), nrhs, recip, h->stream);
   return e == hipSuccess ? OZII_OK : hip_fail(h, e, "limb solve");

@@ -1,12 +1,14 @@
 """Calls that need no ordering between streams, and calls under graph capture:
 solves that overlap on several streams of one handle, and solves captured on a
-handle that has none of their scratch yet.  Bit for bit against the oracle."""
+handle with and without their scratch.  Bit for bit against the oracle."""
 import numpy as np
 import pytest
 
 import oracle as O
+import oracle.limb_lu as OLU
 import workloads as W
 from tests.gpu_util import note, to_dev, to_host
+from tests.test_gpu_limb_lu import _dev, _host, _matrix, _same
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +72,63 @@ def test_getrs_captured(warm):
         assert np.array_equal(to_host(y), other[3])
         X.zero_()
     c.sync_check()
+
+
+def _limb_system(nl, n, nrhs):
+    F, ip, _ = OLU.getrf(_matrix(nl, n, 3 * n + nl), n, "native")
+    B = W.random_limbs(n, nrhs, nl, np.random.default_rng(n), exp_sigma=2.0, zero_frac=0.05)
+    return F, ip.copy(), B, OLU.getrs(F, ip, B)
+
+
+def test_getrs_limbs_overlapping_streams():
+    import torch
+    import paper_2609_29554_amd as Z
+    c = Z.Context(0)
+    sys_ = [_limb_system(nl, n, r) for nl, n, r in [(4, 60, 1), (8, 45, 3), (17, 30, 2), (4, 70, 2)]]
+    dev = [(_dev(F), torch.from_numpy(ip).cuda(), _dev(B)) for F, ip, B, _ in sys_]
+    out = [[tuple(torch.empty_like(t) for t in B) for _ in range(4)] for _, _, B in dev]
+    streams = [torch.cuda.Stream() for _ in sys_]
+    torch.cuda.synchronize()
+    note("getrs_limbs on four streams at once")
+    for rep in range(4):
+        for (F, ip, B), x, s in zip(dev, out, streams):
+            with torch.cuda.stream(s):
+                for d, t in zip(x[rep], B):
+                    d.copy_(t)
+                c.getrs_limbs(F, ip, x[rep])
+    torch.cuda.synchronize()
+    for (_, _, _, want), x in zip(sys_, out):
+        for y in x:
+            _same(_host(y), want)
+
+
+@pytest.mark.parametrize("warm", [False, True])
+def test_getrs_limbs_captured(warm):
+    """Captured on a fresh handle and after a call outside the capture; a larger
+    solve replaces the handle's scratch between the replays."""
+    import torch
+    import paper_2609_29554_amd as Z
+    note(f"captured getrs_limbs warm={warm}")
+    c = Z.Context(0)
+    F, ip, B, want = _limb_system(5, 40, 2)
+    dF, dip, dB = _dev(F), torch.from_numpy(ip).cuda(), _dev(B)
+    X = tuple(torch.empty_like(t) for t in dB)
+    if warm:
+        c.getrs_limbs(dF, dip, _dev(B))
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for d, t in zip(X, dB):
+            d.copy_(t)
+        c.getrs_limbs(dF, dip, X)
+    for nl, n in ((5, 55), (9, 60), (16, 64)):
+        o = _limb_system(nl, n, 1)
+        y = _dev(o[2])
+        c.getrs_limbs(_dev(o[0]), torch.from_numpy(o[1]).cuda(), y)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        _same(_host(X), want)
+        _same(_host(y), o[3])
+        for t in X:
+            t.zero_()
