@@ -353,6 +353,7 @@ struct SolveScratch {
   size_t recip_words = 0;
 };
 constexpr int MAX_SOLVES = 64;
+constexpr int MAX_KEPT = 8;
 
 struct ozII_ctx {
   int device = 0;
@@ -375,9 +376,13 @@ struct ozII_ctx {
   // scratch of the solves that callers may overlap, per stream
   SolveScratch solves[MAX_SOLVES];
   int nsolves = 0;
-  // packed limb numbers: the leaf of a panel
+  // packed limb numbers: the leaf of a panel; a buffer that a captured graph
+  // holds is kept beside the larger one that replaces it
   uint64_t *lpack = nullptr;
   size_t lpack_words = 0;
+  bool lpack_held = false;
+  uint64_t *lpack_kept[MAX_KEPT] = {};
+  int nkept = 0;
   // getrf look-ahead: a side stream (default priority) for the rest of each
   // Schur update while the next panel runs, and the fork / join events
   hipStream_t side = nullptr;
@@ -1002,17 +1007,26 @@ ozII_status limb_scratch(ozII_ctx *h) {
 }
 
 // Scratch for `words` words of packed limb numbers, or null when it cannot be
-// had (no memory, or a growth inside a stream capture): the callers then work
-// on the caller's planes, with the same results.
+// had (no memory, a growth inside a stream capture, or captured graphs holding
+// MAX_KEPT earlier buffers): the callers then work on the caller's planes, with
+// the same results.
 uint64_t *limb_pack(ozII_ctx *h, size_t words) {
-  if (words <= h->lpack_words) return h->lpack;
-  if (capturing(h->stream)) return nullptr;
-  if (h->lpack) {
+  const bool cap = capturing(h->stream);
+  if (words <= h->lpack_words) {
+    if (cap && !h->lpack_held && h->nkept == MAX_KEPT) return nullptr;
+    h->lpack_held = h->lpack_held || cap;
+    return h->lpack;
+  }
+  if (cap) return nullptr;
+  if (h->lpack_held) {
+    h->lpack_kept[h->nkept++] = h->lpack;
+  } else if (h->lpack) {
     if (hipStreamSynchronize(h->stream) != hipSuccess) return nullptr;
     hipFree(h->lpack);
-    h->lpack = nullptr;
-    h->lpack_words = 0;
   }
+  h->lpack = nullptr;
+  h->lpack_words = 0;
+  h->lpack_held = false;
   if (hipMalloc((void **)&h->lpack, words * 8) != hipSuccess) {
     (void)hipGetLastError();
     h->lpack = nullptr;
@@ -1227,6 +1241,7 @@ ozII_status ozII_destroy(ozII_handle h) {
   if (h->batch_ws) hipFree(h->batch_ws);
   if (h->lflag) hipFree(h->lflag);
   if (h->lpack) hipFree(h->lpack);
+  for (int i = 0; i < h->nkept; ++i) hipFree(h->lpack_kept[i]);
   for (int i = 0; i < h->nsolves; ++i) {
     hipFree(h->solves[i].sync);
     hipFree(h->solves[i].recip);

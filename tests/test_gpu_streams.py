@@ -132,3 +132,40 @@ def test_getrs_limbs_captured(warm):
         _same(_host(y), o[3])
         for t in X:
             t.zero_()
+
+
+@pytest.mark.parametrize("nl,n,b,leaf,warm", [
+    (4, 40, 40, 0, 40),    # captured with the packed leaf
+    (4, 40, 40, 0, 5),     # not allocated at that size: on the planes
+    (9, 24, 24, 7, 24), (9, 24, 24, 7, 3),
+    (2, 90, 80, 0, 90), (2, 90, 80, 0, 4),   # leaf wider than 64 columns
+])
+def test_getrf_limbs_captured(nl, n, b, leaf, warm):
+    """Larger factorisations replace the handle's scratch between the replays."""
+    import torch
+    import paper_2609_29554_amd as Z
+    note(f"captured getrf_limbs nl={nl} n={n} b={b} leaf={leaf} warm={warm}")
+    c = Z.Context(0)
+    c.getrf_limbs(_dev(_matrix(nl, warm, 1)), block=b, method=Z.METHOD_NAIVE, leaf=leaf)
+    A = _matrix(nl, n, 7)
+    want, ip, inf = OLU.getrf(A, b, "native", leaf=leaf)
+    dA = _dev(A)
+    X = tuple(torch.empty_like(t) for t in dA)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for d, t in zip(X, dA):
+            d.copy_(t)
+        ipiv, info = c.getrf_limbs(X, block=b, method=Z.METHOD_NAIVE, leaf=leaf)
+    for m in (n + 20, n + 40, n + 60):
+        O2 = _matrix(nl, m, m)
+        y = _dev(O2)
+        c.getrf_limbs(y, block=m, method=Z.METHOD_NAIVE, leaf=0)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        _same(_host(X), want)
+        assert np.array_equal(to_host(ipiv)[:n], ip) and int(info) == inf
+        _same(_host(y), OLU.getrf(O2, m, "native")[0])
+        for t in X:
+            t.zero_()
