@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256) void k_llaswp(LimbMat A, int nl, const int64_t
     src[t] = -1;
     if (q < 2 * kb) {
       const int32_t x = q < kb ? (int32_t)k0 + q : sp[q - kb];
-      if (q < kb || x >= k0 + kb) dst[t] = x;
+      if (q < kb || x < k0 || x >= k0 + kb) dst[t] = x;
       src[t] = x;
     }
   }

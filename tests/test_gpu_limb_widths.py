@@ -66,6 +66,31 @@ def test_solve(nl, n, nrhs, kind):
     _same(_host(dB), want)
 
 
+@pytest.mark.parametrize("nl,n", [(1, 270), (4, 600)])
+def test_solve_any_interchanges(nl, n):
+    """Interchanges with any row, those above the batch of 256 included."""
+    note(f"getrs_limbs interchanges nl={nl} n={n}")
+    rng = np.random.default_rng(n)
+    F = tuple(x.copy() for x in W.random_limbs(n, n, nl, rng, exp_sigma=0.0, zero_frac=0.0))
+    for x in F:                                    # the unit matrix
+        x[...] = 0
+    F[1][...] = OLU.EXP32_ZERO
+    d = np.arange(n)
+    F[0][nl - 1, d, d] = np.uint64(1 << 63)
+    F[1][d, d] = 1
+    ip = rng.integers(0, n, n)
+    ip[[n - 1, n - 3, 10]] = [3, 255, n - 2]
+    B = W.random_limbs(n, 2, nl, rng, exp_sigma=2.0, zero_frac=0.05)
+    order = np.arange(n)
+    for j in range(n):
+        order[[j, ip[j]]] = order[[ip[j], j]]
+    import torch
+    dB = _dev(B)
+    ctx().getrs_limbs(_dev(F), torch.from_numpy(ip).cuda(), dB)
+    ctx().sync_check()
+    _same(_host(dB), tuple(x[..., order] for x in B))
+
+
 @pytest.mark.parametrize("nl,n,b,leaf,method", [(5, 45, 45, 0, "native"), (17, 24, 24, 8, "native"),
                                                 (4, 50, 50, 33, "ozaki"), (33, 12, 6, 3, "ozaki"),
                                                 (2, 80, 16, 0, "native")])
