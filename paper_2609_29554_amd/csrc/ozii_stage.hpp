@@ -69,9 +69,14 @@ __device__ __forceinline__ int32_t exponent_at(const double *x) {
 }
 
 // Outputs per workgroup of the exponent kernels: few on small operands, so
-// that the chip is filled; 16 (whole 128-byte lines at any component count)
-// once 256 workgroups remain.
-inline int exponent_rb(int64_t nout) { return nout >= 4096 ? 16 : (nout >= 512 ? 4 : 1); }
+// that the chip is filled, more (whole 128-byte lines of a row-wise operand at
+// any component count) once 512 workgroups remain.  16 from 4096 outputs on,
+// 256 workgroups, left the CUs waiting for memory: both operands of DD 5 x 4096
+// x 4096 138 us, 8 of them 86, 4 56; of 4096 x 5 x 4096 133, 82, 87; of TD 4096
+// x 5 x 4096 149, 92, 138.
+inline int exponent_rb(int64_t nout) {
+  return nout >= 16384 ? 16 : (nout >= 4096 ? 8 : (nout >= 512 ? 4 : 1));
+}
 
 // Producer of the byte back-ends (INT8 residues, FP8 base-17 digits): the
 // caller's threads fill block (ob, kb) -- rows 16 ob .. 16 ob + 15, inner

@@ -33,6 +33,13 @@ def test_exponents_of_both_operands(nc, M, N, K):
     assert np.array_equal(to_host(st["eb"]), O.exponents(B, False))
 
 
+@pytest.mark.parametrize("nc,M,N,K", [(2, 5, 16390, 40), (3, 16385, 4, 33), (4, 4096, 5, 70),
+                                      (2, 2, 16383, 65)])
+def test_exponents_of_many_outputs(nc, M, N, K):
+    """Eight outputs each from 4096, sixteen from 16384 on."""
+    test_exponents_of_both_operands(nc, M, N, K)
+
+
 @pytest.mark.parametrize("nl,M,N,K", [(1, 4100, 3, 200), (2, 5, 600, 700), (1, 513, 2, 3)])
 def test_limb_product_rows(nl, M, N, K):
     """Sampled rows of A against all of B (row exponents are per row)."""
