@@ -16,6 +16,7 @@
 #include <algorithm>
 
 #include "../../include/ozii.h"
+#include "batch_rules.hpp"
 #include "expansion.hpp"
 #include "ozii_elem.hpp"
 #include "ozii_stage.hpp"
@@ -789,8 +790,7 @@ __device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item,
   __syncthreads();
   for (int64_t k0 = 0; k0 < n; k0 += b) {
     const int64_t k1 = k0 + b < n ? k0 + b : n;
-    const float rem = (float)(n - k0);  // work left, for the helpers' choice
-    const uint32_t left = (uint32_t)((float)(NC * NC) * rem * rem * rem * 0.25f) + 1u;
+    const uint32_t left = ozb::work_left(NC, n - k0);
     // deferring steps shortens the owner's work only where others take it:
     // 16 systems of order 100 to 400 17.6 -> 13.0 ms; without helpers it is 2 to
     // 3 % slower (700 of order 64 to 200, 12.25 -> 12.5 ms), and 256 systems

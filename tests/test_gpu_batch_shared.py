@@ -99,3 +99,8 @@ def test_several_rows_per_thread(nc, n, b):
     assert torch.equal(ip, wip) and int(info) == int(winfo) == 0
     assert torch.equal(LU, wLU)
     assert torch.equal(X, wX)
+
+
+def test_largest_order_shared():
+    """The largest accepted QD system, its first block shared too."""
+    test_several_rows_per_thread(4, 1024, 64)
