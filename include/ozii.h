@@ -371,12 +371,16 @@ ozII_status ozII_batch_prepare(ozII_handle h, int32_t count, const ozII_batch_it
 
 /* ozII_batch_prepare with options.  o == NULL or o->method ==
  * OZII_METHOD_NAIVE: as ozII_batch_prepare.  o->method == OZII_METHOD_OZAKI:
- * every item is factored by one workgroup with the blocked LU of ozII_getrf
- * (panel width b = o->block, default 32, at most 256) whose Schur updates run
- * the Ozaki-II product of Sec. 3.1-3.3 inside the workgroup on the INT8
- * back-end (plans at K = b, honouring o->nslice / extra_groups / guard_ex):
+ * every item is factored by a workgroup that owns it with the blocked LU of
+ * ozII_getrf (panel width b = o->block, default 32, at most 256) whose Schur
+ * updates run the Ozaki-II product of Sec. 3.1-3.3 inside the workgroup on the
+ * INT8 back-end (plans at K = b, honouring o->nslice / extra_groups / guard_ex):
  * per element the operations of ozII_getrf with the same o, so factors,
- * pivots and info agree with it bit for bit; then the solve as above.  The
+ * pivots and info agree with it bit for bit; then the solve as above.
+ * Workgroups without an item help the owners, so the launch has as many as the
+ * items offer tasks at once, at most one per CU, and they stay until the last
+ * item is done: items of order up to b + 64 with small panels take a CU each,
+ * one of order 512 at b = 64 takes 56, large batches the whole GPU.  The
  * handle allocates one scratch slot per workgroup here (exponents, residue
  * planes of L21 and U12, t-planes: about ng nmod (n - b)^2 bytes for the
  * largest item), so ozII_batch_run still allocates nothing.

@@ -11,6 +11,7 @@
 // the oracle) bit for bit.  The launch allocates nothing and clears its queue
 // with a kernel, so it can be captured in a hipGraph.
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <algorithm>
@@ -28,7 +29,7 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int BT = 1024;  // threads per workgroup (4 wavefronts per SIMD)
-constexpr int BTZ = 512;  // the same for the Ozaki-II update
+constexpr int BTZ = ozb::NT;  // the same for the Ozaki-II update
 constexpr int BZ_PRE = 10; // t-byte chunks requested at once by its CRT (nmod <= 40)
 
 // The elements idx = t, t + NT, t + 2 NT, ... of a rectangle with mr > 0 rows
@@ -641,7 +642,9 @@ struct BatchSlot {  // a line of its own for each owner
   int32_t pad[25];
 };
 struct Board {
-  int32_t next, idle, finished, owners;  // items taken, helpers, items done, scratch slots taken
+  // items taken, helpers (and CUs without a workgroup), items done, scratch
+  // slots taken
+  int32_t next, idle, finished, owners;
   int32_t pad[60];
   // followed by nslot job words (rounded up to 64) and nslot slots
   __device__ uint64_t *jobs() { return (uint64_t *)(this + 1); }
@@ -672,7 +675,9 @@ __device__ __forceinline__ void wg_acquire() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
-constexpr int UCH = 32, ACH = 64;  // columns of U12, rows of L21 of a task
+using ozb::ACH;
+using ozb::SB;
+using ozb::UCH;
 
 template <int NC, int NWM, int NT>
 __device__ __forceinline__ int tasks_of(const OzUpdate<NC, NWM, NT> &u, int phase) {
@@ -696,8 +701,6 @@ __device__ __forceinline__ void run_task(const OzUpdate<NC, NWM, NT> &u, int pha
     u.tiles(tm, tm + 1, tn, tn + 1, stage);
   }
 }
-
-constexpr int SB = 8;  // columns of a panel's sub-block when steps are deferred
 
 // Task t of the deferred steps j0 .. j1-1 on the panel's columns j1 .. k1-1,
 // rows from j1 on: NT elements, one per thread, kept in registers through all
@@ -768,7 +771,8 @@ __device__ __forceinline__ void offer(bool share, int total, uint32_t prio, uint
 }
 
 template <int NC, int NWM, int NT>
-__device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item, int count, double (*rkey)[4],
+__device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item, int count, int cus,
+                            double (*rkey)[4],
                             int64_t *ridx, int *s_info, const DevPlan *pl, uint8_t *ws, int b,
                             uint32_t *stage, double (*xs)[4], int64_t *pv, Board *bd, uint64_t *job, BatchSlot *sl, int *s_task) {
   const int tid = threadIdx.x;
@@ -794,12 +798,9 @@ __device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item,
     // deferring steps shortens the owner's work only where others take it:
     // 16 systems of order 100 to 400 17.6 -> 13.0 ms; without helpers it is 2 to
     // 3 % slower (700 of order 64 to 200, 12.25 -> 12.5 ms), and 256 systems
-    // take 33.0 ms with the line at an eighth, a quarter or half of the
-    // workgroups idle, 33.3 at three quarters.  A small panel's steps are not
-    // worth a task: with the line at 0 / 6 / 12 / 24 NT elements, 71 of order 36
-    // to 58 take 1.46 / 1.31 / 1.31 / 1.31 ms, 16 of order 100 to 400 12.8 / 12.6 /
-    // 12.7 / 13.4, 100 of order 150 to 300 (b = 32) 11.9 / 11.7 / 11.4 / 11.7
-    const bool many = (n - k0) * (k1 - k0) >= 12 * NT && helpers() * 2 > (int)gridDim.x;
+    // take 33.0 ms with the line at an eighth, a quarter or half of the CUs
+    // idle, 33.3 at three quarters
+    const bool many = ozb::worth_deferring(n - k0, k1 - k0) && helpers() * 2 > cus;
     const int64_t sb = many ? SB : b;
     for (int64_t j0 = k0; j0 < k1; j0 += sb) {
       // sub-block: its own columns see each step at once, the panel's other
@@ -887,7 +888,7 @@ __device__ __forceinline__ void help(const ozII_batch_item &it, BatchSlot *sl, c
 // consumer's per-thread staging shares the LDS with the pivot search (never
 // live at the same time).
 __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *items, int count,
-                                                    Board *bd, int nslot, uint64_t *times,
+                                                    Board *bd, int nslot, int cus, uint64_t *times,
                                                     const DevPlan *pl2, const DevPlan *pl3,
                                                     const DevPlan *pl4, uint8_t *ws, int64_t slot,
                                                     int b) {
@@ -917,7 +918,7 @@ __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *item
     uint8_t *myws = ws + (int64_t)ms * slot;
     if (times && threadIdx.x == 0) times[2 * it.reserved] = __builtin_amdgcn_s_memrealtime();
 #define OZ_LU(NC_, NWM_, PL_)                                                                        \
-  lu_solve_oz<NC_, NWM_, BTZ>(it, q, count, rkey, ridx, &s_info, PL_, myws, b, lds, xs, pv, bd,          \
+  lu_solve_oz<NC_, NWM_, BTZ>(it, q, count, cus, rkey, ridx, &s_info, PL_, myws, b, lds, xs, pv, bd,          \
                               bd->jobs() + ms,                                                      \
                               slots + ms, &s_task)
     if (it.nc == 2) OZ_LU(2, 6, pl2);
@@ -1018,8 +1019,8 @@ __global__ __launch_bounds__(BT) void k_batch_lu(const ozII_batch_item *items, i
   }
 }
 
-__global__ void k_batch_clear(int *words, int count) {
-  for (int i = threadIdx.x; i < count; i += blockDim.x) words[i] = 0;
+__global__ void k_batch_clear(int *words, int count, int idle) {
+  for (int i = threadIdx.x; i < count; i += blockDim.x) words[i] = i == 1 ? idle : 0;
 }
 
 }  // namespace
@@ -1028,7 +1029,7 @@ namespace ozl {
 hipError_t launch_batch(const ozII_batch_item *items, int count, int *queue, uint64_t *times,
                         int grid, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_batch_clear, dim3(1), dim3(64), 0, s, queue, 1);
+  hipLaunchKernelGGL(k_batch_clear, dim3(1), dim3(64), 0, s, queue, 1, 0);
   hipLaunchKernelGGL(k_batch_lu, dim3((unsigned)grid), dim3(BT), 0, s, items, count, queue, times);
   return hipGetLastError();
 }
@@ -1037,14 +1038,16 @@ size_t batch_board_bytes(int nslot) {
 }
 
 hipError_t launch_batch_oz(const ozII_batch_item *items, int count, void *board, int nslot,
-                          uint64_t *times, int grid, const DevPlan *pl2, const DevPlan *pl3,
-                          const DevPlan *pl4, uint8_t *ws, int64_t slot, int b, hipStream_t s) {
+                          uint64_t *times, int grid, int cus, const DevPlan *pl2,
+                          const DevPlan *pl3, const DevPlan *pl4, uint8_t *ws, int64_t slot, int b,
+                          hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  if (b < 1 || b > 256 || nslot < std::min(count, grid)) return hipErrorInvalidValue;
+  if (b < 1 || b > 256 || nslot < std::min(count, grid) || grid > cus) return hipErrorInvalidValue;
+  static_assert(offsetof(Board, idle) == 4, "the word that k_batch_clear sets");
   hipLaunchKernelGGL(k_batch_clear, dim3(1), dim3(256), 0, s, (int *)board,
-                     (int)(sizeof(Board) / 4) + (nslot + 63) / 64 * 128);
+                     (int)(sizeof(Board) / 4) + (nslot + 63) / 64 * 128, cus - grid);
   hipLaunchKernelGGL(k_batch_lu_oz, dim3((unsigned)grid), dim3(BTZ), 0, s, items, count,
-                     (Board *)board, nslot, times, pl2, pl3, pl4, ws, slot, b);
+                     (Board *)board, nslot, cus, times, pl2, pl3, pl4, ws, slot, b);
   return hipGetLastError();
 }
 }  // namespace ozl

@@ -14,6 +14,7 @@
 
 #include "../../include/ozii.h"
 #include "ozii_elem.hpp"
+#include "batch_rules.hpp"
 #include "ozii_kernels.hpp"
 
 namespace {
@@ -389,7 +390,7 @@ struct ozII_ctx {
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   // batched LU: the uploaded item table (processing order) and its queue
   ozII_batch_item *batch = nullptr;
-  int batch_cap = 0, batch_count = 0, batch_grid = 1, batch_cus = 1;
+  int batch_cap = 0, batch_count = 0, batch_grid = 1, batch_wgs = 1, batch_cus = 1;
   int *batch_queue = nullptr;  // (Ozaki-II update: the board of shared work)
   // batched LU with the Ozaki-II update: panel width (0: native unblocked
   // path), plans per nc = 2, 3, 4 and the per-workgroup scratch
@@ -1722,13 +1723,16 @@ ozII_status ozII_batch_prepare_ex(ozII_handle h, int32_t count, const ozII_batch
                           h->stream)) != hipSuccess)
     return hip_fail(h, e, "batch upload");
   if ((e = hipStreamSynchronize(h->stream)) != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
-  // persistent grid: one workgroup per CU; at most one per item on the native
-  // update, where none could help another
+  // persistent grid: at most one workgroup per CU and per item; with the
+  // Ozaki-II update, where idle workgroups help, per task that the items offer
+  // at once, which leaves the other CUs to the caller's other streams
   int dev = 0, ncu = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess ||
       (e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
     return hip_fail(h, e, "device query");
   const int grid = std::max(1, std::min(count, ncu));
+  int64_t tasks = 0;
+  for (int i = 0; oz && i < count && tasks < ncu; ++i) tasks += ozb::most_tasks(v[i].n, b);
   if (!h->batch_queue &&
       (e = hipMalloc((void **)&h->batch_queue, ozl::batch_board_bytes(ncu))) != hipSuccess)
     return fail(h, OZII_ENOMEM, "batch queue allocation failed");
@@ -1742,6 +1746,7 @@ ozII_status ozII_batch_prepare_ex(ozII_handle h, int32_t count, const ozII_batch
   }
   h->batch_count = count;
   h->batch_grid = grid;
+  h->batch_wgs = (int)std::max<int64_t>(grid, std::min<int64_t>(tasks, ncu));
   h->batch_cus = ncu;
   h->batch_b = b;
   h->batch_slot = slot;
@@ -1755,7 +1760,7 @@ ozII_status ozII_batch_run(ozII_handle h, uint64_t *times) {
   hipError_t e =
       h->batch_b > 0
           ? ozl::launch_batch_oz(h->batch, h->batch_count, h->batch_queue, h->batch_grid, times,
-                                 h->batch_cus, h->batch_pl[0], h->batch_pl[1], h->batch_pl[2],
+                                 h->batch_wgs, h->batch_cus, h->batch_pl[0], h->batch_pl[1], h->batch_pl[2],
                                  h->batch_ws, h->batch_slot, h->batch_b, h->stream)
           : ozl::launch_batch(h->batch, h->batch_count, h->batch_queue, times, h->batch_grid,
                               h->stream);

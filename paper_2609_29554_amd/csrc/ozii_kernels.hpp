@@ -183,10 +183,10 @@ hipError_t launch_batch(const ozII_batch_item *items, int count, int *queue, uin
 // width b <= 256); plans at K = b for nc = 2, 3, 4 (null for absent formats),
 // scratch of `slot` bytes per workgroup
 // board: batch_board_bytes(nslot) bytes of device memory; ws: nslot slots of
-// scratch, nslot >= min(count, grid)
+// scratch, nslot >= min(count, grid); grid: workgroups, at most one per CU (cus)
 size_t batch_board_bytes(int nslot);
 hipError_t launch_batch_oz(const ozII_batch_item *items, int count, void *board, int nslot,
-                           uint64_t *times, int grid, const ozk::DevPlan *pl2,
+                           uint64_t *times, int grid, int cus, const ozk::DevPlan *pl2,
                            const ozk::DevPlan *pl3, const ozk::DevPlan *pl4, uint8_t *ws,
                            int64_t slot, int b, hipStream_t s);
 

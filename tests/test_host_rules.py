@@ -28,3 +28,22 @@ def test_work_left_grows_with_the_order(tmp_path, nc):
     # an order 1024 system ranks above every smaller order's next block
     assert v[1023] > v[1007] > v[511] > v[63]
     assert v[1023] == nc * nc * 2 ** 24 + 1
+
+
+def test_batch_tasks(tmp_path):
+    """Workgroups that can work on one system: its owner alone where nothing is
+    shared, and for an order 512 system of width 64 the 504 x 56 deferred
+    elements in tasks of 512."""
+    sizes = [(1, 32), (64, 64), (100, 32), (128, 64), (129, 64), (512, 64), (1024, 64), (1024, 256),
+             (1024, 1), (90, 256)]
+    rows = _run(tmp_path, "batch_rules.hpp",
+                " ".join(f'std::printf("%ld\\n", (long)ozb::most_tasks({n}, {b}));'
+                         for n, b in sizes))
+    got = dict(zip(sizes, (r[0] for r in rows)))
+    assert got[(1, 32)] == got[(64, 64)] == 1
+    assert got[(100, 32)] == 6          # 68 trailing rows: 4 + 2 chunks, 2 x 2 tiles
+    assert got[(128, 64)] == 14         # 120 x 56 deferred elements
+    assert got[(512, 64)] == 56 and got[(1024, 64)] == 15 * 15
+    assert got[(1024, 1)] == 16 * 16 and got[(90, 256)] == (82 * 82 + 511) // 512
+    # four systems of order 64, or one of 512, leave most CUs alone
+    assert 4 * got[(64, 64)] == 4 and got[(512, 64)] < 64
