@@ -237,8 +237,8 @@ ozII_status ozII_gemm_limbs_stages(ozII_handle h, int32_t mode, int32_t nlimb, i
  * a zero pivot skips its column's division and update.
  * Beside the product's workspace the handle keeps a packed copy of one panel
  * leaf, 8 n w (nlimb + 1) bytes for leaves of w columns (w = b without
- * recursion; 273 MB at n = 2048, 64 limbs, b = 256), allocated on first use.
- * Without it (no memory, or a captured call that would have to allocate it)
+ * recursion; 273 MB at n = 2048, 64 limbs, b = 256), allocated on first use
+ * and given back when another allocation of the handle would fail.  Without it (no memory, or a captured call that would have to allocate it)
  * the panel works on A's planes, slower and with the same results.  A buffer
  * that a captured call used stays allocated until ozII_destroy, also when a
  * larger factorisation takes a larger one; captured calls hold at most 9.

@@ -454,6 +454,38 @@ struct ProfScope {
   }
 };
 
+// Whether stream s is being captured (or cannot be asked, which happens to the
+// default stream while another one is captured).
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// Device memory for the handle.  Where there is none left, the packed panel
+// leaf that a limb LU left behind, which the next one can do without, is given
+// back first.
+hipError_t dev_alloc(ozII_ctx *h, void **p, size_t bytes) {
+  *p = nullptr;
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess) return e;
+  *p = nullptr;
+  (void)hipGetLastError();
+  if (!h->lpack || h->lpack_held || capturing(h->stream)) return e;
+  const hipError_t es = hipStreamSynchronize(h->stream);
+  if (es != hipSuccess) return es;
+  hipFree(h->lpack);
+  h->lpack = nullptr;
+  h->lpack_words = 0;
+  e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    *p = nullptr;
+    (void)hipGetLastError();
+  }
+  return e;
+}
+
 // limbs: plans for the limb format, whose fixed point and group sums live in
 // memory rather than registers; only the slice window (w <= 300) and the
 // byte CRT (at most 24 16-bit digits) bound them.
@@ -473,7 +505,7 @@ ozII_status get_plan(ozII_ctx *h, int p, int64_t K, const ozII_opts *o, const Ho
     DevPlan host_dp;
     build_devplan(pl, host_dp);
     DevPlan *d = nullptr;
-    hipError_t e = hipMalloc((void **)&d, sizeof(DevPlan));
+    hipError_t e = dev_alloc(h, (void **)&d, sizeof(DevPlan));
     if (e != hipSuccess) return hip_fail(h, e, "hipMalloc(plan)");
     e = hipMemcpy(d, &host_dp, sizeof(DevPlan), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(h, e, "hipMemcpy(plan)");
@@ -608,11 +640,8 @@ ozII_status ensure_ws(ozII_ctx *h, size_t bytes) {
     h->ws = nullptr;
     h->ws_bytes = 0;
   }
-  hipError_t e = hipMalloc((void **)&h->ws, bytes);
-  if (e != hipSuccess) {
-    h->ws = nullptr;
+  if (dev_alloc(h, (void **)&h->ws, bytes) != hipSuccess)
     return fail(h, OZII_ENOMEM, "workspace allocation failed");
-  }
   h->ws_bytes = bytes;
   return OZII_OK;
 }
@@ -622,7 +651,7 @@ ozII_status ensure_ws(ozII_ctx *h, size_t bytes) {
 hipError_t alloc_words(ozII_ctx *h) {
   constexpr size_t bytes = 64 + 16;
   uint32_t *p = nullptr;
-  hipError_t e = hipMalloc((void **)&p, bytes);
+  hipError_t e = dev_alloc(h, (void **)&p, bytes);
   if (e == hipSuccess) e = hipMemset(p, 0, bytes);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) {
@@ -634,15 +663,6 @@ hipError_t alloc_words(ozII_ctx *h) {
   h->nmoved = (int *)(p + 8);
   h->epoch = p + 9;
   return e;
-}
-
-// Whether stream s is being captured (or cannot be asked, which happens to the
-// default stream while another one is captured).
-bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();
-  return true;
 }
 
 // The solve scratch of the handle's stream, or null: during capture, or on a
@@ -690,12 +710,14 @@ uint64_t *solve_recip(ozII_ctx *h, size_t words) {
 
 ozII_status ensure_panel(ozII_ctx *h, int64_t n, int kb) {
   if (n <= h->panel_n && kb <= h->panel_kb) return OZII_OK;
-  if (h->crow) {
+  if (h->crow || h->perm || h->moved) {
     hipError_t e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "hipStreamSynchronize");
     hipFree(h->crow);
     hipFree(h->perm);
     hipFree(h->moved);
+    h->crow = nullptr;
+    h->perm = h->moved = nullptr;
   }
   const int64_t nn = std::max<int64_t>(n, h->panel_n);
   const int kk = std::max(kb, h->panel_kb);
@@ -703,16 +725,20 @@ ozII_status ensure_panel(ozII_ctx *h, int64_t n, int kb) {
   hipError_t e = hipSuccess;
   if (!h->bar) e = alloc_words(h);
   if (e == hipSuccess && !h->lines) {
-    e = hipMalloc((void **)&h->lines, 2 * 128 * G);
+    e = dev_alloc(h, (void **)&h->lines, 2 * 128 * G);
     if (e == hipSuccess) e = hipMemset(h->lines, 0, 2 * 128 * G);
   }
   const size_t crow_bytes = 2 * G * ozl::panel_row_bytes(kk);
-  if (e == hipSuccess) e = hipMalloc((void **)&h->crow, crow_bytes);
+  if (e == hipSuccess) e = dev_alloc(h, (void **)&h->crow, crow_bytes);
   if (e == hipSuccess) e = hipMemset(h->crow, 0, crow_bytes);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-  if (e == hipSuccess) e = hipMalloc((void **)&h->perm, sizeof(int) * nn);
-  if (e == hipSuccess) e = hipMalloc((void **)&h->moved, sizeof(int) * nn);
-  if (e != hipSuccess) return fail(h, OZII_ENOMEM, "panel scratch allocation failed");
+  if (e == hipSuccess) e = dev_alloc(h, (void **)&h->perm, sizeof(int) * nn);
+  if (e == hipSuccess) e = dev_alloc(h, (void **)&h->moved, sizeof(int) * nn);
+  if (e != hipSuccess) {
+    // nothing is left of the smaller scratch either
+    h->panel_n = h->panel_kb = 0;
+    return fail(h, OZII_ENOMEM, "panel scratch allocation failed");
+  }
   h->panel_n = nn;
   h->panel_kb = kk;
   return OZII_OK;
@@ -1002,7 +1028,7 @@ ozII_status gemm_limbs_impl(ozII_ctx *h, int mode, int nlimb, int64_t M, int64_t
 // Zero-pivot word of the limb LU (allocated once).
 ozII_status limb_scratch(ozII_ctx *h) {
   if (h->lflag) return OZII_OK;
-  hipError_t e = hipMalloc((void **)&h->lflag, 256);
+  hipError_t e = dev_alloc(h, (void **)&h->lflag, 256);
   if (e != hipSuccess) return hip_fail(h, e, "hipMalloc(limb pivot scratch)");
   return OZII_OK;
 }
@@ -1082,7 +1108,7 @@ struct LimbLU {
   const ozII_opts *o;
   int64_t *ipiv;
   int32_t *info;
-  uint64_t *pack = nullptr;  // a packed panel leaf, or null: on the planes
+  size_t pack_words = 0;  // of a packed panel leaf, or 0: on the planes
 
   double el() const { return 8.0 * nl + 5.0; }
 
@@ -1132,6 +1158,8 @@ struct LimbLU {
       // panel once per leaf (the same rows end up in the same places)
       ProfScope ps(h, OZ_STAGE_PANEL, el() * (double)(n - c0) * w, 0);
       hipError_t e = hipSuccess;
+      // an update's workspace may have taken the leaf's memory
+      uint64_t *pack = pack_words > 0 && pack_words <= h->lpack_words ? h->lpack : nullptr;
       if (pack) {
         const int64_t rows = n - c0;
         const ozl::LimbMat P = ozl::packed_mat(pack, nl, rows);
@@ -1606,7 +1634,8 @@ ozII_status ozII_getrf_limbs(ozII_handle h, int32_t nlimb, int64_t n, ozII_limbs
     }
   }
   const int64_t leafw = std::min<int64_t>(n, L.leaf > 0 ? std::min<int64_t>(L.leaf, b) : b);
-  L.pack = limb_pack(h, (size_t)n * leafw * ozl::packed_words(nlimb));
+  const size_t pack_words = (size_t)n * leafw * ozl::packed_words(nlimb);
+  L.pack_words = limb_pack(h, pack_words) ? pack_words : 0;
   hipError_t e;
   if ((e = ozl::launch_lfill_i32(info, 0, 1, h->stream)) != hipSuccess) return hip_fail(h, e, "info");
   const double el = 8.0 * nlimb + 5.0;
@@ -1714,7 +1743,7 @@ ozII_status ozII_batch_prepare_ex(ozII_handle h, int32_t count, const ozII_batch
     if (h->batch) hipFree(h->batch);
     h->batch = nullptr;
     h->batch_cap = 0;
-    if ((e = hipMalloc((void **)&h->batch, sizeof(ozII_batch_item) * count)) != hipSuccess)
+    if ((e = dev_alloc(h, (void **)&h->batch, sizeof(ozII_batch_item) * count)) != hipSuccess)
       return fail(h, OZII_ENOMEM, "batch table allocation failed");
     h->batch_cap = count;
   }
@@ -1734,13 +1763,13 @@ ozII_status ozII_batch_prepare_ex(ozII_handle h, int32_t count, const ozII_batch
   int64_t tasks = 0;
   for (int i = 0; oz && i < count && tasks < ncu; ++i) tasks += ozb::most_tasks(v[i].n, b);
   if (!h->batch_queue &&
-      (e = hipMalloc((void **)&h->batch_queue, ozl::batch_board_bytes(ncu))) != hipSuccess)
+      (e = dev_alloc(h, (void **)&h->batch_queue, ozl::batch_board_bytes(ncu))) != hipSuccess)
     return fail(h, OZII_ENOMEM, "batch queue allocation failed");
   if (oz && (size_t)(slot * grid) > h->batch_ws_bytes) {
     if (h->batch_ws) hipFree(h->batch_ws);
     h->batch_ws = nullptr;
     h->batch_ws_bytes = 0;
-    if ((e = hipMalloc((void **)&h->batch_ws, (size_t)(slot * grid))) != hipSuccess)
+    if ((e = dev_alloc(h, (void **)&h->batch_ws, (size_t)(slot * grid))) != hipSuccess)
       return fail(h, OZII_ENOMEM, "batch scratch allocation failed");
     h->batch_ws_bytes = (size_t)(slot * grid);
   }
