@@ -448,7 +448,8 @@ ozII_status ozII_tune_limbs(ozII_handle h, int32_t nlimb, int64_t n, const char 
 ozII_status ozII_stream_of(ozII_handle h, void **stream);
 
 /* Wait for the handle's stream and report a device-side error flag raised by
- * a kernel (a grid barrier that did not complete). */
+ * a kernel: a wait for other workgroups that took too long (the exchange of a
+ * panel and the pipelined solves about a second, shared work of a batch ten). */
 ozII_status ozII_sync_check(ozII_handle h);
 
 /* Per-stage timing.  When on, every kernel launch of the library is

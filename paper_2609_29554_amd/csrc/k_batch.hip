@@ -30,7 +30,6 @@ namespace {
 
 constexpr int BT = 1024;  // threads per workgroup (4 wavefronts per SIMD)
 constexpr int BTZ = ozb::NT;  // the same for the Ozaki-II update
-constexpr int BZ_PRE = 10; // t-byte chunks requested at once by its CRT (nmod <= 40)
 
 // The elements idx = t, t + NT, t + 2 NT, ... of a rectangle with mr > 0 rows
 // taken column by column, (i, c) = (idx % mr, idx / mr), with one division
@@ -625,7 +624,9 @@ struct OzUpdate {
 // word (priority << 32 | total << 16 | next) and runs to its end without
 // waiting for anything, an owner waits only for tasks that were taken, and a
 // helper leaves when every item is finished: no workgroup waits for one that
-// does not run.
+// does not run.  Both waits are bounded all the same: an owner whose tasks
+// do not end raises the sticky error flag and leaves, a helper that sees
+// nothing happen for as long just leaves.
 // The owner's data reach the helpers, and the helpers' results the owner,
 // through an agent-scope release by every wavefront before the increment (or
 // the offer) and an acquire by every wavefront after it: the XCDs' L2s are not
@@ -738,15 +739,20 @@ __device__ __forceinline__ void deferred_task(double *A, int64_t n, int j0, int 
   ozx::store<NC>(dst, a);
 }
 
+// Ticks of the 100 MHz counter that an owner or helper waits: 10 s, a hundred
+// times what the longest system takes alone.
+constexpr uint64_t WAIT_TICKS = 1000000000ull;
+
 // By the owner: the tasks 0 .. total-1, shared when there is a helper (share),
 // else one after the other.  put() writes what the helpers need to the slot.
+// False (for every thread) when a task that was taken did not end in time.
 template <class P, class F>
-__device__ __forceinline__ void offer(bool share, int total, uint32_t prio, uint64_t *job, BatchSlot *sl, int *s_task,
-                                      P put, F run) {
+__device__ __forceinline__ bool offer(bool share, int total, uint32_t prio, uint64_t *job,
+                                      BatchSlot *sl, int *s_task, int *err, P put, F run) {
   if (!share) {
     for (int t = 0; t < total; ++t) run(t);
     __syncthreads();
-    return;
+    return true;
   }
   const int tid = threadIdx.x;
   if (tid == 0) {
@@ -765,16 +771,29 @@ __device__ __forceinline__ void offer(bool share, int total, uint32_t prio, uint
     run(t);
     __syncthreads();
   }
-  if (tid == 0)
-    while (ld_agent(&sl->done) + mine < total) __builtin_amdgcn_s_sleep(4);
+  if (tid == 0) {
+    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+    *s_task = 0;
+    while (ld_agent(&sl->done) + mine < total) {
+      if (__builtin_amdgcn_s_memrealtime() - t0 > WAIT_TICKS) {
+        st_agent(err, 4);
+        *s_task = -1;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(4);
+    }
+  }
   wg_acquire();
+  return *s_task == 0;
 }
 
+// False when a wait of offer() ran out; the item is then unfinished.
 template <int NC, int NWM, int NT>
-__device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item, int count, int cus,
+__device__ __forceinline__ bool lu_solve_oz(const ozII_batch_item &it, int item, int count, int cus,
                             double (*rkey)[4],
                             int64_t *ridx, int *s_info, const DevPlan *pl, uint8_t *ws, int b,
-                            uint32_t *stage, double (*xs)[4], int64_t *pv, Board *bd, uint64_t *job, BatchSlot *sl, int *s_task) {
+                            uint32_t *stage, double (*xs)[4], int64_t *pv, Board *bd, uint64_t *job,
+                            BatchSlot *sl, int *s_task, int *err) {
   const int tid = threadIdx.x;
   const int64_t n = it.n;
   double *A = it.A;
@@ -832,16 +851,18 @@ __device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item,
         __syncthreads();
       }
       const int total = (int)(((n - j1) * (k1 - j1) + NT - 1) / NT);
-      offer(total > 1, total, left, job, sl, s_task,
-            [&]() {
-              st_agent(&sl->item, item);
-              st_agent(&sl->k0, (int32_t)k0);
-              st_agent(&sl->j0, (int32_t)j0);
-              st_agent(&sl->j1, (int32_t)j1);
-              st_agent(&sl->zeros, (int32_t)zeros);
-              st_agent(&sl->phase, 2);
-            },
-            [&](int t) { deferred_task<NC, NT>(A, n, (int)j0, (int)j1, (int)k1, zeros, t); });
+      const bool ok = offer(
+          total > 1, total, left, job, sl, s_task, err,
+          [&]() {
+            st_agent(&sl->item, item);
+            st_agent(&sl->k0, (int32_t)k0);
+            st_agent(&sl->j0, (int32_t)j0);
+            st_agent(&sl->j1, (int32_t)j1);
+            st_agent(&sl->zeros, (int32_t)zeros);
+            st_agent(&sl->phase, 2);
+          },
+          [&](int t) { deferred_task<NC, NT>(A, n, (int)j0, (int)j1, (int)k1, zeros, t); });
+      if (!ok) return false;
     }
     if (k1 >= n) break;
     const OzUpdate<NC, NWM, NT> u(A, n, k0, k1, pl, ws);
@@ -858,17 +879,21 @@ __device__ __forceinline__ void lu_solve_oz(const ozII_batch_item &it, int item,
       u.tiles(0, u.Mp / 64, 0, u.Mp / 64, stage);
       continue;
     }
-    for (int phase = 0; phase < 2; ++phase)
-      offer(true, tasks_of(u, phase), left, job, sl, s_task,
-            [&]() {
-              st_agent(&sl->item, item);
-              st_agent(&sl->k0, (int32_t)k0);
-              st_agent(&sl->phase, phase);
-            },
-            [&](int t) { run_task(u, phase, t, stage); });
+    for (int phase = 0; phase < 2; ++phase) {
+      const bool ok = offer(
+          true, tasks_of(u, phase), left, job, sl, s_task, err,
+          [&]() {
+            st_agent(&sl->item, item);
+            st_agent(&sl->k0, (int32_t)k0);
+            st_agent(&sl->phase, phase);
+          },
+          [&](int t) { run_task(u, phase, t, stage); });
+      if (!ok) return false;
+    }
   }
   if (tid == 0) *it.info = *s_info;
   solve_one<NC, NT>(it, xs, pv);
+  return true;
 }
 
 template <int NC, int NWM, int NT>
@@ -891,7 +916,7 @@ __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *item
                                                     Board *bd, int nslot, int cus, uint64_t *times,
                                                     const DevPlan *pl2, const DevPlan *pl3,
                                                     const DevPlan *pl4, uint8_t *ws, int64_t slot,
-                                                    int b) {
+                                                    int b, int *err) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[BTZ * CST];
   static_assert(BTZ * CST * 4 >= BTZ * (32 + 8), "pivot search arrays fit the staging");
   double(*rkey)[4] = (double(*)[4])lds;
@@ -917,14 +942,15 @@ __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *item
     const ozII_batch_item it = items[q];
     uint8_t *myws = ws + (int64_t)ms * slot;
     if (times && threadIdx.x == 0) times[2 * it.reserved] = __builtin_amdgcn_s_memrealtime();
-#define OZ_LU(NC_, NWM_, PL_)                                                                        \
-  lu_solve_oz<NC_, NWM_, BTZ>(it, q, count, cus, rkey, ridx, &s_info, PL_, myws, b, lds, xs, pv, bd,          \
-                              bd->jobs() + ms,                                                      \
-                              slots + ms, &s_task)
+    bool ok;
+#define OZ_LU(NC_, NWM_, PL_)                                                                       \
+  ok = lu_solve_oz<NC_, NWM_, BTZ>(it, q, count, cus, rkey, ridx, &s_info, PL_, myws, b, lds, xs, \
+                                   pv, bd, bd->jobs() + ms, slots + ms, &s_task, err)
     if (it.nc == 2) OZ_LU(2, 6, pl2);
     else if (it.nc == 3) OZ_LU(3, 4, pl3);
     else OZ_LU(4, 4, pl4);
 #undef OZ_LU
+    if (!ok) return;
     __syncthreads();
     if (threadIdx.x == 0) {
       if (times) {
@@ -939,9 +965,14 @@ __global__ __launch_bounds__(BTZ) void k_batch_lu_oz(const ozII_batch_item *item
   const int lane = threadIdx.x & 63;
   for (;;) {
     if (threadIdx.x < 64) {
-      int got = -1;
+      int got = -1, seen = -1;
+      uint64_t since = 0;
       while (got < 0) {
-        const bool over = ld_agent(&bd->finished) >= count;
+        const int fin = __builtin_amdgcn_readfirstlane(ld_agent(&bd->finished));
+        const uint64_t now = __builtin_amdgcn_s_memrealtime();
+        since = fin == seen ? since : now;
+        seen = fin;
+        const bool over = fin >= count || now - since > WAIT_TICKS;
         // the open job of the owner with the most work left
         uint32_t best = 0;
         int bs = -1;
@@ -1040,14 +1071,14 @@ size_t batch_board_bytes(int nslot) {
 hipError_t launch_batch_oz(const ozII_batch_item *items, int count, void *board, int nslot,
                           uint64_t *times, int grid, int cus, const DevPlan *pl2,
                           const DevPlan *pl3, const DevPlan *pl4, uint8_t *ws, int64_t slot, int b,
-                          hipStream_t s) {
+                          int *err, hipStream_t s) {
   if (count <= 0) return hipSuccess;
   if (b < 1 || b > 256 || nslot < std::min(count, grid) || grid > cus) return hipErrorInvalidValue;
   static_assert(offsetof(Board, idle) == 4, "the word that k_batch_clear sets");
   hipLaunchKernelGGL(k_batch_clear, dim3(1), dim3(256), 0, s, (int *)board,
                      (int)(sizeof(Board) / 4) + (nslot + 63) / 64 * 128, cus - grid);
   hipLaunchKernelGGL(k_batch_lu_oz, dim3((unsigned)grid), dim3(BTZ), 0, s, items, count,
-                     (Board *)board, nslot, cus, times, pl2, pl3, pl4, ws, slot, b);
+                     (Board *)board, nslot, cus, times, pl2, pl3, pl4, ws, slot, b, err);
   return hipGetLastError();
 }
 }  // namespace ozl

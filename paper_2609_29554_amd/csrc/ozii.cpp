@@ -1765,6 +1765,8 @@ ozII_status ozII_batch_prepare_ex(ozII_handle h, int32_t count, const ozII_batch
   if (!h->batch_queue &&
       (e = dev_alloc(h, (void **)&h->batch_queue, ozl::batch_board_bytes(ncu))) != hipSuccess)
     return fail(h, OZII_ENOMEM, "batch queue allocation failed");
+  if (oz && !h->bar && alloc_words(h) != hipSuccess)
+    return fail(h, OZII_ENOMEM, "batch error word allocation failed");
   if (oz && (size_t)(slot * grid) > h->batch_ws_bytes) {
     if (h->batch_ws) hipFree(h->batch_ws);
     h->batch_ws = nullptr;
@@ -1790,7 +1792,7 @@ ozII_status ozII_batch_run(ozII_handle h, uint64_t *times) {
       h->batch_b > 0
           ? ozl::launch_batch_oz(h->batch, h->batch_count, h->batch_queue, h->batch_grid, times,
                                  h->batch_wgs, h->batch_cus, h->batch_pl[0], h->batch_pl[1], h->batch_pl[2],
-                                 h->batch_ws, h->batch_slot, h->batch_b, h->stream)
+                                 h->batch_ws, h->batch_slot, h->batch_b, h->err, h->stream)
           : ozl::launch_batch(h->batch, h->batch_count, h->batch_queue, times, h->batch_grid,
                               h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "batched LU");
@@ -1811,7 +1813,7 @@ ozII_status ozII_sync_check(ozII_handle h) {
     int v = 0;
     e = hipMemcpy(&v, h->err, sizeof(int), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(h, e, "read error flag");
-    if (v) return fail(h, OZII_EDEVICE, "a grid-wide wait timed out (panel exchange or pipelined solve)");
+    if (v) return fail(h, OZII_EDEVICE, "a grid-wide wait timed out (panel exchange, pipelined solve or batch)");
   }
   return OZII_OK;
 }

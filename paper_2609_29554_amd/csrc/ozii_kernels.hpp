@@ -183,12 +183,13 @@ hipError_t launch_batch(const ozII_batch_item *items, int count, int *queue, uin
 // width b <= 256); plans at K = b for nc = 2, 3, 4 (null for absent formats),
 // scratch of `slot` bytes per workgroup
 // board: batch_board_bytes(nslot) bytes of device memory; ws: nslot slots of
-// scratch, nslot >= min(count, grid); grid: workgroups, at most one per CU (cus)
+// scratch, nslot >= min(count, grid); grid: workgroups, at most one per CU (cus);
+// err: the sticky error word
 size_t batch_board_bytes(int nslot);
 hipError_t launch_batch_oz(const ozII_batch_item *items, int count, void *board, int nslot,
                            uint64_t *times, int grid, int cus, const ozk::DevPlan *pl2,
                            const ozk::DevPlan *pl3, const ozk::DevPlan *pl4, uint8_t *ws,
-                           int64_t slot, int b, hipStream_t s);
+                           int64_t slot, int b, int *err, hipStream_t s);
 
 // LU on limb matrices outside the Ozaki-II product (k_limb_lu.hip): limb q
 // of element (i, j), e = i + j ld, at limb[q plane + e es], its exponent at
