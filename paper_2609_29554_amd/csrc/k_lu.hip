@@ -13,6 +13,7 @@
 
 #include "expansion.hpp"
 #include "ozii_kernels.hpp"
+#include "panel_tags.hpp"
 
 namespace {
 
@@ -29,9 +30,11 @@ namespace {
 // 8-byte accesses.  A line is overwritten two columns later, which its owner
 // reaches only after every workgroup has published the column in between,
 // and a workgroup publishes that after it has read all it needs of the first.
-// Tags grow over all panels of a handle (the base is a device word that
-// k_panel_begin advances), so nothing has to be cleared.  Waits are bounded:
-// a timeout raises the sticky error flag and ends the kernel.
+// Every panel of a handle has tags of its own (panel_tags.hpp; a device word
+// that k_getrf_begin advances, so that replays of a captured factorisation
+// take new ones), so nothing has to be cleared until 2^22 panels have used them
+// up.  Waits are bounded: a timeout raises the sticky error flag and ends the
+// kernel.
 // ---------------------------------------------------------------------------
 constexpr int LINE_WORDS = 16;  // 8-byte words per candidate line
 
@@ -187,11 +190,23 @@ __device__ __forceinline__ int lead_winner(double lead, int nlead, int &w) {
 constexpr int PANEL_NT = 512;  // threads per panel workgroup
 constexpr int PANEL_NW = PANEL_NT - 64;  // of these, the ones that apply the updates
 
-// Before the panels of a factorisation: info, and a fresh range of tags for each
-// (a panel has at most 512 columns).
-__global__ void k_getrf_begin(uint32_t *epoch, uint32_t panels, int32_t *info) {
-  *epoch += 1024u * panels;
-  *info = 0;
+// Before the panels of a factorisation: info, and a fresh range of tags for
+// each; a workgroup, for the time when the exchange words have to be cleared.
+constexpr int BEGIN_NT = 256;
+__global__ __launch_bounds__(BEGIN_NT) void k_getrf_begin(uint32_t *epoch, uint32_t panels,
+                                                          int32_t *info, uint64_t *lines,
+                                                          int64_t line_words, uint64_t *crow,
+                                                          int64_t crow_words) {
+  const ozp::TagRange r = ozp::next_tags(*epoch, panels);
+  __syncthreads();
+  if (r.clear) {
+    for (int64_t i = threadIdx.x; i < line_words; i += BEGIN_NT) lines[i] = 0;
+    for (int64_t i = threadIdx.x; i < crow_words; i += BEGIN_NT) crow[i] = 0;
+  }
+  if (threadIdx.x == 0) {
+    *epoch = r.end;
+    *info = 0;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -244,7 +259,7 @@ __global__ __launch_bounds__(PANEL_NT) void k_panel(double *A, int64_t lda, int6
 
   const int r0 = wg * R;
   const int cnt = r0 < nr ? (nr - r0 < R ? nr - r0 : R) : 0;
-  const uint32_t tag0 = *epoch - 1024u * (uint32_t)panel + 1u;  // tag of column 0
+  const uint32_t tag0 = ozp::panel_tag0(*epoch, (uint32_t)panel);
   auto RW = [&](int r, int c) { return rows + ((size_t)r * kb + c) * NC; };
   auto LINE = [&](int b, int w) { return lines + ((size_t)b * G + w) * LINE_WORDS; };
   auto CROW = [&](int b, int w) { return crow + ((size_t)b * G + w) * kb * NC * 2; };
@@ -1089,8 +1104,11 @@ const void *panel_kernel_ptr(int nc) {
   return (const void *)k_panel<4>;
 }
 
-hipError_t launch_getrf_begin(uint32_t *epoch, int64_t panels, int32_t *info, hipStream_t s) {
-  hipLaunchKernelGGL(k_getrf_begin, dim3(1), dim3(1), 0, s, epoch, (uint32_t)panels, info);
+hipError_t launch_getrf_begin(uint32_t *epoch, int64_t panels, int32_t *info, uint64_t *lines,
+                              uint64_t *crow, int kb, hipStream_t s) {
+  hipLaunchKernelGGL(k_getrf_begin, dim3(1), dim3(BEGIN_NT), 0, s, epoch, (uint32_t)panels, info,
+                     lines, (int64_t)2 * PANEL_MAXG * LINE_WORDS, crow,
+                     (int64_t)(2 * PANEL_MAXG * panel_row_bytes(kb) / 8));
   return hipGetLastError();
 }
 

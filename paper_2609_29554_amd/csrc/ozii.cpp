@@ -721,7 +721,7 @@ ozII_status ensure_panel(ozII_ctx *h, int64_t n, int kb) {
   }
   const int64_t nn = std::max<int64_t>(n, h->panel_n);
   const int kk = std::max(kb, h->panel_kb);
-  const int G = 256;
+  const int G = ozl::PANEL_MAXG;
   hipError_t e = hipSuccess;
   if (!h->bar) e = alloc_words(h);
   if (e == hipSuccess && !h->lines) {
@@ -1446,7 +1446,8 @@ ozII_status ozII_getrf(ozII_handle h, int32_t nc, int64_t n, double *A, int64_t 
     const hipError_t ee = ozl::launch_trsm_lower_unit(nc, L11, lda, A12, lda, kb, nb, st_);
     return ee == hipSuccess ? OZII_OK : hip_fail(h, ee, "trsm");
   };
-  if ((e = ozl::launch_getrf_begin(h->epoch, (n + b - 1) / b, info, s)) != hipSuccess)
+  if ((e = ozl::launch_getrf_begin(h->epoch, (n + b - 1) / b, info, h->lines, h->crow, h->panel_kb,
+                                   s)) != hipSuccess)
     return hip_fail(h, e, "getrf begin");
   bool side_busy = false;
   for (int64_t k = 0; k < n; k += b) {

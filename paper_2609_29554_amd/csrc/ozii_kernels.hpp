@@ -98,11 +98,15 @@ size_t panel_lds_bytes(int nc, int kb, int R, int64_t nr);
 hipError_t panel_max_blocks(int nc, int kb, int R, int64_t nr, int *maxblocks);
 // bytes of a candidate row of up to kb expansions
 size_t panel_row_bytes(int kb);
-// before the panels 0 .. panels-1 of a factorisation: info = 0 and their tags
-hipError_t launch_getrf_begin(uint32_t *epoch, int64_t panels, int32_t *info, hipStream_t s);
-// lines: 2 * G candidate lines of 128 bytes; crow: 2 * G candidate rows; both
-// zeroed once when allocated, as is epoch, the base of the panels' tags; panel:
-// its number in the factorisation
+// workgroups of a panel
+constexpr int PANEL_MAXG = 256;
+// before the panels 0 .. panels-1 of a factorisation: info = 0 and their tags;
+// kb: the columns that crow was allocated for
+hipError_t launch_getrf_begin(uint32_t *epoch, int64_t panels, int32_t *info, uint64_t *lines,
+                              uint64_t *crow, int kb, hipStream_t s);
+// lines: 2 * PANEL_MAXG candidate lines of 128 bytes; crow: 2 * PANEL_MAXG
+// candidate rows; both zeroed when allocated, as is epoch, the panels' tags;
+// panel: its number in the factorisation; G <= PANEL_MAXG
 hipError_t launch_panel(int nc, double *A, int64_t lda, int64_t n, int64_t k, int kb, int R, int G,
                         int64_t *ipiv, int32_t *info, uint64_t *lines, int *err, uint64_t *crow,
                         uint32_t *epoch, int panel, int *perm, int *moved, int *nmoved,

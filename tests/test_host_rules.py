@@ -47,3 +47,28 @@ def test_batch_tasks(tmp_path):
     assert got[(1024, 1)] == 16 * 16 and got[(90, 256)] == (82 * 82 + 511) // 512
     # four systems of order 64, or one of 512, leave most CUs alone
     assert 4 * got[(64, 64)] == 4 and got[(512, 64)] < 64
+
+
+def test_panel_tags_do_not_come_again(tmp_path):
+    """Over more than 2^32 tags: the tags of the panels between two clearings
+    are disjoint ranges of 512, none of them 0."""
+    panels = [1, 7, 1024, 1 << 20, 3, 400000, 65, 999999]
+    body = """
+  uint32_t end = 0;
+  const uint32_t panels[] = {%s};
+  for (int rep = 0; rep < 2000; ++rep) {
+    const uint32_t n = panels[rep %% 8] / (rep < 1000 ? 1 : 7) + 1;
+    const ozp::TagRange r = ozp::next_tags(end, n);
+    end = r.end;
+    std::printf("%%d %%u %%u %%u\\n", r.clear ? 1 : 0, n, ozp::panel_tag0(end, n - 1),
+                ozp::panel_tag0(end, 0));
+  }""" % ", ".join(map(str, panels))
+    rows = _run(tmp_path, "panel_tags.hpp", body)
+    top, clears = 0, 0
+    for clear, n, lowest, highest in rows:
+        if clear:
+            top, clears = 0, clears + 1
+        assert lowest > top and highest == lowest + 1024 * (n - 1)
+        top = highest + 511
+        assert top < 2 ** 32
+    assert clears > 50
