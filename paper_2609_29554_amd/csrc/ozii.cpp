@@ -1545,9 +1545,10 @@ ozII_status ozII_getrs(ozII_handle h, int32_t nc, int64_t n, int64_t nrhs, const
   // one right-hand side, or few enough that all their pipelines run at once:
   // the pipelined solves (same operations per element).  Several of them:
   // measured with 2 to 64, blocked / pipelined, for DD, TD and QD alike
-  // pipelined is 0.84 to 1.04 times as fast up to n = 256, one block of the
-  // blocked solve, and 1.05 to 1.7 times from n = 288 on (QD n = 256 with 16
-  // 1.63 / 1.69 ms, n = 288 2.18 / 1.91, n = 1000 8.28 / 6.53).
+  // pipelined is 0.8 to 1.03 times as fast up to n = 256, one block of the
+  // blocked solve, and from n = 288 on 1.02 to 1.55 times (QD n = 256 with 16
+  // 1.55 / 1.69 ms, n = 288 2.10 / 1.91, n = 1000 7.92 / 6.54), but 0.93 to 0.96
+  // for DD with 64.
   // The counters of one right-hand side are the handle's; those of several are
   // the stream's, and without them the blocked solve, which has none, runs.
   uint32_t *sync = nullptr;
