@@ -1455,18 +1455,23 @@ ozII_status ozII_getrf(ozII_handle h, int32_t nc, int64_t n, double *A, int64_t 
     const int64_t nr = n - k;
     // panel geometry: G co-resident workgroups of R rows each.  Every
     // workgroup reads every candidate line, so fewer, taller workgroups make
-    // the exchange of a column cheaper, and below about 20 rows the update of
-    // a workgroup's rows hides behind it: measured, getrf with 8 / 16 / 32 /
-    // 64 / 96 / 128 workgroups: DD n = 130 814 / 817 / 831 / 860 / 894 / 942
-    // us, DD 512 2.79 / 2.63 / 2.68 / 2.86 / 2.95 / 2.97 ms, QD 1024 12.8 /
-    // 12.6 / 12.5 / 12.0 / 12.4 / 12.7 ms, QD 2048 (64 / 96 / 128) 25.9 / 25.7 /
-    // 26.2 ms.  More workgroups where the rows do not fit in LDS (the kernel's
-    // static LDS is below 512 bytes).
+    // the exchange of a column cheaper, as long as the update of a workgroup's
+    // rows (up to 1700 elements a column) hides behind it.  Measured, getrf with
+    // 5 / 7 / 10 / 13 / 16 / 20 / 26 rows a workgroup, ms: b = 64 DD n = 1000 5.76 /
+    // 5.70 / 5.61 / 5.53 / 5.47 / 5.42 / 5.48, QD 12.3 / 12.1 / 12.0 / 11.8 / 11.7 /
+    // 11.6 / 11.6; b = 128 TD 9.28 / 9.12 / 8.95 / 9.08 / 9.56 / 9.99 / 11.1, QD n =
+    // 2000 24.4 / 24.3 / 24.0 / 23.8 / 23.8 / 24.2 / 26.0; b = 256 DD 5.06 / 4.99 /
+    // 5.06 / 5.39 / 5.83 / 6.39 / 7.37, TD 9.26 / 9.30 / 9.95 / 10.7 / 12.3 / 13.4;
+    // b = 512 DD 5.92 / 6.11 / 6.69 / 7.61 / 8.79.  (20 rows at b = 256 made TD
+    // slower than 128 workgroups with an arrival counter, 11.8.)  More workgroups
+    // where the rows do not fit in LDS (the kernel's static LDS is below 512
+    // bytes).
     int G = 0, R = 0;
     // Up to 32 rows are one workgroup's, launched alone: n = b = 32 DD 151 -> 124
     // us, QD 295 -> 252; n = 130, b = 32 (last panel 2 rows) 826 -> 810.
-    const int G20 = nr <= 32 ? 1 : (int)std::min<int64_t>(128, std::max<int64_t>(8, (nr + 19) / 20));
-    for (int G0 : {G20, 128, 256}) {
+    const int rows = std::max(5, std::min(20, 1700 / kb));
+    const int Gr = nr <= 32 ? 1 : (int)std::min<int64_t>(128, std::max<int64_t>(8, (nr + rows - 1) / rows));
+    for (int G0 : {Gr, 128, 256}) {
       int g = G0, r = 0, maxb = 0;
       bool ok = false;
       for (;;) {

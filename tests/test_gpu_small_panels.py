@@ -35,3 +35,18 @@ def test_small_panels(nc, n, b, kind):
         assert int(to_host(dinfo)[0]) == info
         assert np.array_equal(to_host(dip), ipiv)
         assert np.array_equal(to_host(dA), LU)
+
+
+@pytest.mark.parametrize("nc,n,b", [(2, 100, 85), (2, 100, 86), (3, 290, 256), (2, 345, 340),
+                                    (2, 345, 341), (4, 150, 130)])
+def test_wide_panels(nc, n, b):
+    """Widths at which the rows of a workgroup change, and few rows a workgroup."""
+    note(f"wide panel nc={nc} n={n} b={b}")
+    rng = np.random.default_rng(n + b)
+    A = W.graded(n, nc, 20.0, rng)
+    want, ipiv, info, _ = O.getrf(A, b, O.METHOD_OZAKI)
+    dA = to_dev(A)
+    ip, inf = ctx().getrf(dA, block=b)
+    ctx().sync_check()
+    assert int(inf) == info and np.array_equal(to_host(ip), ipiv)
+    assert np.array_equal(to_host(dA), want)
