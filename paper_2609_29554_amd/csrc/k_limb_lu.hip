@@ -448,20 +448,24 @@ __global__ __launch_bounds__(256) void k_lrest(LimbMat LU, LimbMat X, int nl, in
   }
 }
 
-// elementwise a op b on vectors (element t at index t): 0 add, 1 sub, 2 mul, 3 div
+// elementwise a op b on vectors (element t at index t): CL = 0 for 0 add, 1 sub
+// and 3 div; CL > 0: 2 mul on the matrix cores, from one limb on.  The products
+// apart, since their registers and LDS leave the other operations fewer
+// wavefronts and the division's do so to them: 200000 products of 1 / 2 / 3 / 16
+// limbs in one kernel 118 / 126 / 132 / 128 us, apart 102 for all (the loop apart
+// 103 / 108 / 115); sums of 33 limbs 169, 156.
 template <int CL>
 __global__ __launch_bounds__(256) void k_larith(int op, int nl, int64_t cnt, LimbMat A, LimbMat B,
                                                 LimbMat C) {
-  __shared__ __attribute__((aligned(16))) uint8_t sbuf[WPB][lfp::PROD_LDS];
+  __shared__ __attribute__((aligned(16))) uint8_t sbuf[WPB][CL > 0 ? lfp::PROD_LDS : 16];
   uint8_t *buf = sbuf[wave_in_block()];
-  lfp::prod_init(buf);
+  if (CL > 0) lfp::prod_init(buf);
   for (int64_t t = wave_global(); t < cnt; t += waves_total()) {
     const WF a = ld_el(A, t, 0, nl), b = ld_el(B, t, 0, nl);
     WF r;
-    if (op == 0) r = lfp::add(a, b, 0u, nl);
-    else if (op == 1) r = lfp::add(a, b, 1u, nl);
-    else if (op == 2) r = lfp::mul<CL>(a, b, nl, buf);
-    else r = lfp::div(a, b, nl);
+    if constexpr (CL > 0) r = lfp::mul<CL>(a, b, nl, buf);
+    else if (op == 3) r = lfp::div(a, b, nl);
+    else r = lfp::add(a, b, (uint32_t)op, nl);
     st_el(C, t, 0, nl, r);
   }
 }
@@ -517,7 +521,6 @@ __global__ void k_lfill_i32(int32_t *p, int32_t v, int count) {
   if (i < count) p[i] = v;
 }
 
-// workgroups for `waves` independent wavefront tasks
 // The product form of nl limbs: the loop below LOOP_LIMBS, else the matrix
 // cores with the tiles of up to CL limbs.  200000 products of 2 / 4 / 8 / 16
 // limbs: loop 119 / 133 / 165 / 235 us, matrix cores 120 / 120 / 121 / 125 us;
@@ -533,6 +536,7 @@ constexpr int LOOP_LIMBS = 4;
     else { constexpr int CL = 64; __VA_ARGS__; }                     \
   } while (0)
 
+// workgroups for `waves` independent wavefront tasks
 int grid_for(int64_t waves, int64_t cap = 8192) {
   int64_t g = (waves + WPB - 1) / WPB;
   if (g < 1) g = 1;
@@ -643,8 +647,12 @@ hipError_t launch_lgetrs(LimbMat LU, int nl, int64_t n, const int64_t *ipiv, Lim
 hipError_t launch_larith(int op, int nl, int64_t cnt, LimbMat A, LimbMat B, LimbMat C,
                          hipStream_t s) {
   if (cnt <= 0) return hipSuccess;
-  OZ_BY_CL(nl, hipLaunchKernelGGL(k_larith<CL>, dim3(grid_for(cnt)), dim3(256), 0, s, op, nl, cnt, A,
-                                  B, C));
+  const dim3 g(grid_for(cnt));
+  if (op == 2)
+    OZ_BY_CL(std::max(nl, LOOP_LIMBS),
+             hipLaunchKernelGGL(k_larith<CL>, g, dim3(256), 0, s, op, nl, cnt, A, B, C));
+  else
+    hipLaunchKernelGGL(k_larith<0>, g, dim3(256), 0, s, op, nl, cnt, A, B, C);
   return hipGetLastError();
 }
 
