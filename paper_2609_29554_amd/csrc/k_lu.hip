@@ -683,16 +683,17 @@ __global__ __launch_bounds__(256) void k_trsm_lower_unit(const double *Lp, int64
 // k_trsm_lower_unit.  UPPER: the same with the rows counted from the last
 // and each value divided by its diagonal entry once its updates are in
 // (x_h <- x_h / u_hh, then x_i -= u_ih x_h, h descending).  Bound by the chain
-// of one multiply-subtract (UPPER: and a division) per row.  The rows of
-// earlier wavefronts and the own ones in a loop each: in one loop with the
-// factor entries of several steps in flight, shifted from step to step, every
-// step waited for its newest load.  One loop / two, us for 256 rows: unit lower
-// DD 153 / 124, TD 287 / 256, QD 344 / 304; UPPER DD 316 / 283, TD 898 / 872, QD
-// 1255 / 1216 (QD with a barrier and a division per row 1490).
+// of one multiply-subtract (UPPER: and a division) per row.  A loop each for the
+// rows of earlier wavefronts and the own ones, unrolled over the factor entries
+// in flight, whose loads take no branch: in one loop, with the entries shifted
+// from step to step, every step waited for its newest load.  That / this, us:
+// unit lower 32 rows DD 18.7 / 16.1, QD 50.9 / 45.8; 100 rows DD 61 / 47, QD 140 /
+// 125; UPPER 32 rows DD 42 / 37, QD 182 / 164; 100 rows DD 132 / 121, QD 549 / 527.
+// 256 QD rows with a barrier and a division per row took 1490, UPPER now 1216.
 template <int NC, int WPC, bool UPPER>
 __global__ __launch_bounds__(256) void k_trsm_w(const double *Fp, int64_t lda, double *Xp,
                                                 int64_t ldx, int kb, int64_t ncols) {
-  constexpr int CPB = 4 / WPC;
+  constexpr int CPB = 4 / WPC, PF = NC == 2 ? 4 : 1;
   __shared__ double xs[CPB][WPC > 1 ? 64 * (WPC - 1) : 1][NC];
   __shared__ int done[CPB];
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
@@ -705,55 +706,65 @@ __global__ __launch_bounds__(256) void k_trsm_w(const double *Fp, int64_t lda, d
   const bool mine = i < kb;
   auto row = [&](int p) { return UPPER ? kb - 1 - p : p; };
   auto F = [&](int p, int h) { return Fp + (row(p) + (int64_t)row(h) * lda) * NC; };
-  double x[NC] = {}, d[NC] = {}, f[NC] = {};
+  double x[NC] = {}, d[NC] = {}, f[PF][NC] = {};
   if (mine) {
     ozx::load<NC>(Xp + (row(i) + c * ldx) * NC, x);
     if (UPPER) ozx::load<NC>(F(i, i), d);
   }
   const int h0 = 64 * part, h1 = kb < h0 + 64 ? kb : h0 + 64;
   if (h0 >= kb) return;
-  // the factor entry of the next step is loaded while this one computes
-  if (mine && i > 0) ozx::load<NC>(F(i, 0), f);
-  for (int h = 0; h < h0; ++h) {
-    double fn[NC] = {}, y[NC], o[NC];
-    if (mine && h + 1 < i) ozx::load<NC>(F(i, h + 1), fn);
-    // published by an earlier wavefront of this column (it never waits for
-    // this one, so this ends)
-    while (__hip_atomic_load(&done[cc], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= h)
-      __builtin_amdgcn_s_sleep(1);
+  // the factor entries of the next PF steps are in flight while one computes;
+  // the load of step h has no use past the diagonal and then reads any entry
+  auto fetch = [&](int h, double (&to)[NC]) { ozx::load<NC>(mine && h < i ? F(i, h) : Fp, to); };
 #pragma unroll
-    for (int q = 0; q < NC; ++q) y[q] = xs[cc][h][q];
-    if (mine) {
-      ozx::fms<NC>(x, f, y, o);
+  for (int t = 0; t < PF; ++t) fetch(t, f[t]);
+  for (int hb = 0; hb < h0; hb += PF) {
 #pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        x[q] = o[q];
-        f[q] = fn[q];
+    for (int t = 0; t < PF; ++t) {
+      const int h = hb + t;
+      double y[NC], o[NC], fh[NC];
+#pragma unroll
+      for (int q = 0; q < NC; ++q) fh[q] = f[t][q];
+      fetch(h + PF, f[t]);
+      // published by an earlier wavefront of this column (it never waits for
+      // this one, so this ends)
+      while (__hip_atomic_load(&done[cc], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= h)
+        __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) y[q] = xs[cc][h][q];
+      if (mine) {
+        ozx::fms<NC>(x, fh, y, o);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) x[q] = o[q];
       }
     }
   }
-  for (int h = h0; h < h1; ++h) {
-    double fn[NC] = {}, y[NC], o[NC];
-    if (mine && h + 1 < i) ozx::load<NC>(F(i, h + 1), fn);
-    if (UPPER) {
-      ozx::div<NC>(x, d, o);
+  for (int hb = h0; hb < h1; hb += PF) {
 #pragma unroll
-      for (int q = 0; q < NC; ++q) x[q] = lane == h - h0 ? o[q] : x[q];
-    }
-    // position h is final
+    for (int t = 0; t < PF; ++t) {
+      const int h = hb + t;
+      if (PF > 1 && h >= h1) break;
+      double y[NC], o[NC], fh[NC];
 #pragma unroll
-    for (int q = 0; q < NC; ++q) y[q] = readlane_f64(x[q], h - h0);
-    if (part + 1 < WPC && lane == h - h0) {
+      for (int q = 0; q < NC; ++q) fh[q] = f[t][q];
+      fetch(h + PF, f[t]);
+      if (UPPER) {
+        ozx::div<NC>(x, d, o);
 #pragma unroll
-      for (int q = 0; q < NC; ++q) xs[cc][h][q] = y[q];
-      __hip_atomic_store(&done[cc], h + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    if (mine && i > h) {
-      ozx::fms<NC>(x, f, y, o);
+        for (int q = 0; q < NC; ++q) x[q] = lane == h - h0 ? o[q] : x[q];
+      }
+      // position h is final
 #pragma unroll
-      for (int q = 0; q < NC; ++q) {
-        x[q] = o[q];
-        f[q] = fn[q];
+      for (int q = 0; q < NC; ++q) y[q] = readlane_f64(x[q], h - h0);
+      if (part + 1 < WPC && lane == h - h0) {
+#pragma unroll
+        for (int q = 0; q < NC; ++q) xs[cc][h][q] = y[q];
+        __hip_atomic_store(&done[cc], h + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      if (mine && i > h) {
+        ozx::fms<NC>(x, fh, y, o);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) x[q] = o[q];
       }
     }
   }

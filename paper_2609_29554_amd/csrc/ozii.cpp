@@ -1550,10 +1550,10 @@ ozII_status ozII_getrs(ozII_handle h, int32_t nc, int64_t n, int64_t nrhs, const
   // one right-hand side, or few enough that all their pipelines run at once:
   // the pipelined solves (same operations per element).  Several of them:
   // measured with 2 to 64, blocked / pipelined, for DD, TD and QD alike
-  // pipelined is 0.8 to 1.03 times as fast up to n = 256, one block of the
-  // blocked solve, and from n = 288 on 1.02 to 1.55 times (QD n = 256 with 16
-  // 1.55 / 1.69 ms, n = 288 2.10 / 1.91, n = 1000 7.92 / 6.54), but 0.93 to 0.96
-  // for DD with 64.
+  // pipelined is 0.7 to 0.97 times as fast up to n = 256, one block of the
+  // blocked solve, and from n = 288 on 0.99 to 1.47 times (QD n = 256 with 16
+  // 1.52 / 1.69 ms, n = 288 2.05 / 1.91, n = 1000 7.61 / 6.55), but 0.91 to 0.98
+  // for DD with 64 up to n = 512.
   // The counters of one right-hand side are the handle's; those of several are
   // the stream's, and without them the blocked solve, which has none, runs.
   uint32_t *sync = nullptr;
