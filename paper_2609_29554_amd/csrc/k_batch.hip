@@ -437,8 +437,9 @@ __device__ __forceinline__ void fms_sweep(int32_t mr, int32_t mc, W where) {
 //   (S4) every wavefront takes 64 x 64 tiles of the (group, modulus)
 //        products: 4 x 4 MFMA 16x16x64 fragments, operands straight from
 //        the scratch planes, the t-bytes stored as 4-byte column runs;
-//   (S5)+(S6) one element per thread: consume_element_b and the expansion
-//        subtraction.
+//   (S5)+(S6) every wavefront takes 64 consecutive elements of a column
+//        through the matrix-core CRT (crt_group_mx), one element per lane for
+//        the rounding and the expansion subtraction.
 // Per element the operations are those of ozII_getrf with the same b and
 // method = Ozaki-II on the INT8 back-end, so the factors agree bit for bit.
 //
@@ -453,8 +454,8 @@ struct OzUpdate {
   const DevPlan *pl;
   int32_t *ea, *eb;
   uint8_t *pa, *pb, *tpl;
-  __device__ __forceinline__ OzUpdate(double *A_, int64_t n_, int64_t k0_, int64_t k1_, const DevPlan *pl_,
-                                      uint8_t *ws)
+  __device__ __forceinline__ OzUpdate(double *A_, int64_t n_, int64_t k0_, int64_t k1_,
+                                      const DevPlan *pl_, uint8_t *ws)
       : A(A_), n(n_), k0(k0_), k1(k1_), K(k1_ - k0_), m2(n_ - k1_), pl(pl_) {
     Mp = (m2 + 63) & ~(int64_t)63;
     Kp = (K + 63) & ~(int64_t)63;
@@ -473,7 +474,8 @@ struct OzUpdate {
     const int64_t ld = n, kb = k1;
     for (int64_t k = k0; k + 1 < k1; ++k) {
       fms_sweep<NC, NT>((int32_t)(k1 - k - 1), (int32_t)(c1 - c0),
-                        [&](int32_t i, int32_t c, double *&pa_, const double *&pl_, const double *&pu_) {
+                        [&](int32_t i, int32_t c, double *&pa_, const double *&pl_,
+                            const double *&pu_) {
                           double *col = P + (kb + c0 + c) * ld * NC;
                           pa_ = col + (k + 1 + i) * NC;
                           pl_ = P + (k + 1 + i + k * ld) * NC;
@@ -832,7 +834,8 @@ __device__ __forceinline__ bool lu_solve_oz(const ozII_batch_item &it, int item,
         const bool zero = pivot_column<NC, NT>(it, j, rkey, ridx, s_info);
         zeros |= (uint32_t)zero << ((j - j0) & 31);
         fms_sweep<NC, NT>(zero ? 0 : (int32_t)(n - j - 1), (int32_t)(j1 - j - 1),
-                          [&](int32_t i, int32_t c, double *&pa, const double *&pl_, const double *&pu) {
+                          [&](int32_t i, int32_t c, double *&pa, const double *&pl_,
+                              const double *&pu) {
                             pa = E(j + 1 + i, j + 1 + c);
                             pl_ = E(j + 1 + i, j);
                             pu = E(j, j + 1 + c);
@@ -843,7 +846,8 @@ __device__ __forceinline__ bool lu_solve_oz(const ozII_batch_item &it, int item,
       // the sub-block's rows of the other columns step by step, then the rest
       for (int64_t k = j0; k + 1 < j1; ++k) {
         fms_sweep<NC, NT>((zeros >> (k - j0)) & 1u ? 0 : (int32_t)(j1 - k - 1), (int32_t)(k1 - j1),
-                          [&](int32_t i, int32_t c, double *&pa, const double *&pl_, const double *&pu) {
+                          [&](int32_t i, int32_t c, double *&pa, const double *&pl_,
+                              const double *&pu) {
                             pa = E(k + 1 + i, j1 + c);
                             pl_ = E(k + 1 + i, k);
                             pu = E(k, j1 + c);

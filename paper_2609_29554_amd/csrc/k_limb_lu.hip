@@ -184,8 +184,7 @@ __global__ __launch_bounds__(1024) void k_lpiv(LimbMat A, int nl, int64_t j, int
   br = srow[l & (FIN_WAVES - 1)];
   bc = scnt[l & (FIN_WAVES - 1)];
   over(FIN_WAVES);
-  // rows fit 32 bits (the exponents and limbs of a column would not fit the
-  // memory otherwise)
+  // (rows fit 32 bits: the limbs of a longer column would not fit the memory)
   // zeros tie only with zeros: the lowest row
   if (bt != 0 && bc > 1) {
     __syncthreads();
@@ -553,8 +552,8 @@ hipError_t launch_lpack(LimbMat A, LimbMat P, int nl, int64_t i0, int64_t rows, 
   for (int64_t c = 0; c < w; c += 65535) {
     LimbMat Q = P;
     Q.limb += c * P.ld * P.es;
-    hipLaunchKernelGGL(k_lpack, dim3((unsigned)((rows + 63) / 64), (unsigned)std::min<int64_t>(65535, w - c)),
-                       dim3(256), 0, s, A, Q, nl, i0, rows, c0 + c, unpack);
+    const dim3 g((unsigned)((rows + 63) / 64), (unsigned)std::min<int64_t>(65535, w - c));
+    hipLaunchKernelGGL(k_lpack, g, dim3(256), 0, s, A, Q, nl, i0, rows, c0 + c, unpack);
   }
   return hipGetLastError();
 }

@@ -822,12 +822,15 @@ hipError_t launch_consumer_limbs(const void *tpl, int tbytes, int64_t Mp, int64_
 
 // One wavefront per element costs 0.2 ns an element whatever nl; a thread per
 // element costs less than that for few limbs, but walks its words one by one.
-// Measured (whole product, us, separate kernels / one pass), 640 x 640 x 64 and
-// 40 x 30 x 40: mode 0  nl 4: 100 / 173, 35.2 / 34.5   nl 16: 305 / 362, 80 / 70
-// nl 32: 653 / 655, 144 / 119   nl 49: 1050 / 1037, 217 / 181; mode 1  nl 4:
-// 131 / 245, 52.4 / 46.8   nl 16: 422 / 457, 117 / 84   nl 32: 886 / 770,
-// 204 / 134.  The break-even counts of elements between the two sizes grow
-// about as nl^2.
+// Measured (whole product, us, separate kernels / one pass), 40 x 30 x 40, 200 x
+// 180 x 64, 400 x 350 x 64 and 800 x 700 x 64: mode 0  nl 4: 36 / 36, 44 / 47, 70 /
+// 93, 136 / 231   nl 12: 63 / 57, 84 / 83, 136 / 150, 308 / 379   nl 24: 109 / 93,
+// 146 / 129, 252 / 250, 649 / 667   nl 40: 180 / 150, 232 / 198, 436 / 409, 1137 /
+// 1088; mode 1  nl 4: 47 / 41, 55 / 57, 86 / 116, 171 / 307   nl 12: 84 / 62, 112 /
+// 91, 175 / 172, 415 / 462   nl 24: 148 / 99, 200 / 137, 324 / 271, 874 / 757   nl
+// 40: 244 / 158, 320 / 206, 574 / 439, 1538 / 1185.  The break-even counts of
+// elements grow about as nl^2; the line leaves up to 16 % to the other side (mode
+// 1, nl 20 to 31, more than half a million elements).
 bool limb_finish_fits(int nl, int nwords, int64_t M, int64_t N, int mode) {
   if (nl > 64 || nwords > 256) return false;
   return nl >= 32 || (double)M * (double)N <= (mode ? 768.0 : 256.0) * nl * nl;
@@ -838,7 +841,7 @@ hipError_t launch_limb_finish(const uint32_t *cw, int nwords, int64_t M, int64_t
                               int mode, uint64_t *climb, int32_t *cexp, uint8_t *csign, int64_t ldc,
                               int64_t planec, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  // at most 49.4 KiB (nl 64, 256 words)
+  // at most 48.6 KiB (nl 64, 256 words)
   const size_t lds = (size_t)FE * ((nlimb | 1) * 8 + 8 + (nwords | 1) * 4);
   hipLaunchKernelGGL(k_limb_finish, dim3((unsigned)((M + FE - 1) / FE), (unsigned)N), dim3(256),
                      (unsigned)lds, s, cw, M * N, nwords, M, ea, eb, w, g0, Q, nlimb, mode, climb, cexp,

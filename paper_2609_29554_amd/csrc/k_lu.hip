@@ -1166,8 +1166,8 @@ hipError_t launch_laswp(int nc, double *A, int64_t lda, int64_t k, int64_t c0, i
 }
 
 template <int NC>
-static void trsm_l(int kb, dim3 g, hipStream_t s, const double *L, int64_t lda, double *X,
-                   int64_t ldx, int64_t ncols) {
+static void trsm_l(int kb, hipStream_t s, const double *L, int64_t lda, double *X, int64_t ldx,
+                   int64_t ncols) {
   if (kb <= 64)
     hipLaunchKernelGGL((k_trsm_w<NC, 1, false>), dim3((unsigned)((ncols + 3) / 4)), dim3(256),
                        0, s, L, lda, X, ldx, kb, ncols);
@@ -1178,18 +1178,17 @@ static void trsm_l(int kb, dim3 g, hipStream_t s, const double *L, int64_t lda, 
     hipLaunchKernelGGL((k_trsm_w<NC, 4, false>), dim3((unsigned)ncols), dim3(256), 0, s, L,
                        lda, X, ldx, kb, ncols);
   else
-    hipLaunchKernelGGL((k_trsm_lower_unit<NC, 1, 2>), g, dim3(256), 0, s, L, lda, X, ldx, kb, ncols);
+    hipLaunchKernelGGL((k_trsm_lower_unit<NC, 1, 2>), dim3((unsigned)ncols), dim3(256), 0, s, L, lda,
+                       X, ldx, kb, ncols);
 }
 
 hipError_t launch_trsm_lower_unit(int nc, const double *L, int64_t lda, double *X, int64_t ldx,
                                   int kb, int64_t ncols, hipStream_t s) {
   if (ncols <= 0 || kb <= 0) return hipSuccess;
   if (kb > 512) return hipErrorInvalidValue;
-  const int cpb = kb <= 256 ? 2 : 1;
-  dim3 g((unsigned)((ncols + cpb - 1) / cpb));
-  if (nc == 2) trsm_l<2>(kb, g, s, L, lda, X, ldx, ncols);
-  else if (nc == 3) trsm_l<3>(kb, g, s, L, lda, X, ldx, ncols);
-  else trsm_l<4>(kb, g, s, L, lda, X, ldx, ncols);
+  if (nc == 2) trsm_l<2>(kb, s, L, lda, X, ldx, ncols);
+  else if (nc == 3) trsm_l<3>(kb, s, L, lda, X, ldx, ncols);
+  else trsm_l<4>(kb, s, L, lda, X, ldx, ncols);
   return hipGetLastError();
 }
 

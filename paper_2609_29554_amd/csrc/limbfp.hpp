@@ -21,8 +21,9 @@
 // The includer provides LFP_FN and the cross-lane primitives lane_id,
 // ballot, readlane64 (wave-uniform lane), shfl64 (any lane), up1_64 and
 // up1_32 (from lane l-1, 0 into lane 0), dn1_64 (from lane l+1, 0 into lane
-// 63), lane_bit (a lane's bit of a uniform mask), rot1_64 (from lane (l-1) mod 64), addc32 (32-bit add with carry),
-// align_bits (funnel shift), mfma_bytes and lds_order.
+// 63), lane_bit (a lane's bit of a uniform mask), rot1_64 (from lane (l-1) mod
+// 64), addc32 (32-bit add with carry), align_bits (funnel shift), mfma_bytes
+// and lds_order.
 // Every function must be called by all 64 lanes of a converged wavefront;
 // branches below depend on wave-uniform values only.
 #pragma once

@@ -345,8 +345,9 @@ int64_t roundup(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 // Scratch of one stream for the solves that callers may overlap (getrs with
 // several right-hand sides, getrs_limbs): calls on different streams of a
 // handle may run at once, those on one stream follow each other.  Captured
-// calls use none, since their graphs may be replayed on any stream.  A handle keeps it for up to MAX_SOLVES streams, until it is
-// destroyed; on further streams the solves work without.
+// calls use none, since their graphs may be replayed on any stream.  A handle
+// keeps it for up to MAX_SOLVES streams, until it is destroyed; on further
+// streams the solves work without.
 struct SolveScratch {
   hipStream_t stream = nullptr;
   uint32_t *sync = nullptr;   // counters of the pipelined solves
@@ -1470,7 +1471,8 @@ ozII_status ozII_getrf(ozII_handle h, int32_t nc, int64_t n, double *A, int64_t 
     // Up to 32 rows are one workgroup's, launched alone: n = b = 32 DD 151 -> 124
     // us, QD 295 -> 252; n = 130, b = 32 (last panel 2 rows) 826 -> 810.
     const int rows = std::max(5, std::min(20, 1700 / kb));
-    const int Gr = nr <= 32 ? 1 : (int)std::min<int64_t>(128, std::max<int64_t>(8, (nr + rows - 1) / rows));
+    const int Gr =
+        nr <= 32 ? 1 : (int)std::min<int64_t>(128, std::max<int64_t>(8, (nr + rows - 1) / rows));
     for (int G0 : {Gr, 128, 256}) {
       int g = G0, r = 0, maxb = 0;
       bool ok = false;

@@ -45,7 +45,8 @@ __device__ __forceinline__ int32_t block_exponents(F f, bool rowwise, int64_t o0
   }
   // partial maxima per wavefront: RB of them row-wise, 64 / G (or one) column-wise
   const int per = rowwise ? RB : (G < 64 ? 64 / G : 1);
-  if (rowwise ? lane < RB : lane % (64 / per) == 0) sm[wv * per + (rowwise ? lane : lane * per / 64)] = best;
+  if (rowwise ? lane < RB : lane % (64 / per) == 0)
+    sm[wv * per + (rowwise ? lane : lane * per / 64)] = best;
   __syncthreads();
   if (t < RB) {
     if (rowwise) {
