@@ -242,7 +242,7 @@ ozII_status ozII_gemm_limbs_stages(ozII_handle h, int32_t mode, int32_t nlimb, i
  * (no memory, or a captured call that would have to allocate it) the panel
  * works on A's planes, slower and with the same results.  A buffer that a
  * captured call used stays allocated until ozII_destroy, also when a larger
- * factorisation takes a larger one; captured calls hold at most 9.
+ * factorisation takes a larger one; captured calls hold at most 8.
  * Errors: OZII_EINVAL (bad sizes, null pointers, bad descriptor, nlimb outside
  * 1..64, unknown method), OZII_EUNSUPPORTED (a back-end other than INT8,
  * or a plan beyond the compiled sizes), OZII_ENOMEM, OZII_EHIP. */

@@ -1800,8 +1800,9 @@ ozII_status ozII_batch_run(ozII_handle h, uint64_t *times) {
   hipError_t e =
       h->batch_b > 0
           ? ozl::launch_batch_oz(h->batch, h->batch_count, h->batch_queue, h->batch_grid, times,
-                                 h->batch_wgs, h->batch_cus, h->batch_pl[0], h->batch_pl[1], h->batch_pl[2],
-                                 h->batch_ws, h->batch_slot, h->batch_b, h->err, h->stream)
+                                 h->batch_wgs, h->batch_cus, h->batch_pl[0], h->batch_pl[1],
+                                 h->batch_pl[2], h->batch_ws, h->batch_slot, h->batch_b, h->err,
+                                 h->stream)
           : ozl::launch_batch(h->batch, h->batch_count, h->batch_queue, times, h->batch_grid,
                               h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "batched LU");
@@ -1822,7 +1823,9 @@ ozII_status ozII_sync_check(ozII_handle h) {
     int v = 0;
     e = hipMemcpy(&v, h->err, sizeof(int), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(h, e, "read error flag");
-    if (v) return fail(h, OZII_EDEVICE, "a grid-wide wait timed out (panel exchange, pipelined solve or batch)");
+    if (v)
+      return fail(h, OZII_EDEVICE,
+                  "a grid-wide wait timed out (panel exchange, pipelined solve or batch)");
   }
   return OZII_OK;
 }

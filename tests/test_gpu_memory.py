@@ -39,7 +39,10 @@ def test_panel_leaf_makes_room():
             assert int(info) == 1
             torch.cuda.empty_cache()
             free, _ = torch.cuda.mem_get_info()
-            hog = torch.empty(free - spare, dtype=torch.uint8, device="cuda")
+            try:
+                hog = torch.empty(free - spare, dtype=torch.uint8, device="cuda")
+            except torch.OutOfMemoryError:
+                pytest.skip("the free memory cannot be taken in one piece")
             free, _ = torch.cuda.mem_get_info()
             note(f"{free} bytes left, the product takes {ws_bytes}")
             assert free < ws_bytes
