@@ -50,3 +50,33 @@ def test_wide_panels(nc, n, b):
     ctx().sync_check()
     assert int(inf) == info and np.array_equal(to_host(ip), ipiv)
     assert np.array_equal(to_host(dA), want)
+
+
+def test_tags_start_over():
+    """Refused factorisations of order 2^20, b = 1, use up a quarter of the
+    panels' tags each, so that the words are cleared between the others."""
+    import ctypes as C
+    import torch
+    import paper_2609_29554_amd as Z
+    rng = np.random.default_rng(11)
+    c = Z.Context(0)
+    cases = []
+    for nc, n, b in ((2, 150, 64), (4, 70, 32)):
+        A = W.graded(n, nc, 20.0, rng)
+        cases.append((to_dev(A), b) + O.getrf(A, b, O.METHOD_OZAKI)[:3])
+    small = torch.zeros(16, dtype=torch.float64, device="cuda")
+    ipiv = torch.zeros(16, dtype=torch.int64, device="cuda")
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
+    o = Z.make_opts(block=1, method=Z.METHOD_NAIVE)
+    for rep in range(6):
+        note(f"tags start over rep={rep}")
+        for dA, b, want, ip, inf in cases:
+            X = dA.clone()
+            p, i = c.getrf(X, block=b)
+            c.sync_check()
+            assert int(i) == inf and np.array_equal(to_host(p), ip)
+            assert np.array_equal(to_host(X), want)
+        st = Z.lib().ozII_getrf(c._h, 2, 1 << 20, small.data_ptr(), 1 << 20, ipiv.data_ptr(),
+                                info.data_ptr(), C.byref(o))
+        assert st == Z.EUNSUPPORTED   # no panel of so many rows; nothing is factored
+    c.close()
