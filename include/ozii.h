@@ -22,7 +22,8 @@
  * on one stream, or the caller orders the streams.  ozII_getrs with two or
  * more right-hand sides, ozII_getrs_limbs and ozII_limbs_arith need no such
  * order: with separate operands they may overlap other calls of the handle on
- * other streams.
+ * other streams.  The handle knows streams by their address: destroy one only
+ * when the calls on it have ended.
  */
 #ifndef OZII_H
 #define OZII_H
